@@ -1117,6 +1117,13 @@ std::string occ_attr(const LaneMap& M, const Schedule& S = Schedule()) {
   return occ > 0 ? "__attribute__((amdgpu_waves_per_eu(" + std::to_string(occ) + "))) " : std::string();
 }
 
+// Between two passes (phases) of a sender walk: the wave reads back the gy words it stored itself in the pass before.
+// Writer and reader are the same wave, so workgroup scope is enough (the CU's vector L1 is written through and shared by
+// the workgroup): a wait for the stores.  An agent-scope fence writes the XCD's whole L2 back once per wave and pass and
+// the loads then miss the L1.  conv_backward on a 3 000-node graph of degree 30, one MI355X: 65 channels 759 -> 221 us
+// (fp32), 584 -> 328 us (fp64); 192 channels 805 -> 402 us (fp32), 952 -> 740 us (fp64).
+const char* const kWaveRereads = "__builtin_amdgcn_fence(__ATOMIC_ACQ_REL, \"workgroup\");";
+
 // Common head of every kernel: lane ids and the wave's global index.
 // xcd_blocks: workgroups are handed to the 8 XCDs round-robin (workgroup b runs on XCD b % 8, each XCD with an L2
 // of its own).  The convolution kernels renumber their workgroups so that the workgroups of one XCD own one
@@ -1505,10 +1512,10 @@ void emit_uvu_backward(const Plan& P, bool conv, Kernel& K) {
         o << "      if (" << (phase_index > 0 ? "true" : "pass > 0") << ") {\n";
         for (int j : E.used_y_words()) {
           if (E.dup)   // every lane reads the word, one lane adds it (no lane-conditional region)
-            o << "        { const T o_ = __hip_atomic_load(gyb + " << j << ", __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); " << Em::GY(j)
+            o << "        { const T o_ = __hip_atomic_load(gyb + " << j << ", __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); " << Em::GY(j)
               << " += g_ == 0 ? o_ : (T)0; }\n";
           else
-          o << "        if (g_ == 0) " << Em::GY(j) << " += __hip_atomic_load(gyb + " << j << ", __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n";
+          o << "        if (g_ == 0) " << Em::GY(j) << " += __hip_atomic_load(gyb + " << j << ", __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);\n";
         }
         o << "      }\n";
       }
@@ -1612,12 +1619,12 @@ void emit_uvu_backward(const Plan& P, bool conv, Kernel& K) {
       emit_phase();
       if (xph.size() > 1) {
         // the next phase reads back the gy this one stored
-        o << "    }\n    __threadfence();\n    __builtin_amdgcn_sched_barrier(0);\n";
+        o << "    }\n    " << kWaveRereads << "\n    __builtin_amdgcn_sched_barrier(0);\n";
         E.xsel.clear();
         E.store_unused = true;
       }
     }
-    if (M.npass > 1) o << "    __threadfence();\n";
+    if (M.npass > 1) o << "    " << kWaveRereads << "\n";
     o << "  }\n}\n";
   }
   K.source = o.str();
@@ -1887,10 +1894,10 @@ void emit_uvu_conv_double(const Plan& P, bool backward_like, Kernel& K) {
       o << "      if (pass > 0) {\n";
       for (int jj : E.used_y_words()) {
         if (E.dup)
-          o << "        { const T o_ = __hip_atomic_load(gyb + " << jj << ", __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); " << Em::GY(jj)
+          o << "        { const T o_ = __hip_atomic_load(gyb + " << jj << ", __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); " << Em::GY(jj)
             << " += g_ == 0 ? o_ : (T)0; }\n";
         else
-        o << "        if (g_ == 0) " << Em::GY(jj) << " += __hip_atomic_load(gyb + " << jj << ", __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n";
+        o << "        if (g_ == 0) " << Em::GY(jj) << " += __hip_atomic_load(gyb + " << jj << ", __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);\n";
       }
       o << "      }\n";
     }
@@ -1905,7 +1912,7 @@ void emit_uvu_conv_double(const Plan& P, bool backward_like, Kernel& K) {
     o << "      }\n";
     o << "      ++r;\n";
     o << "    }\n";
-    if (M.npass > 1) o << "    __threadfence();\n";
+    if (M.npass > 1) o << "    " << kWaveRereads << "\n";
     o << "  }\n}\n";
   }
   K.source = o.str();
