@@ -82,8 +82,28 @@ LaneMap pick_map(const Plan& P, int kind) {
     // 64 lanes of an atomic instruction cover contiguous words (8 requests in fp32 instead of 16 with pairs)
     if (atomic) cpl = 1;
     // twice the operands of the first-order kernels per channel
-    // (measured: the sender walk of the convolution's second-order pass is faster with two, 1.49 -> 1.05 ms)
-    if (kind == CGTP_K_TP_DBL_BWD || kind == CGTP_K_CONV_DBL_FWD) cpl = 1;
+    if (kind == CGTP_K_TP_DBL_BWD) cpl = 1;
+    // A convolution kernel that needs a second pass walks its whole edge range again (y, the graph arrays and the
+    // gathers' latency once more, and a sender walk reads back its gy words), so the lane takes as many adjacent
+    // channels (up to `most`) as bring it to one pass.
+    // us on 3 000 nodes of degree 30 (* 1 500), fp32, with two passes -> one: 96 channels fwd 92 -> 83, bwd 160 -> 141,
+    // second order 365 -> 338; 192 channels 228 -> 199, 402 -> 356, 990 -> 882; 256 channels, l <= 3 (*) 222 -> 190,
+    // 378 -> 357, 1013 -> 883.  fp64 with 96 channels 163 -> 129, 310 -> 241, 732 -> 573, but three or four channels are
+    // too many registers there: bwd 192 channels 740 -> 822, 256 channels 774 -> 855.  The receiver walk of the
+    // second-order pass up to 128 fp32 channels stays at one channel and two passes (128 channels 645, in one pass 667).
+    if (conv && !atomic) {
+      int most = P.dtype == CGTP_F32 ? 4 : 2;
+      if (kind == CGTP_K_CONV_DBL_FWD && P.dtype == CGTP_F32 && M <= 128) most = 1;
+      for (int c = 1; c <= most; ++c) {
+        bool divides = true;
+        for (auto& q : P.paths) divides = divides && q.mul_x % c == 0;
+        if (divides && M <= 64 * c) {
+          cpl = c;
+          break;
+        }
+      }
+      if (most == 1) cpl = 1;
+    }
   }
   for (auto& q : P.paths)
     if (q.mul_x % cpl) cpl = 1;
