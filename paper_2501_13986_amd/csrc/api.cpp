@@ -248,6 +248,15 @@ cgtp_status ensure_ws(Plan& P, size_t bytes) {
   return CGTP_OK;
 }
 
+// The merge kernel of the convolution's split rows: one wave per edge range and slice of a row (emit_fixup).
+cgtp_status launch_fixup(const Plan& P, const void* out, const void* part, const int64_t* ptr, int64_t V, int64_t E, int64_t nchunk,
+                         int64_t row, hipStream_t st) {
+  const int64_t words = 64 * (P.dtype == CGTP_F64 ? 2 : 4), slices = (row + words - 1) / words, wpw = P.k_fix.wg / 64;
+  int dim = (int)row;
+  void* args[] = {(void*)&out, (void*)&part, (void*)&ptr, (void*)&V, (void*)&E, (void*)&nchunk, (void*)&dim};
+  return launch(P.k_fix, (unsigned)((nchunk * slices + wpw - 1) / wpw), args, st);
+}
+
 int64_t resident_waves(const Plan& P, const Kernel& k) { return (int64_t)k.blocks_per_cu * P.num_cu * (k.wg / 64); }
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -755,9 +764,7 @@ cgtp_status conv_forward_impl(cgtp_plan* plan, const void* x_nodes, const void* 
                   (void*)&V,       (void*)&E,       (void*)&part,    (void*)&nchunk,  (void*)&edge_perm};
   s = launch(k, grid, args, st);
   if (s != CGTP_OK) return s;
-  int dim = (int)P.dim_z();
-  void* fargs[] = {(void*)&z_nodes, (void*)&part, (void*)&row_ptr, (void*)&V, (void*)&E, (void*)&nchunk, (void*)&dim};
-  return launch(P.k_fix, (unsigned)nchunk, fargs, st);
+  return launch_fixup(P, z_nodes, part, row_ptr, V, E, nchunk, P.dim_z(), st);
 }
 }  // namespace
 
@@ -825,9 +832,7 @@ cgtp_status conv_backward_perm(cgtp_plan* plan, const void* x_nodes, const void*
                   (void*)&dummy};
   s = launch(k, grid, args, st);
   if (s != CGTP_OK) return s;
-  int dim = (int)P.dim_x();
-  void* fargs[] = {(void*)&gx_nodes, (void*)&part, (void*)&t_row_ptr, (void*)&V, (void*)&E, (void*)&nchunk, (void*)&dim};
-  return launch(P.k_fix, (unsigned)nchunk, fargs, st);
+  return launch_fixup(P, gx_nodes, part, t_row_ptr, V, E, nchunk, P.dim_x(), st);
 }
 
 cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,
@@ -874,9 +879,7 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
                     (void*)&nf};
     s = launch(kf, grid, args, st);
     if (s != CGTP_OK) return s;
-    int dim = (int)P.dim_z();
-    void* fargs[] = {(void*)&Lgz_nodes, (void*)&part, (void*)&row_ptr, (void*)&V, (void*)&E, (void*)&nf, (void*)&dim};
-    s = launch(P.k_fix, (unsigned)nf, fargs, st);
+    s = launch_fixup(P, Lgz_nodes, part, row_ptr, V, E, nf, P.dim_z(), st);
     if (s != CGTP_OK) return s;
   }
   int64_t* t_recv = (int64_t*)((char*)P.ws + part_b);
@@ -889,9 +892,7 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
                     (void*)&t_recv,   (void*)&V,        (void*)&E,        (void*)&part,     (void*)&nb};
     s = launch(kb, grid, args, st);
     if (s != CGTP_OK) return s;
-    int dim = (int)P.dim_x();
-    void* fargs[] = {(void*)&Lx_nodes, (void*)&part, (void*)&t_row_ptr, (void*)&V, (void*)&E, (void*)&nb, (void*)&dim};
-    return launch(P.k_fix, (unsigned)nb, fargs, st);
+    return launch_fixup(P, Lx_nodes, part, t_row_ptr, V, E, nb, P.dim_x(), st);
   }
 }
 

@@ -1921,26 +1921,47 @@ void emit_fixup(const Plan& P, Kernel& K) {
   K.name = "cgtp_conv_fixup";
   E.preamble();
   E.emit_row_of();
-  E.o << "extern \"C\" __global__ void __launch_bounds__(" << K.wg << ") " << K.name
-      << "(T* __restrict__ out, const T* __restrict__ part, const i64* __restrict__ ptr, i64 V, i64 E, i64 nchunk, int dim)\n{\n"
-         "  const i64 w = blockIdx.x;\n"
-         "  const i64 e0 = (w * E) / nchunk, e1 = ((w + 1) * E) / nchunk;\n"
-         "  if (e1 <= e0 || e1 >= E) return;\n"
-         "  const i64 lo = row_of(ptr, V, e1 - 1);\n"
-         "  const i64 rbeg = ptr[lo], rend = ptr[lo + 1];\n"
-         "  if (!(rend > e1 && rbeg >= e0)) return;\n"
-         "  for (int d = threadIdx.x; d < dim; d += blockDim.x) {\n"
-         "    T acc = part[(w * 2 + 1) * dim + d];\n";
-  if (P.kahan_conv)   // the pieces of a split row are added with the same compensated sum as the edges inside a piece
-    E.o << "    T cmp = (T)0;\n"
-           "    for (i64 v = w + 1; v < nchunk && (v * E) / nchunk < rend; ++v) {\n"
-           "      const T y_ = part[(v * 2) * dim + d] - cmp; const T t_ = acc + y_; cmp = (t_ - acc) - y_; acc = t_;\n"
-           "    }\n";
-  else
-    E.o << "    for (i64 v = w + 1; v < nchunk && (v * E) / nchunk < rend; ++v) acc += part[(v * 2) * dim + d];\n";
-  E.o << "    out[lo * dim + d] = acc;\n"
-         "  }\n}\n";
-  K.source = E.o.str();
+  // Bound by its chain of dependent loads (row search, row ends, pieces), so the work is cut for many short waves: one
+  // wave per range and slice of 64 vectors of the row, every lane adds one vector, and the pieces are read ahead of their
+  // sums.  Whole calls, against
+  // one 256-thread workgroup per range with a division per piece and word: forward + backward on 27 nodes (32 channels)
+  // 31.8 -> 25.8 us; 3 000 nodes of 4 channels (one edge per range) 378 -> 136 us; 3 001 nodes of 32 channels 204 -> 193 us;
+  // second-order pass of 128 channels on 2 000 nodes 657 -> 643 us.
+  const int v = P.dtype == CGTP_F64 ? 2 : 4;
+  const std::string V = "V" + std::to_string(v);
+  auto& o = E.o;
+  o << "extern \"C\" __global__ void __launch_bounds__(" << K.wg << ") " << K.name
+    << "(T* __restrict__ out, const T* __restrict__ part, const i64* __restrict__ ptr, i64 V, i64 E, i64 nchunk, int dim)\n{\n"
+       "  const int nsl = (dim + " << 64 * v - 1 << ") / " << 64 * v << ";\n"
+       "  const i64 item = (i64)blockIdx.x * " << K.wg / 64 << " + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));\n"
+       "  const i64 w = item / nsl;\n"
+       "  if (w >= nchunk) return;\n"
+       "  const i64 e0 = (w * E) / nchunk, e1 = ((w + 1) * E) / nchunk;\n"
+       "  if (e1 <= e0 || e1 >= E) return;\n"
+       "  const i64 lo = row_of(ptr, V, e1 - 1);\n"
+       "  const i64 rbeg = ptr[lo], rend = ptr[lo + 1];\n"
+       "  if (!(rend > e1 && rbeg >= e0)) return;\n"
+       "  const i64 wend = (rend * nchunk + E - 1) / E;   // first range that begins at or after the row's end\n"
+       "  const int d = ((int)(item - w * nsl) * 64 + (int)(threadIdx.x & 63)) * " << v << ";\n"
+       "  const int nd = dim - d < " << v << " ? dim - d : " << v << ";\n";
+  // S: the type of a lane's sum, n: words of a vector load (the last vector of a row may be short: single words)
+  auto merge = [&](const std::string& S, const std::string& at, const char* ind) {
+    o << ind << S << " acc = *(const " << S << "*)(part + (w * 2 + 1) * dim + " << at << ");\n";
+    if (P.kahan_conv) o << ind << S << " cmp = (T)0;\n";   // the same compensated sum as over the edges inside a piece
+    o << ind << "#pragma unroll 4\n";
+    o << ind << "for (i64 q = w + 1; q < wend; ++q) {\n";
+    o << ind << "  const " << S << " p_ = *(const " << S << "*)(part + (q * 2) * dim + " << at << ");\n";
+    if (P.kahan_conv) o << ind << "  const " << S << " y_ = p_ - cmp; const " << S << " t_ = acc + y_; cmp = (t_ - acc) - y_; acc = t_;\n";
+    else o << ind << "  acc += p_;\n";
+    o << ind << "}\n";
+    o << ind << "*(" << S << "*)(out + lo * dim + " << at << ") = acc;\n";
+  };
+  o << "  if (nd == " << v << ") {\n";
+  merge(V, "d", "    ");
+  o << "  } else {\n    for (int t = 0; t < nd; ++t) {\n";
+  merge("T", "d + t", "      ");
+  o << "    }\n  }\n}\n";
+  K.source = o.str();
 }
 
 }  // namespace cgtp
