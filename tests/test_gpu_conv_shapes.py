@@ -17,7 +17,6 @@ SPECS.update({
     "mul75": ("75x0e+75x1o", "1x0e+1x1o", "75x0e+75x1o"),         # three channels per lane (fp32)
     "mul130": ("130x0e+130x1o", "1x0e+1x1o", "130x0e+130x1o"),    # even, above 128, no divisor up to four that fits: two passes of two
     "mul256": ("256x0e+256x1o", "1x0e+1x1o", "256x0e+256x1o"),    # four channels per lane (fp32), two passes of two (fp64)
-    "uneven": ("100x0e+20x1o", "1x0e+1x1o", "100x0e+20x1o"),      # a segment far narrower than the lane map
     "odd_row": ("3x0e+3x1o", "1x0e+1x1o", "3x0e+3x1o+1x2e"),      # rows of 12 and 17 words
 })
 GRAPHS.update({"hub": (3, 30000, ())})                            # thousands of ranges in one row
@@ -48,7 +47,7 @@ def check(spec_name, graph, prec, double=True):
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32"])
-@pytest.mark.parametrize("spec_name", ["mul65", "mul75", "mul96", "mul130", "mul192", "mul256", "uneven"])
+@pytest.mark.parametrize("spec_name", ["mul65", "mul75", "mul96", "mul130", "mul192", "mul256"])
 def test_lane_maps_above_one_wave(spec_name, prec):
     check(spec_name, "empty_ends", prec)
 
