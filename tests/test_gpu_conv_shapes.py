@@ -17,7 +17,7 @@ SPECS.update({
     "mul75": ("75x0e+75x1o", "1x0e+1x1o", "75x0e+75x1o"),         # three channels per lane (fp32)
     "mul130": ("130x0e+130x1o", "1x0e+1x1o", "130x0e+130x1o"),    # even, above 128, no divisor up to four that fits: two passes of two
     "mul256": ("256x0e+256x1o", "1x0e+1x1o", "256x0e+256x1o"),    # four channels per lane (fp32), two passes of two (fp64)
-    "odd_row": ("3x0e+3x1o", "1x0e+1x1o", "3x0e+3x1o+1x2e"),      # rows of 12 and 17 words
+    "odd_row": ("3x0e+3x1o", "1x0e+1x1o", "3x0e+3x1o+3x1e"),      # rows of 12 and 21 words
 })
 GRAPHS.update({"hub": (3, 30000, ())})                            # thousands of ranges in one row
 
