@@ -3,6 +3,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -258,6 +259,33 @@ cgtp_status launch_fixup(const Plan& P, const void* out, const void* part, const
 }
 
 int64_t resident_waves(const Plan& P, const Kernel& k) { return (int64_t)k.blocks_per_cu * P.num_cu * (k.wg / 64); }
+
+// 64 words of pinned host memory, one per cache line, handed out to concurrent calls; allocated on first use and kept
+// until the process ends.  take() answers -1 if none is free or the allocation failed.
+struct HostFlags {
+  int32_t* flags = nullptr;
+  std::atomic<uint64_t> used{0};
+  HostFlags() {
+    if (hipHostMalloc((void**)&flags, 64 * 64, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      flags = nullptr;
+    }
+  }
+  int take() {
+    if (!flags) return -1;
+    uint64_t u = used.load();
+    while (~u) {
+      const int slot = __builtin_ctzll(~u);
+      if (used.compare_exchange_weak(u, u | ((uint64_t)1 << slot))) return slot;
+    }
+    return -1;
+  }
+  void give(int slot) { used.fetch_and(~((uint64_t)1 << slot)); }
+};
+HostFlags& host_flags() {
+  static HostFlags* h = new HostFlags();   // not destroyed: calls may still run while the process ends
+  return *h;
+}
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -1007,14 +1035,26 @@ cgtp_status cgtp_csr_from_coo(const int64_t* recv, const int64_t* send, int64_t 
     }
     ws = sc.p;
   }
-  int32_t* flag = (int32_t*)ws;
+  // the one synchronisation of this call: the range check is part of its return value.  The kernels write it into a
+  // page of pinned host memory (a copy of four bytes from the device costs 8 us of the call); callers beyond the
+  // page's slots copy it.
+  HostFlags& hf = host_flags();
+  const int slot = hf.take();
+  int32_t* flag = slot >= 0 ? hf.flags + slot * 16 : (int32_t*)ws;
+  if (slot >= 0) __atomic_store_n(flag, 0, __ATOMIC_RELEASE);
   cgtp_status s = cgtp_csr_from_coo_async(recv, send, E, V, row_ptr, col, perm, t_row_ptr, t_perm, (char*)ws + 256, need - 256,
                                           flag, hip_stream);
-  if (s != CGTP_OK) return s;
-  // the one synchronisation of this call: the range check is part of its return value
   int bad = 0;
-  HIP_TRY(hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, (hipStream_t)hip_stream));
-  HIP_TRY(hipStreamSynchronize((hipStream_t)hip_stream));
+  hipError_t e = hipSuccess;
+  if (s == CGTP_OK && slot < 0) e = hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, (hipStream_t)hip_stream);
+  const hipError_t waited = hipStreamSynchronize((hipStream_t)hip_stream);   // also after a failed launch: earlier ones may still write the slot
+  if (slot >= 0) {
+    bad = __atomic_load_n(flag, __ATOMIC_ACQUIRE);
+    if (waited == hipSuccess) hf.give(slot);
+  }
+  if (s != CGTP_OK) return s;
+  HIP_TRY(e);
+  HIP_TRY(waited);
   if (bad) return fail(CGTP_EINVAL, "edge index outside [0, V)");
   return CGTP_OK;
 }

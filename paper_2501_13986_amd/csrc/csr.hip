@@ -86,6 +86,348 @@ __global__ void k_add_inplace(T* __restrict__ a, const T* __restrict__ b, int64_
   for (; i < n; i += step) a[i] += b[i];
 }
 
+// ---- bucket path: graphs of up to about 2.6 million edges ---------------------------------------------------------------
+// A general radix sort costs a launch or two per digit or merge round (ten rounds for 800 000 keys, twice), each a few
+// microseconds long whatever it does.  Here the edges are cut once into at most 1 024 buckets of consecutive rows, and
+// one workgroup finishes a bucket in LDS: rows are placed by counting, and the order inside a row comes from counting
+// the smaller records of that row (unique records: row, other end, original position packed into 64 bits, so the order
+// of arrival does not matter and the result is the stable one).  The kernel that finishes the receivers hands its edges
+// on to the buckets of the senders.  Five launches for any size, one if the graph fits a single workgroup.
+// What is left is the latency of dependent passes.  Synchronous call, sorts -> buckets: 27 nodes of degree 9 72 -> 28 us,
+// 300 nodes of degree 20 118 -> 45, 3 001 nodes of degree 32 176 -> 53, 20 000 nodes of degree 40 416 -> 81 us (kernels
+// 2 + 9 + 14 + 21 + 14); conv_forward_perm + conv_backward_perm with the preparation, 3 001 nodes of 32 channels 343 -> 243 us.
+constexpr int kThreads = 1024;     // of every kernel of this path; one thread per bucket in the scans
+constexpr int kBuckets = 1024;
+constexpr int kPer = 4;            // records of a thread
+constexpr int kCap = kThreads * kPer;
+constexpr int kRows = 4096;        // rows of a bucket
+constexpr int kTilePer = 8;        // edges of a thread in the counting and distributing passes
+constexpr int kTile = kThreads * kTilePer;
+
+struct BucketPlan {
+  int shift, nb, eb, vb;   // bucket of a row = row >> shift; number of buckets; bits of an edge index and of a node index
+};
+
+struct BucketWs {          // in the caller's workspace
+  int *total1, *total2, *base1, *base2, *cursor2, *before;   // zeroed: total1, total2
+  uint64_t *rec1, *rec2;
+};
+
+struct SortLds {
+  uint64_t rec[kCap];
+  int off[kRows + 1];
+  int wave[kThreads / 64];
+};
+
+// exclusive sum over the 1 024 threads of the workgroup
+__device__ __forceinline__ int block_scan(int v, int* wave) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int s = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(s, o, 64);
+    s += lane >= o ? t : 0;
+  }
+  if (lane == 63) wave[w] = s;
+  __syncthreads();
+  int before = 0;
+  for (int i = 0; i < kThreads / 64; ++i) before += i < w ? wave[i] : 0;
+  __syncthreads();
+  return before + s - v;
+}
+
+// rec[j] (valid for threadIdx.x + j * 1024 < n, row = rec >> row_bits < rows): on return rec[j] is some record of the same
+// set and pos[j] its place in ascending order; S.off[r] = first place of row r, S.off[rows] = n.
+__device__ __forceinline__ void sort_in_lds(SortLds& S, uint64_t (&rec)[kPer], int (&pos)[kPer], int n, int rows, int row_bits) {
+  const int t = threadIdx.x;
+  for (int r = t; r <= rows; r += kThreads) S.off[r] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if (t + j * kThreads < n) pos[j] = atomicAdd(&S.off[(int)(rec[j] >> row_bits)], 1);
+  __syncthreads();
+  constexpr int kRowsPer = kRows / kThreads;
+  int c[kRowsPer], sum = 0;
+#pragma unroll
+  for (int q = 0; q < kRowsPer; ++q) {
+    const int r = t * kRowsPer + q;
+    c[q] = r < rows ? S.off[r] : 0;
+    sum += c[q];
+  }
+  int at = block_scan(sum, S.wave);
+#pragma unroll
+  for (int q = 0; q < kRowsPer; ++q) {
+    const int r = t * kRowsPer + q;
+    if (r < rows) S.off[r] = at;
+    at += c[q];
+  }
+  if (t == 0) S.off[rows] = n;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if (t + j * kThreads < n) S.rec[S.off[(int)(rec[j] >> row_bits)] + pos[j]] = rec[j];
+  __syncthreads();
+  // neighbouring lanes now hold records of the same row: their reads of the row are broadcasts
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if (t + j * kThreads < n) {
+      const uint64_t k = S.rec[t + j * kThreads];
+      const int r = (int)(k >> row_bits), beg = S.off[r], end = S.off[r + 1];
+      int less = beg;
+#pragma unroll 4
+      for (int q = beg; q < end; ++q) less += S.rec[q] < k ? 1 : 0;
+      rec[j] = k;
+      pos[j] = less;
+    }
+}
+
+__device__ __forceinline__ bool load_edge(const int64_t* __restrict__ recv, const int64_t* __restrict__ send, int64_t e, int64_t V,
+                                          uint64_t& r, uint64_t& s) {
+  r = (uint64_t)recv[e];
+  s = (uint64_t)send[e];
+  const bool ok = r < (uint64_t)V && s < (uint64_t)V;   // also refuses negative values
+  if (!ok) r = s = 0;
+  return ok;
+}
+
+// E <= 4 096 and V <= 4 096: everything in one workgroup
+__global__ void __launch_bounds__(kThreads) k_csr_small(const int64_t* __restrict__ recv, const int64_t* __restrict__ send, int E, int V,
+                                                        int eb, int vb, int64_t* __restrict__ row_ptr, int64_t* __restrict__ col,
+                                                        int64_t* __restrict__ perm, int64_t* __restrict__ t_row_ptr,
+                                                        int64_t* __restrict__ t_perm, int* __restrict__ bad_flag) {
+  __shared__ SortLds S;
+  const int t = threadIdx.x;
+  const uint64_t emask = ((uint64_t)1 << eb) - 1, vmask = ((uint64_t)1 << vb) - 1;
+  uint64_t rec[kPer];
+  int pos[kPer], bad = 0;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int e = t + j * kThreads;
+    rec[j] = 0;
+    pos[j] = 0;
+    if (e < E) {
+      uint64_t r, s;
+      if (!load_edge(recv, send, e, V, r, s)) bad = 1;
+      rec[j] = (r << (eb + vb)) | (s << eb) | (uint64_t)e;
+    }
+  }
+  bad = __syncthreads_or(bad);
+  if (t == 0 && bad_flag) *bad_flag = bad ? 1 : 0;
+  sort_in_lds(S, rec, pos, E, V, eb + vb);
+  for (int r = t; r <= V; r += kThreads) row_ptr[r] = S.off[r];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if (t + j * kThreads < E) {
+      const uint64_t s = (rec[j] >> eb) & vmask;
+      perm[pos[j]] = (int64_t)(rec[j] & emask);
+      col[pos[j]] = (int64_t)s;
+      rec[j] = (s << eb) | (uint64_t)pos[j];
+    }
+  if (!t_row_ptr) return;
+  __syncthreads();
+  sort_in_lds(S, rec, pos, E, V, eb);
+  for (int r = t; r <= V; r += kThreads) t_row_ptr[r] = S.off[r];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if (t + j * kThreads < E) t_perm[pos[j]] = (int64_t)(rec[j] & emask);
+}
+
+__global__ void k_csr_clear(int* __restrict__ totals, int n, int* __restrict__ bad) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) totals[i] = 0;
+  if (i == 0) *bad = 0;
+}
+
+// edges per bucket of receivers and of senders; before[block][bucket]: edges of that bucket that other workgroups placed
+// ahead of this one's
+__global__ void __launch_bounds__(kThreads) k_csr_count(const int64_t* __restrict__ recv, const int64_t* __restrict__ send, int64_t E,
+                                                        int64_t V, BucketPlan B, BucketWs w, int transpose) {
+  __shared__ int h1[kBuckets], h2[kBuckets];
+  const int t = threadIdx.x;
+  h1[t] = 0;
+  h2[t] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kTilePer; ++j) {
+    const int64_t e = (int64_t)blockIdx.x * kTile + j * kThreads + t;
+    if (e < E) {
+      uint64_t r, s;
+      (void)load_edge(recv, send, e, V, r, s);
+      atomicAdd(&h1[(int)(r >> B.shift)], 1);
+      if (transpose) atomicAdd(&h2[(int)(s >> B.shift)], 1);
+    }
+  }
+  __syncthreads();
+  if (t < B.nb) {
+    const int c1 = h1[t], c2 = h2[t];
+    w.before[(int64_t)blockIdx.x * B.nb + t] = c1 ? atomicAdd(&w.total1[t], c1) : 0;
+    if (transpose && c2) atomicAdd(&w.total2[t], c2);
+  }
+}
+
+// records into the buckets of receivers; the last workgroup (if there is a transpose) lays out the buckets of senders
+__global__ void __launch_bounds__(kThreads) k_csr_distribute(const int64_t* __restrict__ recv, const int64_t* __restrict__ send, int64_t E,
+                                                             int64_t V, BucketPlan B, BucketWs w, int tiles, int* __restrict__ bad) {
+  __shared__ int dst[kBuckets];
+  __shared__ int wave[kThreads / 64];
+  const int t = threadIdx.x;
+  const bool second = (int)blockIdx.x == tiles;
+  const int start = block_scan(t < B.nb ? (second ? w.total2[t] : w.total1[t]) : 0, wave);
+  if (second) {
+    if (t < B.nb) {
+      w.base2[t] = start;
+      w.cursor2[t] = start;
+    }
+    if (t == 0) w.base2[B.nb] = (int)E;
+    return;
+  }
+  if (blockIdx.x == 0) {
+    if (t < B.nb) w.base1[t] = start;
+    if (t == 0) w.base1[B.nb] = (int)E;
+  }
+  if (t < B.nb) dst[t] = start + w.before[(int64_t)blockIdx.x * B.nb + t];
+  __syncthreads();
+  const uint64_t in_bucket = ((uint64_t)1 << B.shift) - 1;
+#pragma unroll
+  for (int j = 0; j < kTilePer; ++j) {
+    const int64_t e = (int64_t)blockIdx.x * kTile + j * kThreads + t;
+    if (e < E) {
+      uint64_t r, s;
+      if (!load_edge(recv, send, e, V, r, s)) *bad = 1;
+      const int q = atomicAdd(&dst[(int)(r >> B.shift)], 1);
+      w.rec1[q] = ((r & in_bucket) << (B.eb + B.vb)) | (s << B.eb) | (uint64_t)e;
+    }
+  }
+}
+
+// A bucket of more than 4 096 records (a few receivers or senders with very many edges): one workgroup sorts it in global
+// memory, 8 bits at a time, between the records and the output array of the bucket's range.  An even number of passes
+// leaves the result where it began.  Slow (about 4 us per pass and 1 000 records), but such graphs are not what this
+// path is for and the result is the same.
+__device__ void sort_in_memory(uint64_t* a, uint64_t* b, int n, int bits, SortLds& S) {
+  int* count = S.off;                       // [16 waves][256 digits]
+  int* next = (int*)S.rec;                  // [256]
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int passes = ((bits + 7) / 8 + 1) & ~1;
+  for (int p = 0; p < passes; ++p) {
+    const int sh = p * 8 < 56 ? p * 8 : 56;
+    const bool empty = p * 8 >= bits;       // padding pass: keeps the order
+    __syncthreads();
+    if (t < 256) next[t] = 0;
+    __syncthreads();
+    for (int i = t; i < n; i += kThreads) atomicAdd(&next[empty ? 0 : (int)((a[i] >> sh) & 255)], 1);
+    __syncthreads();
+    const int c = t < 256 ? next[t] : 0;
+    const int first = block_scan(c, S.wave);
+    if (t < 256) next[t] = first;
+    for (int i0 = 0; i0 < n; i0 += kThreads) {
+      for (int q = t; q < 16 * 256; q += kThreads) count[q] = 0;
+      __syncthreads();
+      const int i = i0 + t;
+      const bool in = i < n;
+      const uint64_t k = in ? a[i] : 0;
+      const int d = empty ? 0 : (int)((k >> sh) & 255);
+      // lanes of this wave with the same digit
+      uint64_t same = __ballot(in);
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit) {
+        const uint64_t m = __ballot((d >> bit) & 1);
+        same &= ((d >> bit) & 1) ? m : ~m;
+      }
+      const int rank = __popcll(same & (((uint64_t)1 << lane) - 1));
+      if (in && rank == 0) count[wv * 256 + d] = __popcll(same);
+      __syncthreads();
+      if (t < 256) {                        // places of each wave's digit groups, and where the next tile continues
+        int at = next[t];
+        for (int q = 0; q < 16; ++q) {
+          const int v = count[q * 256 + t];
+          count[q * 256 + t] = at;
+          at += v;
+        }
+        next[t] = at;
+      }
+      __syncthreads();
+      if (in) b[count[wv * 256 + d] + rank] = k;
+      __syncthreads();
+    }
+    uint64_t* x = a;
+    a = b;
+    b = x;
+  }
+  __syncthreads();
+}
+
+// One bucket: kSecond false: the rows of its receivers (row_ptr, col, perm), and its edges on to the buckets of senders;
+// true: the rows of its senders (t_row_ptr, t_perm).
+template <bool kSecond>
+__global__ void __launch_bounds__(kThreads) k_csr_rows(BucketPlan B, BucketWs w, int64_t V, int64_t E, int64_t* __restrict__ ptr,
+                                                       int64_t* idx, int64_t* __restrict__ col, int transpose) {
+  __shared__ SortLds S;
+  __shared__ int h2[kSecond ? 1 : kBuckets];
+  const int t = threadIdx.x, bucket = blockIdx.x;
+  const int base = (kSecond ? w.base2 : w.base1)[bucket], n = (kSecond ? w.base2 : w.base1)[bucket + 1] - base;
+  uint64_t* const in = (kSecond ? w.rec2 : w.rec1) + base;
+  const int row_bits = B.eb + (kSecond ? 0 : B.vb);
+  const int64_t row0 = (int64_t)bucket << B.shift;
+  const int rows = (int)(V - row0 < ((int64_t)1 << B.shift) ? V - row0 : (int64_t)1 << B.shift);
+  const uint64_t emask = ((uint64_t)1 << B.eb) - 1, vmask = ((uint64_t)1 << B.vb) - 1;
+  const uint64_t in_bucket = ((uint64_t)1 << B.shift) - 1;
+  if (bucket == B.nb - 1 && t == 0) ptr[V] = E;
+  if (n > kCap) {
+    sort_in_memory(in, (uint64_t*)(idx + base), n, row_bits + B.shift, S);
+    for (int i = t; i < n; i += kThreads) {
+      const uint64_t k = in[i];
+      const int r = (int)(k >> row_bits);
+      for (int q = i > 0 ? (int)(in[i - 1] >> row_bits) + 1 : 0; q <= r; ++q) ptr[row0 + q] = base + i;
+      if (i == n - 1)
+        for (int q = r + 1; q < rows; ++q) ptr[row0 + q] = base + n;
+      idx[base + i] = (int64_t)(k & emask);
+      if (!kSecond) {
+        const uint64_t s = (k >> B.eb) & vmask;
+        col[base + i] = (int64_t)s;
+        if (transpose) w.rec2[atomicAdd(&w.cursor2[(int)(s >> B.shift)], 1)] = ((s & in_bucket) << B.eb) | (uint64_t)(base + i);
+      }
+    }
+    return;
+  }
+  uint64_t rec[kPer];
+  int pos[kPer];
+  if (!kSecond) h2[t] = 0;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int i = t + j * kThreads;
+    rec[j] = i < n ? in[i] : 0;
+    pos[j] = 0;
+  }
+  sort_in_lds(S, rec, pos, n, rows, row_bits);
+  for (int r = t; r < rows; r += kThreads) ptr[row0 + r] = base + S.off[r];
+  int rank[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    rank[j] = 0;
+    if (t + j * kThreads < n) {
+      idx[base + pos[j]] = (int64_t)(rec[j] & emask);
+      if (!kSecond) {
+        const uint64_t s = (rec[j] >> B.eb) & vmask;
+        col[base + pos[j]] = (int64_t)s;
+        if (transpose) rank[j] = atomicAdd(&h2[(int)(s >> B.shift)], 1);
+      }
+    }
+  }
+  if (kSecond || !transpose) return;
+  __syncthreads();
+  if (t < B.nb) {
+    const int c = h2[t];
+    if (c) h2[t] = atomicAdd(&w.cursor2[t], c);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if (t + j * kThreads < n) {
+      const uint64_t s = (rec[j] >> B.eb) & vmask;
+      w.rec2[h2[(int)(s >> B.shift)] + rank[j]] = ((s & in_bucket) << B.eb) | (uint64_t)(base + pos[j]);
+    }
+}
+
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 // Scratch for the entry point that allocates nothing (conv_forward_static): device memory that exists from the
@@ -219,11 +561,76 @@ hipError_t csr_build(const int64_t* recv, const int64_t* send, int64_t E, int64_
   return hipSuccess;
 }
 
+enum class CsrPath { kSmall, kBuckets, kSort };
+
+// One workgroup where rows and edges fit its LDS; buckets up to 2 560 edges a bucket on average (4 096 fit, so rows may
+// be uneven): as many buckets as leave each 512 edges (5 000 nodes of degree 32: 56 us a call, with 256 edges 69, with
+// 1 300 57), but no more than the chip holds at once, two workgroups a CU (20 000 nodes of degree 40: 313 buckets 81 us,
+// 625 buckets 87).  Everything else takes the sorts: above 2.6 million edges, and at most 4 096 edges on more than
+// 4 096 nodes, where the buckets' tables would need more workspace than the sort.
+CsrPath csr_path(int64_t E, int64_t V, BucketPlan& B) {
+  B.eb = (int)bits_for((uint64_t)(E > 1 ? E - 1 : 1));
+  B.vb = (int)bits_for((uint64_t)(V > 1 ? V - 1 : 1));
+  if (E <= kCap) return V <= kRows ? CsrPath::kSmall : CsrPath::kSort;
+  const int64_t least = 512, most = 2560, at_once = 512;
+  for (int sh = 0; ((int64_t)1 << sh) <= kRows; ++sh) {
+    const int64_t nb = (V + ((int64_t)1 << sh) - 1) >> sh;
+    if (nb > kBuckets) continue;
+    if (E > most * nb) break;
+    const int64_t half = (V + ((int64_t)2 << sh) - 1) >> (sh + 1);   // buckets of twice the rows
+    if (half < nb && ((int64_t)2 << sh) <= kRows && E <= most * half && (E < least * nb || nb > at_once)) continue;
+    B.shift = sh;
+    B.nb = (int)nb;
+    return CsrPath::kBuckets;
+  }
+  return CsrPath::kSort;
+}
+
+size_t up256(size_t v) { return (v + 255) / 256 * 256; }
+
+size_t bucket_layout(const BucketPlan& B, int64_t E, char* at, BucketWs& w) {
+  const size_t table = up256((kBuckets + 1) * sizeof(int)), recs = up256((size_t)E * 8);
+  const int64_t tiles = (E + kTile - 1) / kTile;
+  size_t o = 0;
+  auto take = [&](size_t bytes) { char* p = at + o; o += bytes; return p; };
+  w.total1 = (int*)take(table);
+  w.total2 = (int*)take(table);
+  w.base1 = (int*)take(table);
+  w.base2 = (int*)take(table);
+  w.cursor2 = (int*)take(table);
+  w.before = (int*)take(up256((size_t)tiles * B.nb * sizeof(int)));
+  w.rec1 = (uint64_t*)take(recs);
+  w.rec2 = (uint64_t*)take(recs);
+  return o + 256;   // the range-check flag of a caller that gives none
+}
+
+hipError_t csr_buckets(const int64_t* recv, const int64_t* send, int64_t E, int64_t V, int64_t* row_ptr, int64_t* col, int64_t* perm,
+                       int64_t* t_row_ptr, int64_t* t_perm, char* block, const BucketPlan& B, int* bad_flag, hipStream_t st) {
+  BucketWs w;
+  const size_t total = bucket_layout(B, E, block, w);
+  int* bad = bad_flag ? bad_flag : (int*)(block + total - 256);
+  const int transpose = t_row_ptr != nullptr, tiles = (int)((E + kTile - 1) / kTile);
+  const int tables = (int)(w.base1 - w.total1);   // both totals
+  hipLaunchKernelGGL(k_csr_clear, dim3((tables + kBlock - 1) / kBlock), dim3(kBlock), 0, st, w.total1, tables, bad);
+  hipLaunchKernelGGL(k_csr_count, dim3(tiles), dim3(kThreads), 0, st, recv, send, E, V, B, w, transpose);
+  hipLaunchKernelGGL(k_csr_distribute, dim3(tiles + transpose), dim3(kThreads), 0, st, recv, send, E, V, B, w, tiles, bad);
+  hipLaunchKernelGGL(k_csr_rows<false>, dim3(B.nb), dim3(kThreads), 0, st, B, w, V, E, row_ptr, perm, col, transpose);
+  if (transpose) hipLaunchKernelGGL(k_csr_rows<true>, dim3(B.nb), dim3(kThreads), 0, st, B, w, V, E, t_row_ptr, t_perm, (int64_t*)nullptr, 0);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t csr_workspace_bytes(int64_t E, int64_t V, size_t* bytes) {
   *bytes = 256;
   if (E <= 0) return hipSuccess;
+  BucketPlan B;
+  BucketWs w;
+  switch (csr_path(E, V, B)) {
+    case CsrPath::kSmall: return hipSuccess;   // no scratch
+    case CsrPath::kBuckets: *bytes = bucket_layout(B, E, nullptr, w); return hipSuccess;
+    case CsrPath::kSort: break;
+  }
   CsrLayout L;
   CSR_TRY(csr_layout(E, V, L));
   *bytes = L.total;
@@ -241,6 +648,18 @@ hipError_t csr_from_coo_async(const int64_t* recv, const int64_t* send, int64_t 
     if (transpose) CSR_TRY(launch_fill_zero(t_row_ptr, (size_t)(V + 1) * 8, st));
     if (bad_flag) CSR_TRY(launch_fill_zero(bad_flag, 4, st));
     return hipSuccess;
+  }
+  BucketPlan B;
+  const CsrPath path = csr_path(E, V, B);
+  if (path == CsrPath::kSmall) {
+    hipLaunchKernelGGL(k_csr_small, dim3(1), dim3(kThreads), 0, st, recv, send, (int)E, (int)V, B.eb, B.vb, row_ptr, col, perm, t_row_ptr,
+                       t_perm, bad_flag);
+    return hipGetLastError();
+  }
+  if (path == CsrPath::kBuckets) {
+    BucketWs w;
+    if (!workspace || workspace_bytes < bucket_layout(B, E, nullptr, w)) return hipErrorInvalidValue;
+    return csr_buckets(recv, send, E, V, row_ptr, col, perm, t_row_ptr, t_perm, (char*)workspace, B, bad_flag, st);
   }
   CsrLayout L;
   CSR_TRY(csr_layout(E, V, L));
