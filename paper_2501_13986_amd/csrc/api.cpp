@@ -90,10 +90,12 @@ LaneMap pick_map(const Plan& P, int kind) {
     // us on 3 000 nodes of degree 30 (* 1 500), fp32, with two passes -> one: 96 channels fwd 92 -> 83, bwd 160 -> 141,
     // second order 365 -> 338; 192 channels 228 -> 199, 402 -> 356, 990 -> 882; 256 channels, l <= 3 (*) 222 -> 190,
     // 378 -> 357, 1013 -> 883.  fp64 with 96 channels 163 -> 129, 310 -> 241, 732 -> 573, but three or four channels are
-    // too many registers there: bwd 192 channels 740 -> 822, 256 channels 774 -> 855.  The receiver walk of the
+    // too many registers there: bwd 192 channels 740 -> 822, 256 channels 774 -> 855.  The forward
+    // walk stops at three: four would halve the edge ranges of a 256-channel plan, and conv_forward_static, whose static
+    // buffer bounds the ranges, is documented to refuse that plan.  The receiver walk of the
     // second-order pass up to 128 fp32 channels stays at one channel and two passes (128 channels 645, in one pass 667).
     if (conv && !atomic) {
-      int most = P.dtype == CGTP_F32 ? 4 : 2;
+      int most = P.dtype == CGTP_F32 ? (kind == CGTP_K_CONV_FWD ? 3 : 4) : 2;
       if (kind == CGTP_K_CONV_DBL_FWD && P.dtype == CGTP_F32 && M <= 128) most = 1;
       for (int c = 1; c <= most; ++c) {
         bool divides = true;
