@@ -262,6 +262,19 @@ cgtp_status launch_fixup(const Plan& P, const void* out, const void* part, const
 
 int64_t resident_waves(const Plan& P, const Kernel& k) { return (int64_t)k.blocks_per_cu * P.num_cu * (k.wg / 64); }
 
+// Edge ranges of a convolution kernel: one per resident worker, but where that leaves fewer than two edges each, ranges of
+// three (of eight for workers that share a wave with many others), as long as 1 024 waves have work: every range costs
+// a row search and up to two pieces of split rows for the merge kernel.
+// forward + backward, one edge range per worker -> this: 3 000 nodes of 4 channels 136 -> 69 us, 300 nodes of 96 channels
+// 46 -> 39, 300 nodes of 128 channels 69 -> 67 (second order 93 -> 85).  With two edges per worker already, three are
+// slower (second order, 700 nodes of 32 channels 72 -> 76), and so is a range of four for each of fewer than 1 024 waves
+// (27 nodes of 32 channels 26 -> 30).
+int64_t conv_ranges(const Plan& P, const Kernel& k, int spw, int64_t E) {
+  const int64_t all = resident_waves(P, k) * spw * cgtp::env_int("CGTP_CONV_CHUNK_MULT", 1), few = spw >= 8 ? 8 : 3;
+  if (E >= 2 * all) return all;
+  return std::min(std::min(E, all), std::max<int64_t>(1024 * spw, E / few));
+}
+
 // 64 words of pinned host memory, one per cache line, handed out to concurrent calls; allocated on first use and kept
 // until the process ends.  take() answers -1 if none is free or the allocation failed.
 struct HostFlags {
@@ -768,7 +781,7 @@ cgtp_status conv_forward_impl(cgtp_plan* plan, const void* x_nodes, const void* 
   const Kernel& k = P.k[CGTP_K_CONV_FWD];
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_FWD].spw;   // edge-range workers per wave
-  int64_t nchunk = std::min<int64_t>(E, resident_waves(P, k) * spw * cgtp::env_int("CGTP_CONV_CHUNK_MULT", 1));
+  int64_t nchunk = conv_ranges(P, k, spw, E);
   size_t part_bytes = (size_t)nchunk * 2 * P.dim_z() * P.elt();
   void* part = nullptr;
   cgtp_status s = CGTP_OK;
@@ -843,7 +856,7 @@ cgtp_status conv_backward_perm(cgtp_plan* plan, const void* x_nodes, const void*
   const Kernel& k = P.k[CGTP_K_CONV_BWD];
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_BWD].spw;   // edge-range workers per wave
-  int64_t nchunk = std::min<int64_t>(E, resident_waves(P, k) * spw * cgtp::env_int("CGTP_CONV_CHUNK_MULT", 1));
+  int64_t nchunk = conv_ranges(P, k, spw, E);
   size_t part_bytes = round_up((size_t)nchunk * 2 * P.dim_x() * P.elt(), 256);
   const size_t recv_bytes = round_up((size_t)E * 8, 256);
   // one scratch row for the gy / gW words of the pipelined kernel's phantom edge (odd edge ranges)
@@ -892,9 +905,8 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
   const Kernel& kb = P.k[CGTP_K_CONV_DBL_BWD];
   if (!kf.fn || !kb.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spwf = P.map[CGTP_K_CONV_DBL_FWD].spw, spwb = P.map[CGTP_K_CONV_DBL_BWD].spw;
-  const int mult = cgtp::env_int("CGTP_CONV_CHUNK_MULT", 1);
-  int64_t nf = std::min<int64_t>(E, resident_waves(P, kf) * spwf * mult);
-  int64_t nb = std::min<int64_t>(E, resident_waves(P, kb) * spwb * mult);
+  int64_t nf = conv_ranges(P, kf, spwf, E);
+  int64_t nb = conv_ranges(P, kb, spwb, E);
   // the two walks run one after the other on the stream and share the side buffer
   size_t part_f = (size_t)nf * 2 * P.dim_z() * P.elt();
   size_t part_b = round_up((size_t)nb * 2 * P.dim_x() * P.elt(), 256);
@@ -943,7 +955,7 @@ cgtp_status conv_forward_atomic(cgtp_plan* plan, const void* x_nodes, const void
   const Kernel& k = P.k[CGTP_K_CONV_FWD_ATOMIC];
   const int wpw = k.wg / 64;
   const int spw = P.map[CGTP_K_CONV_FWD_ATOMIC].spw;   // edge-range workers per wave
-  int64_t nchunk = std::min<int64_t>(E, resident_waves(P, k) * spw * cgtp::env_int("CGTP_CONV_CHUNK_MULT", 1));
+  int64_t nchunk = conv_ranges(P, k, spw, E);
   unsigned grid = (unsigned)((nchunk + (int64_t)wpw * spw - 1) / ((int64_t)wpw * spw));
   const int64_t* no_perm = nullptr;
   void* args[] = {(void*)&x_nodes, (void*)&y_edges, (void*)&W_edges, (void*)&z_nodes, (void*)&recv,
