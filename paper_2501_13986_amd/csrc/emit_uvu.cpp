@@ -111,6 +111,12 @@ struct Em {
   bool nt_loads = false, nt_stores = false;
   int nt_all = 0;             // batched kernels (every operand is used once): 1 = non-temporal loads, 2 = stores, 3 = both
   bool stream_nt = false;     // the kernel wants its per-edge streams non-temporal (conv kernels)
+  // Not where a worker's run of weights is shorter than a cache line: the rest of the line belongs to the next path, and a
+  // line marked non-temporal is fetched (or written out) again for it.
+  // 4 channels, 20 000 nodes of degree 40: forward 154 -> 121 us, backward 413 -> 269; 16 fp32 channels, 9 000 nodes of degree
+  // 30: 86 -> 74, 189 -> 172, second order 448 -> 350.  From 128 bytes on the hint pays (16 fp64 channels, backward 215 us
+  // with it, 242 without; 32 fp32 channels 424 and 457).
+  bool stream_hint() const { return env_int("CGTP_STREAM_NT", 1) != 0 && M.G * M.cpl * (int)P.elt() >= 128; }
   bool emit_lz = true;            // double backward: also form dL/dgz (the convolution's sender walk leaves it out)
   bool accumulate_store = false;  // add to what memory holds (plain read-modify-write by the owning lane)
   std::set<int> written_z;        // double backward with phases: dL/dgz segments an earlier phase has stored
@@ -1225,7 +1231,7 @@ static void emit_uvu_forward_impl(const Plan& P, bool conv, Kernel& K, bool atom
          "   const i64* __restrict__ row_ptr, const i64* __restrict__ col, i64 V, i64 E, T* __restrict__ part, i64 nchunk,\n"
          "   const i64* __restrict__ eperm)\n{\n";
     head(E, wpw, true, true);
-    E.stream_nt = env_int("CGTP_STREAM_NT", 1) != 0;  // measured: 3-5 % on the backward, neutral on the forward
+    E.stream_nt = E.stream_hint();
     E.dup = M.spw == 1;
     o << "  if (wave >= nchunk) return;\n";
     o << "  const i64 e0 = (wave * E) / nchunk, e1 = ((wave + 1) * E) / nchunk;\n";
@@ -1449,7 +1455,7 @@ void emit_uvu_backward(const Plan& P, bool conv, Kernel& K) {
          "   const i64* __restrict__ t_row_ptr, const i64* __restrict__ t_perm, const i64* __restrict__ t_recv,\n"
          "   i64 V, i64 E, T* __restrict__ part, i64 nchunk, const i64* __restrict__ eperm, T* __restrict__ dummy)\n{\n";
     head(E, wpw, true, true);
-    E.stream_nt = env_int("CGTP_STREAM_NT", 1) != 0;  // measured: 3-5 % on the backward, neutral on the forward
+    E.stream_nt = E.stream_hint();
     E.dup = M.spw == 1;
     E.pin_accumulators = true;
     o << "  if (wave >= nchunk) return;\n";
@@ -1783,7 +1789,7 @@ void emit_uvu_conv_double(const Plan& P, bool backward_like, Kernel& K) {
          "   const T* __restrict__ Lb, const T* __restrict__ LC, T* __restrict__ z,\n"
          "   const i64* __restrict__ row_ptr, const i64* __restrict__ col, i64 V, i64 E, T* __restrict__ part, i64 nchunk)\n{\n";
     head(E, wpw, true, true);
-    E.stream_nt = env_int("CGTP_STREAM_NT", 1) != 0;
+    E.stream_nt = E.stream_hint();
     E.dup = M.spw == 1;
     o << "  if (wave >= nchunk) return;\n";
     o << "  const i64 e0 = (wave * E) / nchunk, e1 = ((wave + 1) * E) / nchunk;\n";
@@ -1835,7 +1841,7 @@ void emit_uvu_conv_double(const Plan& P, bool backward_like, Kernel& K) {
          "   const i64* __restrict__ t_row_ptr, const i64* __restrict__ t_perm, const i64* __restrict__ t_recv,\n"
          "   i64 V, i64 E, T* __restrict__ part, i64 nchunk)\n{\n";
     head(E, wpw, true, true);
-    E.stream_nt = env_int("CGTP_STREAM_NT", 1) != 0;
+    E.stream_nt = E.stream_hint();
     E.dup = M.spw == 1;
     E.emit_lz = false;
     o << "  if (wave >= nchunk) return;\n";
