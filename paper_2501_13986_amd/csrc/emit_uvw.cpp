@@ -27,6 +27,12 @@ namespace {
 constexpr int kTile = 16;   // samples per wave tile (MFMA M)
 constexpr int kWaves = 4;   // waves per workgroup
 int odd_pitch(int64_t d) { return (int)(d | 1); }
+// A dense product can run over the 2 l3 + 1 components of z' (contract with y and C first) or over the 2 l1 + 1 of x
+// (contract afterwards).  The matrix instructions are the larger part of the kernels' issue time, the contraction costs
+// about the same on either side, so the paths with at most half as many components in x take the second form (the
+// scalars' paths; l <= 2: 29 products a channel step instead of 35).  (1, 1, 2) would save two more, but its operands
+// or accumulators are the registers that put the kernels into private memory.
+bool uvw_x_form(const PathInfo& q) { return 2 * (2 * q.l1 + 1) <= 2 * q.l3 + 1; }
 std::string lit(double v) {
   char b[48];
   std::snprintf(b, sizeof b, "(%.9ef)", v);
@@ -84,6 +90,30 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
   o << "extern \"C\" __global__ void __launch_bounds__(" << K.wg << ") " << (staged ? "" : "__attribute__((amdgpu_waves_per_eu(" + std::to_string(env_int("CGTP_UVW_OCC", 2)) + "))) ") << K.name
     << "(const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ W, T* __restrict__ z, i64 B)\n{\n";
   o << "  __shared__ __attribute__((aligned(16))) T lds_w[" << P.n_w << "];\n";
+  // Paths whose product runs over the components of x: D = x W accumulates over the channel loop, the contraction with y
+  // and C follows it in D's layout, with y through LDS.  Not where the LDS for that would cost a workgroup, and not where D's
+  // registers would come on top of more than 80 of accumulators (256 are there).  32-channel plan, 100 000 rows
+  // 83.7 -> 78.4 us, 17 000 rows 26.3 -> 23.7; unequal multiplicities (32, 16, 16 -> 16, 32, 16), 50 000 rows 27.3 -> 26.4.
+  int yd_lo = 0, yd_hi = -1, acc_regs = 0;
+  {
+    std::set<int> zs;
+    for (auto& pq : P.paths) zs.insert(pq.iz);
+    for (int sz : zs) acc_regs += 4 * (2 * P.irz[sz].l + 1) * (P.irz[sz].mul / 16);
+  }
+  for (auto& pq : P.paths)
+    if (uvw_x_form(pq))
+      for (auto& n : pq.nz) {
+        const int j = (int)P.offy[pq.iy] + n.j;
+        yd_lo = yd_hi < 0 ? j : std::min(yd_lo, j);
+        yd_hi = std::max(yd_hi, j);
+      }
+  const int yd_words = (yd_hi - yd_lo + 1 + 3) / 4 * 4;
+  const int64_t yd_bytes = (int64_t)kWaves * kTile * yd_words * 4;
+  auto groups = [](int64_t lds) { return std::min<int64_t>(2, 160 * 1024 / lds); };   // workgroups of a CU (registers allow two)
+  const bool x_forms = !staged && acc_regs <= 80 && groups(lds_bytes) == groups(lds_bytes + yd_bytes);
+  const int yd_pitch = x_forms ? yd_words : 0;
+  auto x_form = [&](const PathInfo& pq) { return x_forms && uvw_x_form(pq); };
+  if (yd_pitch) o << "  __shared__ __attribute__((aligned(16))) T lds_yd[" << kWaves * kTile * yd_pitch << "];\n";
   if (staged) o << "  __shared__ T lds_t[" << kWaves << "][" << region << "];\n";
   // weights -> LDS once per workgroup (the grid is one workgroup per CU slot): all loads of a thread
   // are in flight before its first LDS write
@@ -204,6 +234,13 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
     for (int k = 0; k < 2 * ir.l + 1; ++k)
       for (int h = 0; h < ir.mul / 16; ++h) o << "    f4 acc" << sz << "_" << k << "_" << h << " = {0.0f, 0.0f, 0.0f, 0.0f};\n";
   }
+  if (yd_pitch)
+    for (int j = yd_lo; j <= yd_hi; ++j)
+      if (ywords.count(j)) o << "    lds_yd[(wv * " << kTile << " + s) * " << yd_pitch << " + " << j - yd_lo << "] = y" << j << ";\n";
+  for (size_t p = 0; p < P.paths.size(); ++p)
+    if (x_form(P.paths[p]))
+      for (int i = 0; i < 2 * P.paths[p].l1 + 1; ++i)
+        for (int h = 0; h < P.paths[p].mul_z / 16; ++h) o << "    f4 xw" << p << "_" << i << "_" << h << " = {0.0f, 0.0f, 0.0f, 0.0f};\n";
   // coefficient products, once per tile
   int tcount = 0;
   std::vector<std::vector<std::pair<std::string, bool>>> tref(P.paths.size());
@@ -351,7 +388,7 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
     o << "      " << (pq.mul_x < maxmul ? "if (4 * c < " + std::to_string(pq.mul_x) + ") " : std::string()) << "{ // path " << p << ": l=("
       << pq.l1 << "," << pq.l2 << "," << pq.l3 << ")\n";
     std::vector<bool> started((size_t)n3, false);
-    for (size_t n = 0; n < pq.nz.size(); ++n) {
+    for (size_t n = 0; n < pq.nz.size() && !x_form(pq); ++n) {
       const Nz& nz = pq.nz[n];
       std::string tt = std::string(tref[p][n].second ? "-" : "") + tref[p][n].first;
       std::string xx = "x" + std::to_string(pq.ix) + "_" + std::to_string(nz.i);
@@ -371,11 +408,44 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
         if (started[k])
           o << "          acc" << pq.iz << "_" << k << "_" << h << " = __builtin_amdgcn_mfma_f32_16x16x4f32(q" << k << ", b_, acc" << pq.iz
             << "_" << k << "_" << h << ", 0, 0, 0);\n";
+      for (int i = 0; i < 2 * pq.l1 + 1 && x_form(pq); ++i)
+        o << "          xw" << p << "_" << i << "_" << h << " = __builtin_amdgcn_mfma_f32_16x16x4f32(x" << pq.ix << "_" << i << ", b_, xw" << p << "_" << i
+          << "_" << h << ", 0, 0, 0);\n";
       o << "        }\n";
     }
     o << "      }\n";
   }
   o << "    }\n";
+  {
+    // register r of lane (s, q) of D is sample 4q+r, column w = 16h+s: that sample's y comes from LDS (kept in registers
+    // over the channel loop and exchanged between the lanes, the words put the kernel into private memory)
+    for (int r = 0; r < 4 && yd_pitch; ++r) {
+      std::vector<std::string> nm;
+      for (int j = yd_lo; j <= yd_hi; ++j) nm.push_back("yd" + std::to_string(j) + "_" + std::to_string(r));
+      o << "    T";
+      for (size_t t = 0; t < nm.size(); ++t) o << (t ? ", " : " ") << nm[t];
+      o << ";\n    { const T* p_ = lds_yd + (wv * " << kTile << " + 4 * q + " << r << ") * " << yd_pitch << ";";
+      wide_load(o, nm);
+      o << " }\n";
+    }
+    for (size_t p = 0; p < P.paths.size(); ++p) {
+      const PathInfo& pq = P.paths[p];
+      if (!x_form(pq)) continue;
+      for (auto& n : pq.nz) {
+        const double c = n.v * pq.coeff;
+        for (int r = 0; r < 4; ++r) {
+          const std::string yv = "yd" + std::to_string((int)P.offy[pq.iy] + n.j) + "_" + std::to_string(r);
+          const std::string t = std::fabs(std::fabs(c) - 1.0) < 1e-15 ? (c < 0 ? "-" : "") + yv : yv + " * " + lit(c);
+          o << "    { const T t_ = " << t << ";";
+          for (int h = 0; h < pq.mul_z / 16; ++h) {
+            const std::string acc = "acc" + std::to_string(pq.iz) + "_" + std::to_string(n.k) + "_" + std::to_string(h) + "[" + std::to_string(r) + "]";
+            o << " " << acc << " = FMA(t_, xw" << p << "_" << n.i << "_" << h << "[" << r << "], " << acc << ");";
+          }
+          o << " }\n";
+        }
+      }
+    }
+  }
   if (staged) {
   // z tile through LDS: accumulator register i of lane (s, q) is sample 4q+i, column w = 16h+s
   o << "    __builtin_amdgcn_wave_barrier();\n";
@@ -671,7 +741,7 @@ void emit_uvw_backward(const Plan& P, Kernel& K, Kernel& Kred) {
       std::set<std::pair<long long, int>> tp;
       for (auto& n : q.nz) tp.insert({std::llround(std::fabs(n.v * q.coeff) * 1e13), n.j});
       const int hz = q.mul_z / 16;
-      return 32.0 * (2 * std::min(q.l1, q.l3) + 1) * hz + 4.0 * (double)(q.nz.size() * (q.l1 < q.l3 ? hz : 1) + tp.size());
+      return 32.0 * (2 * (uvw_x_form(q) ? q.l1 : q.l3) + 1) * hz + 4.0 * (double)(q.nz.size() * (uvw_x_form(q) ? hz : 1) + tp.size());
     };
     double total = 0;
     for (auto& q : P.paths) total += unit_cost(q) * (q.mul_x / 16);
@@ -1094,13 +1164,10 @@ void emit_uvw_backward(const Plan& P, Kernel& K, Kernel& Kred) {
         o << "          { // path " << it.p << " l=(" << pq.l1 << "," << pq.l2 << "," << pq.l3 << "), u block " << it.h << ", sample 4q+" << it.i << "\n";
         std::map<std::pair<long long, int>, std::string> seen;
         int tc = 0;
-        // The product sums over the smaller of the two component counts: A = z' (row u = 16h+s, inner index q <-> sample
-        // 4q+i) and B = gz of the same samples, one matrix instruction per k; or, where 2 l1 + 1 < 2 l3 + 1, A = x and
-        // B = sum_jk C y_j gz_k, one per component of x (35 -> 27 for l <= 2; the matrix instructions are the larger
-        // part of a block wave's issue time and the extra FMAs, one per nonzero and further half of w, the smaller).
-        // 32-channel plan: tp_backward 100 000 rows 212 -> 195 us, 17 000 rows 66 -> 62, 1 000 rows 32.6 -> 30.7, and the error of
-        // gW against fp64 falls from 7.1e-7 to 6.2e-7.
-        const bool x_form = pq.l1 < pq.l3;
+        // A = z' (row u = 16h+s, inner index q <-> sample 4q+i) and B = gz of the same samples, one matrix instruction per
+        // k; or, for the paths of uvw_x_form, A = x and B = sum_jk C y_j gz_k, one per component of x.  32-channel plan,
+        // 100 000 rows 212 -> 195 us, 17 000 rows 66 -> 62, 1 000 rows 32.6 -> 31.0, error of gW against fp64 7.2e-7 -> 6.6e-7.
+        const bool x_form = uvw_x_form(pq);
         const int n1 = 2 * pq.l1 + 1, terms = x_form ? n1 : n3, copies = x_form ? HZ : 1;
         std::vector<bool> started((size_t)terms, false);
         for (auto& nz : pq.nz) {
