@@ -234,6 +234,9 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
     for (int k = 0; k < 2 * ir.l + 1; ++k)
       for (int h = 0; h < ir.mul / 16; ++h) o << "    f4 acc" << sz << "_" << k << "_" << h << " = {0.0f, 0.0f, 0.0f, 0.0f};\n";
   }
+  // one lane's words of lds_yd are read by others of its wave: barriers (no instruction, an order for the compiler) keep the
+  // stores behind the reads of the tile before and ahead of this tile's
+  if (yd_pitch) o << "    __builtin_amdgcn_wave_barrier();\n";
   if (yd_pitch)
     for (int j = yd_lo; j <= yd_hi; ++j)
       if (ywords.count(j)) o << "    lds_yd[(wv * " << kTile << " + s) * " << yd_pitch << " + " << j - yd_lo << "] = y" << j << ";\n";
@@ -419,6 +422,7 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
   {
     // register r of lane (s, q) of D is sample 4q+r, column w = 16h+s: that sample's y comes from LDS (kept in registers
     // over the channel loop and exchanged between the lanes, the words put the kernel into private memory)
+    if (yd_pitch) o << "    __builtin_amdgcn_wave_barrier();\n";
     for (int r = 0; r < 4 && yd_pitch; ++r) {
       std::vector<std::string> nm;
       for (int j = yd_lo; j <= yd_hi; ++j) nm.push_back("yd" + std::to_string(j) + "_" + std::to_string(r));

@@ -1,0 +1,29 @@
+"""What the shared-weight uvw forward's generated code has to keep (no GPU needed)."""
+import pytest
+
+from paper_2501_13986_amd import binding as b, synth
+
+PLANS = {
+    "nequip": (synth.NEQUIP_X, synth.NEQUIP_Y, synth.NEQUIP_Z),
+    "scalars_only": ("16x0e", "1x0e+1x1o+1x2e", "16x0e+16x1o+16x2e"),
+}
+
+
+@pytest.mark.parametrize("name", list(PLANS))
+def test_lanes_exchange_y_through_lds_behind_a_wave_barrier(name):
+    """A lane reads words of lds_yd that other lanes of its wave stored: a barrier has to stand between the stores of a
+    tile and its reads, and between its reads and the stores of the wave's next tile."""
+    p = b.Plan(*PLANS[name], mode=b.CGTP_UVW, shared_weights=True, dtype=b.CGTP_F32, device=-1)
+    loop = p.source(b.K_TP_FWD).split("for (i64 t_ = ", 1)[1].split("const int wvu", 1)[0]
+    p.close()
+    kinds = []
+    for line in loop.splitlines():
+        if "wave_barrier()" in line:
+            kinds.append("barrier")
+        elif "lds_yd[" in line:
+            kinds.append("store")
+        elif "= lds_yd + " in line:
+            kinds.append("load")
+    assert "store" in kinds and "load" in kinds
+    turns = [k for i, k in enumerate(kinds) if i == 0 or k != kinds[i - 1]]
+    assert turns == ["barrier", "store", "barrier", "load"], turns
