@@ -113,6 +113,27 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
   const bool x_forms = !staged && acc_regs <= 80 && groups(lds_bytes) == groups(lds_bytes + yd_bytes);
   const int yd_pitch = x_forms ? yd_words : 0;
   auto x_form = [&](const PathInfo& pq) { return x_forms && uvw_x_form(pq); };
+  // acc[k] += C y_j D_i of the samples 4q+r (register r), for the accumulators that `own` names
+  auto contract_d = [&](auto own, const char* ind) {
+    for (size_t p = 0; p < P.paths.size(); ++p) {
+      const PathInfo& pq = P.paths[p];
+      if (!x_form(pq)) continue;
+      for (auto& n : pq.nz) {
+        if (!own(pq.iz, n.k)) continue;
+        const double c = n.v * pq.coeff;
+        for (int r = 0; r < 4; ++r) {
+          const std::string yv = "yd" + std::to_string((int)P.offy[pq.iy] + n.j) + "_" + std::to_string(r);
+          const std::string t = std::fabs(std::fabs(c) - 1.0) < 1e-15 ? (c < 0 ? "-" : "") + yv : yv + " * " + lit(c);
+          o << ind << "{ const T t_ = " << t << ";";
+          for (int h = 0; h < pq.mul_z / 16; ++h) {
+            const std::string acc = "acc" + std::to_string(pq.iz) + "_" + std::to_string(n.k) + "_" + std::to_string(h) + "[" + std::to_string(r) + "]";
+            o << " " << acc << " = FMA(t_, xw" << p << "_" << n.i << "_" << h << "[" << r << "], " << acc << ");";
+          }
+          o << " }\n";
+        }
+      }
+    }
+  };
   if (yd_pitch) o << "  __shared__ __attribute__((aligned(16))) T lds_yd[" << kWaves * kTile * yd_pitch << "];\n";
   if (staged) o << "  __shared__ T lds_t[" << kWaves << "][" << region << "];\n";
   // weights -> LDS once per workgroup (the grid is one workgroup per CU slot): all loads of a thread
@@ -432,23 +453,7 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
       wide_load(o, nm);
       o << " }\n";
     }
-    for (size_t p = 0; p < P.paths.size(); ++p) {
-      const PathInfo& pq = P.paths[p];
-      if (!x_form(pq)) continue;
-      for (auto& n : pq.nz) {
-        const double c = n.v * pq.coeff;
-        for (int r = 0; r < 4; ++r) {
-          const std::string yv = "yd" + std::to_string((int)P.offy[pq.iy] + n.j) + "_" + std::to_string(r);
-          const std::string t = std::fabs(std::fabs(c) - 1.0) < 1e-15 ? (c < 0 ? "-" : "") + yv : yv + " * " + lit(c);
-          o << "    { const T t_ = " << t << ";";
-          for (int h = 0; h < pq.mul_z / 16; ++h) {
-            const std::string acc = "acc" + std::to_string(pq.iz) + "_" + std::to_string(n.k) + "_" + std::to_string(h) + "[" + std::to_string(r) + "]";
-            o << " " << acc << " = FMA(t_, xw" << p << "_" << n.i << "_" << h << "[" << r << "], " << acc << ");";
-          }
-          o << " }\n";
-        }
-      }
-    }
+    contract_d([](int, int) { return true; }, "    ");
   }
   if (staged) {
   // z tile through LDS: accumulator register i of lane (s, q) is sample 4q+i, column w = 16h+s
@@ -516,21 +521,47 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
   if (tail) {
     // units of work: one (output segment, k) pair = the accumulators of that component for both halves of w; its
     // cost is one matrix instruction per path into the segment, half of w and channel step.  Longest first onto the
-    // least loaded of the four waves.
+    // least loaded of the four waves.  The paths whose product runs over x keep that form, operand for operand and in the
+    // same order, so that a row's result does not depend on its place in the batch; every wave that holds one of their
+    // components forms D again.
     struct Unit { int sz, k, cost; };
     std::vector<Unit> units;
     for (int sz : used_z) {
       int np = 0;
-      for (auto& pq : P.paths) np += pq.iz == sz;
+      for (auto& pq : P.paths) np += pq.iz == sz && !x_form(pq);
       for (int k = 0; k < 2 * P.irz[sz].l + 1; ++k) units.push_back({sz, k, np * (P.irz[sz].mul / 16)});
     }
     std::stable_sort(units.begin(), units.end(), [](const Unit& a, const Unit& b) { return a.cost > b.cost; });
     std::vector<std::vector<Unit>> role(kWaves);
     std::vector<int> load(kWaves, 0);
+    // the components i of x that a wave with the (segment, k) pairs `mine` needs of path p's D
+    auto d_parts = [&](size_t p, const std::set<std::pair<int, int>>& mine) {
+      std::set<int> is;
+      if (x_form(P.paths[p]))
+        for (auto& n : P.paths[p].nz)
+          if (mine.count({P.paths[p].iz, n.k})) is.insert(n.i);
+      return is;
+    };
+    auto d_cost = [&](const std::set<std::pair<int, int>>& mine) {
+      int c = 0;
+      for (size_t p = 0; p < P.paths.size(); ++p) c += (int)d_parts(p, mine).size() * (P.paths[p].mul_z / 16);
+      return c;
+    };
+    std::vector<std::set<std::pair<int, int>>> pairs(kWaves);
     for (auto& un : units) {
-      const int r = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-      role[r].push_back(un);
-      load[r] += un.cost;
+      int best = 0, cost = 0;
+      for (int r = 0; r < kWaves; ++r) {
+        auto with = pairs[r];
+        with.insert({un.sz, un.k});
+        const int c = load[r] + un.cost + d_cost(with) - d_cost(pairs[r]);
+        if (r == 0 || c < cost) {
+          best = r;
+          cost = c;
+        }
+      }
+      role[best].push_back(un);
+      pairs[best].insert({un.sz, un.k});
+      load[best] = cost;
     }
     o << "  const int wvu = __builtin_amdgcn_readfirstlane(wv);\n";
     o << "  for (i64 tt_ = nmain + blockIdx.x; tt_ < ntile; tt_ += gridDim.x) {\n";
@@ -541,19 +572,26 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
     o << "    const T* xrow = x + row_ * " << DX << ";\n";
     for (int r = 0; r < kWaves; ++r) {
       o << "    " << (r ? "else " : "") << "if (wvu == " << r << ") {\n";
-      std::set<std::pair<int, int>> mine;
-      for (auto& un : role[r]) mine.insert({un.sz, un.k});
+      const std::set<std::pair<int, int>>& mine = pairs[r];
       std::vector<size_t> rp;   // paths with a component in this role
       for (size_t p = 0; p < P.paths.size(); ++p)
         for (int k = 0; k < 2 * P.paths[p].l3 + 1; ++k)
           if (mine.count({P.paths[p].iz, k})) { rp.push_back(p); break; }
-      std::set<int> yw, xs;
+      std::set<int> yw, yd, xs;   // yd: words of y that D's contraction takes for the samples 4q+0..3
       for (size_t p : rp) {
         xs.insert(P.paths[p].ix);
         for (auto& n : P.paths[p].nz)
-          if (mine.count({P.paths[p].iz, n.k})) yw.insert((int)P.offy[P.paths[p].iy] + n.j);
+          if (mine.count({P.paths[p].iz, n.k})) (x_form(P.paths[p]) ? yd : yw).insert((int)P.offy[P.paths[p].iy] + n.j);
       }
       for (int j : yw) o << "      const T y" << j << " = yb[" << j << "];\n";
+      for (int i = 0; i < 4 && !yd.empty(); ++i) {
+        o << "      const T* yd_" << i << " = y + (b0 + (4 * q + " << i << " < rows ? 4 * q + " << i << " : 0)) * " << DY << ";\n     ";
+        for (int j : yd) o << " const T yd" << j << "_" << i << " = yd_" << i << "[" << j << "];";
+        o << "\n";
+      }
+      for (size_t p : rp)
+        for (int i : d_parts(p, mine))
+          for (int h = 0; h < P.paths[p].mul_z / 16; ++h) o << "      f4 xw" << p << "_" << i << "_" << h << " = {0.0f, 0.0f, 0.0f, 0.0f};\n";
       for (auto& un : role[r])
         for (int h = 0; h < P.irz[un.sz].mul / 16; ++h) o << "      f4 acc" << un.sz << "_" << un.k << "_" << h << " = {0.0f, 0.0f, 0.0f, 0.0f};\n";
       // coefficient products of the role's nonzeros
@@ -564,7 +602,7 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
         std::map<std::pair<long long, int>, std::string> seen;
         for (auto& n : pq.nz) {
           const double c = n.v * pq.coeff, a = std::fabs(c);
-          if (!mine.count({pq.iz, n.k})) { tr[p].push_back({"", false}); continue; }
+          if (x_form(pq) || !mine.count({pq.iz, n.k})) { tr[p].push_back({"", false}); continue; }
           auto key = std::make_pair(std::llround(a * 1e13), n.j);
           auto it = seen.find(key);
           if (it == seen.end()) {
@@ -602,7 +640,7 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
         std::vector<bool> started((size_t)n3, false);
         for (size_t n = 0; n < pq.nz.size(); ++n) {
           const Nz& nz = pq.nz[n];
-          if (!mine.count({pq.iz, nz.k})) continue;
+          if (x_form(pq) || !mine.count({pq.iz, nz.k})) continue;
           const std::string tt = std::string(tr[p][n].second ? "-" : "") + tr[p][n].first;
           const std::string xx = "x" + std::to_string(pq.ix) + "_" + std::to_string(nz.i);
           if (!started[nz.k]) {
@@ -618,11 +656,15 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
             if (started[k])
               o << "            acc" << pq.iz << "_" << k << "_" << h << " = __builtin_amdgcn_mfma_f32_16x16x4f32(q" << k << ", b_, acc" << pq.iz
                 << "_" << k << "_" << h << ", 0, 0, 0);\n";
+          for (int i : d_parts(p, mine))
+            o << "            xw" << p << "_" << i << "_" << h << " = __builtin_amdgcn_mfma_f32_16x16x4f32(x" << pq.ix << "_" << i << ", b_, xw" << p
+              << "_" << i << "_" << h << ", 0, 0, 0);\n";
           o << "          }\n";
         }
         o << "        }\n";
       }
       o << "      }\n";
+      contract_d([&](int sz, int k) { return mine.count({sz, k}) > 0; }, "      ");
       // accumulator register i of lane (s, q) is sample 4q+i, column w = 16h+s
       for (int i = 0; i < 4; ++i) {
         o << "      if (4 * q + " << i << " < rows) { T* p_ = z + (b0 + 4 * q + " << i << ") * " << DZ << ";\n";

@@ -40,3 +40,18 @@ def test_uvw_forms(name, B):
     assert_close(z.cpu().numpy(), otp.forward(spec, x, y, W), "f32", "z")
     for got, ref, what in zip(g, otp.backward(spec, x, y, W, gz), ("gx", "gy", "gW")):
         assert_close(got.cpu().numpy(), ref, "f32", what)
+
+
+@pytest.mark.parametrize("B", [1000, 40007])   # tiles split over a workgroup only; whole tiles and split ones
+@pytest.mark.parametrize("name", list(PLANS))
+def test_uvw_forward_row_does_not_depend_on_its_place(name, B):
+    """Equal rows give equal results, bit for bit, whichever tile they are in."""
+    from paper_2501_13986_amd import binding as b
+    irr, paths = PLANS[name][:3], (PLANS[name][3] if len(PLANS[name]) > 3 else None)
+    print(f"plan={name} B={B} entry=tp_forward uvw, equal rows", flush=True)
+    plan = b.Plan(*irr, paths=paths, mode=b.CGTP_UVW, shared_weights=True, dtype=b.CGTP_F32, device=0)
+    row = lambda seed, n: torch.from_numpy(synth.normal(seed, (1, n)).astype(np.float32)).cuda().expand(B, n).contiguous()
+    W = torch.from_numpy(synth.normal(3, plan.n_w, 0.2).astype(np.float32)).cuda()
+    z = b.tp_forward(plan, row(1, plan.dim_x), row(2, plan.dim_y), W, torch.full((B, plan.dim_z), float("nan"), device="cuda"))
+    torch.cuda.synchronize()
+    assert torch.equal(z, z[:1].expand(B, -1).contiguous())
