@@ -59,7 +59,8 @@ int pow2ceil(int v) {
 
 // Channel -> lane assignment.  Adjacent channels share a lane (`cpl` of them) so that a lane's
 // words are contiguous; a wave is filled with several samples when the multiplicity is small.
-LaneMap pick_map(const Plan& P, int kind) {
+// step: 0 the convolution's wide map, 1 the narrow one, 2 one channel per lane (other kernels: the same map for all).
+LaneMap pick_map(const Plan& P, int kind, int step) {
   static const char* const kTag[9] = {"TP_FWD",          "TP_BWD",     "CONV_FWD",     "CONV_BWD",    "CONV_FWD_ATOMIC",
                                       "CONV_BWD_ATOMIC", "TP_DBL_BWD", "CONV_DBL_FWD", "CONV_DBL_BWD"};
   const bool conv = kind == CGTP_K_CONV_FWD || kind == CGTP_K_CONV_BWD || kind == CGTP_K_CONV_FWD_ATOMIC ||
@@ -83,7 +84,7 @@ LaneMap pick_map(const Plan& P, int kind) {
     // 64 lanes of an atomic instruction cover contiguous words (8 requests in fp32 instead of 16 with pairs)
     if (atomic) cpl = 1;
     // twice the operands of the first-order kernels per channel
-    if (kind == CGTP_K_TP_DBL_BWD) cpl = 1;
+    if (kind == CGTP_K_TP_DBL_BWD || (kind == CGTP_K_CONV_DBL_FWD && step > 0)) cpl = 1;
     // A convolution kernel that needs a second pass walks its whole edge range again (y, the graph arrays and the
     // gathers' latency once more, and a sender walk reads back its gy words), so the lane takes as many adjacent
     // channels (up to `most`) as bring it to one pass.
@@ -94,7 +95,8 @@ LaneMap pick_map(const Plan& P, int kind) {
     // walk stops at three: four would halve the edge ranges of a 256-channel plan, and conv_forward_static, whose static
     // buffer bounds the ranges, is documented to refuse that plan.  The receiver walk of the
     // second-order pass up to 128 fp32 channels stays at one channel and two passes (128 channels 645, in one pass 667).
-    if (conv && !atomic) {
+    if (conv && step == 2) cpl = 1;
+    if (conv && !atomic && step == 0) {
       int most = P.dtype == CGTP_F32 ? (kind == CGTP_K_CONV_FWD ? 3 : 4) : 2;
       if (kind == CGTP_K_CONV_DBL_FWD && P.dtype == CGTP_F32 && M <= 128) most = 1;
       for (int c = 1; c <= most; ++c) {
@@ -178,10 +180,21 @@ struct CompileError {
   std::string msg;
 };
 
+// Plans with more paths than this are tuned for registers, not by their first schedule.
+constexpr size_t kFewPaths = 24;
+
+// What a kernel's registers cost, best first: 0 no private memory and (many paths) within 256 registers, i.e. two waves per
+// SIMD; 1 within 256 with a light spill (many paths); 2 no private memory, one wave per SIMD; above: the spill.
+long register_class(const Kernel& k, bool few) {
+  if (k.scratch == 0) return few || k.vgprs <= 256 ? 0 : 2;
+  if (!few && k.scratch <= 256 && k.vgprs <= 256) return 1;
+  return 2 + k.scratch;
+}
+
 template <class Emit>
 void build_kernel(cgtp::Plan& P, int kind, Emit emit, int device) {
   Kernel& K = P.k[kind];
-  const bool small = P.paths.size() <= 24;
+  const bool small = P.paths.size() <= kFewPaths;
   std::vector<cgtp::Schedule> cands = schedule_candidates(kind, small);
   if (cgtp::env_int("CGTP_NO_SCHEDULE_SEARCH", 0)) cands.resize(1);
   Kernel best;
@@ -209,7 +222,7 @@ void build_kernel(cgtp::Plan& P, int kind, Emit emit, int device) {
     } catch (const std::exception& e) {
       throw CompileError{e.what()};
     }
-    const bool fits = cur.scratch == 0 && (small || cur.vgprs <= 256);
+    const bool fits = register_class(cur, small) == 0;
     // ranking of the candidates that do not fit (many-path plans): within 256 registers with at most 256 B of
     // private memory, then spill-free with more registers (one wave per SIMD), then by the amount of spill
     long key;
@@ -411,13 +424,13 @@ cgtp_status cgtp_plan_create_ex(const char* irreps_x, const char* irreps_y, cons
   if (P.shared_w && P.mode == CGTP_UVU) return fail(CGTP_EUNSUPPORTED, "shared weights are supported for uvw plans only");
   if (P.ir_mul && P.mode != CGTP_UVU) return fail(CGTP_EUNSUPPORTED, "the IR_MUL layout is implemented for uvu plans only");
 
-  for (int k = 0; k < 9; ++k) P.map[k] = pick_map(P, k);
+  for (int k = 0; k < 9; ++k) P.map[k] = pick_map(P, k, 0);
   try {
     if (P.mode == CGTP_UVU) {
       // A convolution kernel whose wave holds several edge-range workers is lane-divergent by design.  If every
       // schedule of it is refused (see jit_compile: divergence together with register relocation), the kernel is
       // generated again with one worker per wave, which has no lane-conditional code.
-      auto build_conv = [&](int kind, auto emit) {
+      auto build_worker = [&](int kind, auto emit) {
         try {
           build_kernel(P, kind, emit, device);
         } catch (const CompileError&) {
@@ -430,6 +443,50 @@ cgtp_status cgtp_plan_create_ex(const char* irreps_x, const char* irreps_y, cons
           m.npass = (M + m.G * m.cpl - 1) / (m.G * m.cpl);
           build_kernel(P, kind, emit, device);
         }
+      };
+      // The wide lane map is chosen from the multiplicities alone; what it costs in registers depends on the paths.  Where its
+      // kernel needs private memory or (many paths, second-order pass) leaves one wave per SIMD, the narrow map's is
+      // compiled as well, then one channel per lane's, and the first of the best class (register_class) is kept.  The
+      // receiver walks of a plan with many paths take the narrow map at once: they are bound by their instructions (in fp64
+      // the second-order one is not where both maps leave one wave per SIMD).
+      // us per kernel, 1 000 nodes of degree 30, both parities, y of l <= 3, wide -> this: second-order sender walk fp32
+      // 96 channels l <= 3 1260 -> 723, 144 6377 -> 1894, 192 5893 -> 1740, 256 9028 -> 2351, 160 channels l <= 2 1377 -> 547;
+      // fp64 96 channels l <= 3 8243 -> 3567, 192 channels l <= 2 5758 -> 1395; second-order receiver walk 160 channels l <= 2
+      // 1137 -> 323, 192 466 -> 358; forward fp32 96 channels l <= 3 289 -> 226 (but 144 l <= 2 173 -> 223), fp64 989 -> 697.
+      // The sender walk of the backward gains from the wide map with any number of paths: 96 channels l <= 3 577 -> 450.
+      auto build_conv = [&](int kind, auto emit) {
+        const bool receiver = kind == CGTP_K_CONV_FWD || (kind == CGTP_K_CONV_DBL_FWD && dtype == CGTP_F32), many = P.paths.size() > kFewPaths;
+        std::vector<LaneMap> maps;
+        auto add = [&](const LaneMap& m) {
+          for (auto& have : maps)
+            if (have.cpl == m.cpl) return;
+          maps.push_back(m);
+        };
+        if (!(receiver && many)) add(pick_map(P, kind, 0));
+        add(pick_map(P, kind, 1));
+        if (kind == CGTP_K_CONV_BWD || kind == CGTP_K_CONV_DBL_BWD) add(pick_map(P, kind, 2));
+        Kernel best;
+        LaneMap best_map;
+        long best_class = -1;
+        for (size_t t = 0; t < maps.size(); ++t) {
+          P.map[kind] = maps[t];
+          P.k[kind] = Kernel();
+          try {
+            build_worker(kind, emit);
+          } catch (const CompileError&) {
+            if (best_class < 0 && t + 1 == maps.size()) throw;
+            continue;
+          }
+          const long c = register_class(P.k[kind], !many || kind == CGTP_K_CONV_BWD);
+          if (best_class < 0 || c < best_class) {
+            best = std::move(P.k[kind]);
+            best_map = P.map[kind];
+            best_class = c;
+          }
+          if (device == -1 || best_class == 0) break;
+        }
+        P.k[kind] = std::move(best);
+        P.map[kind] = best_map;
       };
       build_kernel(P, CGTP_K_TP_FWD, [&](Kernel& k) { cgtp::emit_uvu_forward(P, false, k); }, device);
       build_kernel(P, CGTP_K_TP_BWD, [&](Kernel& k) { cgtp::emit_uvu_backward(P, false, k); }, device);

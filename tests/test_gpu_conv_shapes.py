@@ -12,14 +12,19 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+PAR = "{0}x0e+{0}x0o+{0}x1e+{0}x1o+{0}x2e+{0}x2o+{0}x3e+{0}x3o"
 SPECS.update({
     "mul65": ("65x0e+65x1o", "1x0e+1x1o", "65x0e+65x1o"),         # odd: two passes of one channel per lane
     "mul75": ("75x0e+75x1o", "1x0e+1x1o", "75x0e+75x1o"),         # three channels per lane (fp32)
     "mul130": ("130x0e+130x1o", "1x0e+1x1o", "130x0e+130x1o"),    # even, above 128, no divisor up to four that fits: two passes of two
     "mul256": ("256x0e+256x1o", "1x0e+1x1o", "256x0e+256x1o"),    # four channels per lane (fp32), two passes of two (fp64)
+    # 68 paths: the wide map, the narrow one and one channel per lane in one plan, by what each kernel's registers allow
+    "par96": (PAR.format(96), "1x0e+1x1o+1x2e+1x3o", PAR.format(96)),
+    "par192": (PAR.format(192), "1x0e+1x1o+1x2e+1x3o", PAR.format(192)),
     "odd_row": ("3x0e+3x1o", "1x0e+1x1o", "3x0e+3x1o+3x1e"),      # rows of 12 and 21 words
 })
-GRAPHS.update({"hub": (3, 30000, ())})                            # thousands of ranges in one row
+GRAPHS.update({"hub": (3, 30000, ()),                             # thousands of ranges in one row
+               "small_typical": (12, 150, (0, 7))})
 
 
 def check(spec_name, graph, prec, double=True):
@@ -56,3 +61,9 @@ def test_lane_maps_above_one_wave(spec_name, prec):
 @pytest.mark.parametrize("spec_name", ["odd_row", "mul1", "small"])
 def test_rows_split_over_thousands_of_ranges(spec_name, prec):
     check(spec_name, "hub", prec, double=spec_name == "odd_row")
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("spec_name", ["par96", "par192"])
+def test_lane_maps_of_many_paths(spec_name, prec):
+    check(spec_name, "small_typical", prec)
