@@ -525,7 +525,20 @@ cgtp_status cgtp_plan_create_ex(const char* irreps_x, const char* irreps_y, cons
         }
       }
     } else {
-      cgtp::emit_uvw_forward(P, P.k[CGTP_K_TP_FWD]);
+      // forward: the scalars' paths over x, or all over z' if the former needs more private memory (degree 3, 16 -> 16 channels:
+      // 1 092 bytes against 600)
+      Kernel& kf = P.k[CGTP_K_TP_FWD];
+      cgtp::emit_uvw_forward(P, kf);
+      if (device != -1) {
+        cgtp::jit_compile(kf, -2);
+        if (kf.scratch > 0) {
+          Kernel other;
+          other.sched.x_form = 0;
+          cgtp::emit_uvw_forward(P, other);
+          cgtp::jit_compile(other, -2);
+          if (other.scratch < kf.scratch) kf = std::move(other);
+        }
+      }
       try {
         cgtp::emit_uvw_backward(P, P.k[CGTP_K_TP_BWD], P.k_fix);
       } catch (const cgtp::ShapeNotCovered&) {  // multiplicities the backward does not cover: forward-only plan

@@ -92,7 +92,8 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
   o << "  __shared__ __attribute__((aligned(16))) T lds_w[" << P.n_w << "];\n";
   // Paths whose product runs over the components of x: D = x W accumulates over the channel loop, the contraction with y
   // and C follows it in D's layout, with y through LDS.  Not where the LDS for that would cost a workgroup, and not where D's
-  // registers would come on top of more than 80 of accumulators (256 are there).  32-channel plan, 100 000 rows
+  // registers would come on top of more than 80 of accumulators; whether the rest of the kernel leaves room for them shows only
+  // when it is compiled, so the caller compares both forms where this one needs private memory (sched.x_form).  32-channel plan, 100 000 rows
   // 83.7 -> 78.4 us, 17 000 rows 26.3 -> 23.7; unequal multiplicities (32, 16, 16 -> 16, 32, 16), 50 000 rows 27.3 -> 26.4.
   int yd_lo = 0, yd_hi = -1, acc_regs = 0;
   {
@@ -110,7 +111,7 @@ void emit_uvw_forward(const Plan& P, Kernel& K) {
   const int yd_words = (yd_hi - yd_lo + 1 + 3) / 4 * 4;
   const int64_t yd_bytes = (int64_t)kWaves * kTile * yd_words * 4;
   auto groups = [](int64_t lds) { return std::min<int64_t>(2, 160 * 1024 / lds); };   // workgroups of a CU (registers allow two)
-  const bool x_forms = !staged && acc_regs <= 80 && groups(lds_bytes) == groups(lds_bytes + yd_bytes);
+  const bool x_forms = K.sched.x_form && !staged && acc_regs <= 80 && groups(lds_bytes) == groups(lds_bytes + yd_bytes);
   const int yd_pitch = x_forms ? yd_words : 0;
   auto x_form = [&](const PathInfo& pq) { return x_forms && uvw_x_form(pq); };
   // acc[k] += C y_j D_i of the samples 4q+r (register r), for the accumulators that `own` names

@@ -66,6 +66,7 @@ struct Schedule {
   int fresh_y = -1;    // 1: the products v*y[j] are formed anew in every path (never shared between paths)
   int occ = -1;        // waves per SIMD asked of the compiler (overrides the lane map's request)
   int one_kernel = 0;  // per-sample uvw second-order pass: the backward-like kernel also computes dL/dgz (no forward-like kernel)
+  int x_form = 1;      // shared-weight uvw forward: the scalars' paths run over the components of x (0: all paths over those of z')
   int phases = 1;      // backward: x segments, forward convolution: output segments, split into this many phases
                        // (only a phase's own rows and accumulators are live)
 };

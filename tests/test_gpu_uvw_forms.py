@@ -17,6 +17,7 @@ PLANS = {
     "two_scalars": ("32x0e+16x0o", "1x1o+1x2e", "16x1o+32x2e+16x1e"),         # a y segment that starts after word 0, z reached twice
     "l3_coeff": ("16x0e+16x1o", "1x0e+1x3o", "32x3o+16x0e+16x2e", [(0, 1, 0, 1, -0.5), (0, 0, 1, 1, 2.0), (1, 1, 2, 1, 1.5)]),
     "nequip": (synth.NEQUIP_X, synth.NEQUIP_Y, synth.NEQUIP_Z),
+    "degree3": ("16x0e+16x1o+16x2e+16x3o", "1x0e+1x1o+1x2e+1x3o", "16x0e+16x1o+16x2e+16x3o"),   # too many registers: z' form
     "wide_z": ("32x0e", "1x0e+1x1o+1x2e", "64x0e+64x1o+32x2e"),               # too many accumulators: z' form in the forward
 }
 

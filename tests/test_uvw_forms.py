@@ -27,3 +27,19 @@ def test_lanes_exchange_y_through_lds_behind_a_wave_barrier(name):
     assert "store" in kinds and "load" in kinds
     turns = [k for i, k in enumerate(kinds) if i == 0 or k != kinds[i - 1]]
     assert turns == ["barrier", "store", "barrier", "load"], turns
+
+
+# private memory with every path over the components of z'; with the scalars' paths over x it is 1 092, 1 088 and 700 bytes
+@pytest.mark.parametrize("x,y,z,most", [
+    ("16x0e+16x1o+16x2e+16x3o", "1x0e+1x1o+1x2e+1x3o", "16x0e+16x1o+16x2e+16x3o", 600),
+    ("32x0e+32x1o+32x2e+32x3o", "1x0e+1x1o+1x2e+1x3o", "16x0e+16x1o+16x2e+16x3o", 648),
+    ("16x0e+16x0o+16x1e+16x1o+16x2e+16x2o", "1x0e+1x1o+1x2e+1x3o", "16x0e+16x0o+16x1e+16x1o+16x2e+16x2o", 520),
+    (synth.NEQUIP_X, synth.NEQUIP_Y, synth.NEQUIP_Z, 0),
+])
+def test_the_form_with_less_private_memory_is_kept(x, y, z, most):
+    p = b.Plan(x, y, z, mode=b.CGTP_UVW, shared_weights=True, dtype=b.CGTP_F32, device=-2)
+    info = p.kernel_info(b.K_TP_FWD)
+    uses_x = "lds_yd" in p.source(b.K_TP_FWD)
+    p.close()
+    assert info["scratch"] <= most, info
+    assert uses_x == (most == 0)
