@@ -25,6 +25,11 @@ CASES = [  # V, E, receivers, senders
     (5000, 70000, "hub", "hub"),
     (777, 60000, "few", "few"),              # three rows only, all others empty
     (20000, 800000, "sorted", "uniform"),
+    (2, 4500, "one", "uniform"),             # a bucket of one row, cut into pieces
+    (2, 4500, "one", "one"),                 # of equal edges
+    (20000, 900000, "tail", "tail"),         # padding: equal edges at the end of the list
+    (3000, 60000, "missed", "missed"),       # a row that no sampled edge enters: sorted in memory
+    (4194304, 9000, "hub", "tail"),          # the most nodes of the bucket path
     (2000, 2700001, "uniform", "uniform"),   # more edges than the buckets hold: sorts
 ]
 
@@ -37,6 +42,17 @@ def nodes(rng, V, E, how):
         a = np.array([0, V // 2, V - 1])[rng.integers(0, 3, E)]
     elif how == "sorted":
         a.sort()
+    elif how == "one":
+        a[:] = V - 1
+    elif how == "tail":
+        a[E - E // 9:] = V - 1
+    elif how == "missed":                            # the sample: eight neighbours from each of 512 equal parts
+        run = np.arange(512, dtype=np.int64)
+        lo, hi = run * E // 512, (run + 1) * E // 512
+        first = lo + ((((run * 2654435761) % 2 ** 32) * (hi - lo - 7)) >> 32)
+        looked_at = np.zeros(E, bool)
+        looked_at[(first[:, None] + np.arange(8)).ravel()] = True
+        a[~looked_at & (np.arange(E) % 3 != 0)] = V // 2
     return a.astype(np.int64)
 
 
