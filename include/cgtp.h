@@ -270,6 +270,7 @@ cgtp_status cgtp_csr_from_coo(const int64_t* recv, const int64_t* send, int64_t 
  * their neighbour list every step need it on the stream like any other kernel): everything is enqueued on hip_stream,
  * nothing is allocated, nothing waits.  `workspace` is caller-owned device memory of at least
  * cgtp_csr_workspace_bytes(E, V) bytes, 256-byte aligned (CGTP_EINVAL if it is smaller); its contents are scratch.
+ * The size does not shrink when E or V grow: a buffer for the largest graph serves every smaller one.
  * bad_flag (device int32, may be NULL) receives 1 if any index lies outside [0, V) - such edges are then treated as
  * (0, 0) - else 0.  t_row_ptr and t_perm may both be NULL: the transpose (needed by the backward pass only) is skipped. */
 size_t cgtp_csr_workspace_bytes(int64_t E, int64_t V);

@@ -871,15 +871,17 @@ hipError_t csr_build(const int64_t* recv, const int64_t* send, int64_t E, int64_
 
 enum class CsrPath { kSmall, kBuckets, kSort };
 
-// One workgroup where rows and edges fit its LDS; buckets up to 2 560 edges a bucket on average (4 096 fit, so rows may
+// One workgroup where rows and edges fit its LDS; buckets up to 2 560 edges for each of 1 024 (4 096 fit, so rows may
 // be uneven): as many buckets as leave each 512 edges (5 000 nodes of degree 32: 56 us a call, with 256 edges 69, with
 // 1 300 57), but no more than the chip holds at once, two workgroups a CU (20 000 nodes of degree 40: 313 buckets 81 us,
-// 625 buckets 87).  Everything else takes the sorts: above 2.6 million edges, and at most 4 096 edges on more than
-// 4 096 nodes, where the buckets' tables would need more workspace than the sort.
+// 625 buckets 87); with fewer rows than that, as many buckets as there are rows, and cuts.  Larger graphs take the sorts.
+constexpr int64_t kMostEdges = (int64_t)2560 * kBuckets, kMostNodes = (int64_t)kBuckets * kRows;
+
 CsrPath csr_path(int64_t E, int64_t V, BucketPlan& B) {
   B.eb = (int)bits_for((uint64_t)(E > 1 ? E - 1 : 1));
   B.vb = (int)bits_for((uint64_t)(V > 1 ? V - 1 : 1));
-  if (E <= kCap) return V <= kRows ? CsrPath::kSmall : CsrPath::kSort;
+  if (E <= kCap && V <= kRows) return CsrPath::kSmall;
+  if (E > kMostEdges || V > kMostNodes) return CsrPath::kSort;
   const int64_t least = 512, most = 2560, at_once = 512;
   // A bucket is cut if its samples speak for more than fits: 3 500 records, or `most` and five standard deviations of the
   // sample's count, whichever is more (buckets of `most` would be cut for nothing otherwise).  Pieces of about 1 536 records,
@@ -888,17 +890,15 @@ CsrPath csr_path(int64_t E, int64_t V, BucketPlan& B) {
   const double share = (double)B.samples / (double)E;
   B.heavy = (int)std::ceil(std::max(3500 * share, most * share + 5 * std::sqrt(most * share)));
   B.cut = std::max(2, (int)(1536 * share));
-  for (int sh = 0; ((int64_t)1 << sh) <= kRows; ++sh) {
-    const int64_t nb = (V + ((int64_t)1 << sh) - 1) >> sh;
-    if (nb > kBuckets) continue;
-    if (E > most * nb) break;
-    const int64_t half = (V + ((int64_t)2 << sh) - 1) >> (sh + 1);   // buckets of twice the rows
-    if (half < nb && ((int64_t)2 << sh) <= kRows && E <= most * half && (E < least * nb || nb > at_once)) continue;
-    B.shift = sh;
-    B.nb = (int)nb;
-    return CsrPath::kBuckets;
+  B.shift = 0;
+  auto buckets = [&](int shift) { return (V + ((int64_t)1 << shift) - 1) >> shift; };
+  while (buckets(B.shift) > kBuckets) ++B.shift;
+  for (; ((int64_t)2 << B.shift) <= kRows; ++B.shift) {
+    const int64_t nb = buckets(B.shift), half = buckets(B.shift + 1);   // half: with buckets of twice the rows
+    if (half == nb || E > most * half || (E >= least * nb && nb <= at_once)) break;
   }
-  return CsrPath::kSort;
+  B.nb = (int)buckets(B.shift);
+  return CsrPath::kBuckets;
 }
 
 hipError_t csr_buckets(const int64_t* recv, const int64_t* send, int64_t E, int64_t V, int64_t* row_ptr, int64_t* col, int64_t* perm,
@@ -917,18 +917,19 @@ hipError_t csr_buckets(const int64_t* recv, const int64_t* send, int64_t E, int6
 
 }  // namespace
 
+// Grows with E and with V, so that one buffer serves every smaller graph: nothing where one workgroup does it, what E makes of
+// the buckets' tables up to the largest graph that they take, and beyond that at least as much as there.
 hipError_t csr_workspace_bytes(int64_t E, int64_t V, size_t* bytes) {
   *bytes = 256;
   if (E <= 0) return hipSuccess;
   BucketPlan B;
-  switch (csr_path(E, V, B)) {
-    case CsrPath::kSmall: return hipSuccess;   // no scratch
-    case CsrPath::kBuckets: *bytes = BucketWs::bytes(E); return hipSuccess;
-    case CsrPath::kSort: break;
-  }
+  const CsrPath path = csr_path(E, V, B);
+  if (path == CsrPath::kSmall) return hipSuccess;
+  *bytes = BucketWs::bytes(std::min(E, kMostEdges));
+  if (path == CsrPath::kBuckets) return hipSuccess;
   CsrLayout L;
   CSR_TRY(csr_layout(E, V, L));
-  *bytes = L.total;
+  *bytes = std::max(*bytes, L.total);
   return hipSuccess;
 }
 

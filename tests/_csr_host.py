@@ -201,7 +201,7 @@ def build():
     """Path of the compiled program (in a directory of its own)."""
     s = open(CSR).read()
     kernels = s[s.index("// ---- bucket path"):s.index("inline unsigned blocks_for(int64_t n)")]
-    host = s[s.index("CsrPath csr_path(int64_t E"):s.index("hipError_t csr_buckets(")]
+    host = s[s.index("constexpr int64_t kMostEdges"):s.index("hipError_t csr_buckets(")]
     d = tempfile.mkdtemp(prefix="csr_host_")
     src = os.path.join(d, "csr_host.cpp")
     with open(src, "w") as f:

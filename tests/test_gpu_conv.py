@@ -148,7 +148,7 @@ def test_conv_no_edges_zero_fills():
     assert st == 0 and torch.all(z == 0)
 
 
-# 65 536 nodes is the last size whose keys recv * V + send fit 32 bits; 70 001 takes the 64-bit keys
+# (tests/test_gpu_csr.py has the sizes at which the preparation changes its path)
 @pytest.mark.parametrize("V,E,seed", [(23, 140, 0), (1000, 33000, 1), (5, 0, 2), (4, 9, 3), (65536, 50000, 4), (70001, 50000, 5)])
 def test_csr_from_coo_bit_exact(V, E, seed):
     b = _b()

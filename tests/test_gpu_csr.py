@@ -12,10 +12,10 @@ torch = pytest.importorskip("torch")
 CASES = [  # V, E, receivers, senders
     (4096, 4096, "uniform", "uniform"),      # the largest graph of one workgroup
     (4096, 4097, "uniform", "uniform"),      # the smallest with buckets
-    (4097, 4096, "uniform", "uniform"),      # few edges on many nodes: sorts
+    (4097, 4096, "uniform", "uniform"),      # more nodes than one workgroup takes: buckets
     (4097, 4097, "uniform", "uniform"),
     (1, 4096, "uniform", "uniform"),         # one row, the whole LDS
-    (1, 4097, "uniform", "uniform"),         # one row in memory
+    (1, 4097, "uniform", "uniform"),         # one bucket of one row, cut
     (2, 9001, "uniform", "uniform"),
     (3001, 96033, "uniform", "uniform"),
     (1025, 600001, "uniform", "uniform"),
@@ -30,7 +30,11 @@ CASES = [  # V, E, receivers, senders
     (20000, 900000, "tail", "tail"),         # padding: equal edges at the end of the list
     (3000, 60000, "missed", "missed"),       # a row that no sampled edge enters: sorted in memory
     (4194304, 9000, "hub", "tail"),          # the most nodes of the bucket path
-    (2000, 2700001, "uniform", "uniform"),   # more edges than the buckets hold: sorts
+    (2000, 2621440, "uniform", "hub"),       # the most edges that the buckets hold
+    (2000, 2621441, "uniform", "hub"),       # one more: sorts, 32-bit keys
+    (2000, 2700001, "uniform", "uniform"),
+    (70001, 2700001, "uniform", "uniform"),  # 64-bit keys
+    (4194305, 4000, "uniform", "uniform"),   # more nodes than the buckets hold: sorts, 64-bit keys
 ]
 
 
