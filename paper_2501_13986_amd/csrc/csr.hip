@@ -49,12 +49,13 @@ __global__ void k_lower_bounds(const K* __restrict__ keys, int64_t E, int64_t V,
   ptr[j] = lo;
 }
 
+// senders from the sorted keys recv * V + send (not from the list: an out-of-range edge is (0, 0))
 template <class K>
-__global__ void k_col_from_perm(const int64_t* __restrict__ send, const int64_t* __restrict__ perm, int64_t E,
-                                int64_t* __restrict__ col, K* __restrict__ colkey, int64_t* __restrict__ pos) {
+__global__ void k_col_from_keys(const K* __restrict__ keys, int64_t E, int64_t V, int64_t* __restrict__ col, K* __restrict__ colkey,
+                                int64_t* __restrict__ pos) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= E) return;
-  int64_t c = send[perm[e]];
+  int64_t c = (int64_t)((uint64_t)keys[e] % (uint64_t)V);
   col[e] = c;
   colkey[e] = (K)c;
   pos[e] = e;
@@ -858,7 +859,7 @@ hipError_t csr_build(const int64_t* recv, const int64_t* send, int64_t E, int64_
   hipLaunchKernelGGL(k_lower_bounds<K>, dim3(blocks_for(V + 1)), dim3(kBlock), 0, st, (const K*)keys_out, E, V, (uint64_t)V, row_ptr);
   CSR_TRY(hipGetLastError());
   // col, and the keys of the transpose: CSR positions stably sorted by sender
-  hipLaunchKernelGGL(k_col_from_perm<K>, dim3(blocks_for(E)), dim3(kBlock), 0, st, send, (const int64_t*)perm, E, col, keys_in, vals_in);
+  hipLaunchKernelGGL(k_col_from_keys<K>, dim3(blocks_for(E)), dim3(kBlock), 0, st, (const K*)keys_out, E, V, col, keys_in, vals_in);
   CSR_TRY(hipGetLastError());
   if (transpose) {
     tmp_bytes = L.tmp;

@@ -82,10 +82,10 @@ def test_csr_paths_bit_exact(V, E, recv_how, send_how):
     assert torch.all(out[3] == -5) and torch.all(out[4] == -5)
 
 
-@pytest.mark.parametrize("V,E", [(50, 900), (900, 30000)])
+@pytest.mark.parametrize("V,E", [(50, 900), (900, 30000), (4194305, 4000)])
 @pytest.mark.parametrize("value", [-1, "V", 2 ** 40])
 def test_csr_flags_out_of_range_indices_as_edge_zero_zero(V, E, value):
-    """In both of the paths that do not sort; such an edge is treated as (0, 0)."""
+    """In every path; such an edge is treated as (0, 0)."""
     from paper_2501_13986_amd import binding as b
     value = V if value == "V" else value
     print(f"V={V} E={E} index={value}", flush=True)
