@@ -114,9 +114,12 @@ constexpr int kBuckets = 1024;     // of consecutive rows
 constexpr int kPer = 4;            // records of a thread
 constexpr int kCap = kThreads * kPer;
 constexpr int kRows = 4096;        // rows of a bucket
-// Edges of a thread in the counting and distributing passes: 800 000 edges 8 + 13 us with eight, 10 + 9 with four, 15 + 9 with two.
+// Edges of a thread in the counting and distributing passes, up to a million edges: 800 000 edges 8 + 13 us with eight, 10 + 9
+// with four, 15 + 9 with two.  Above it twice as many (kBigTiles), because the tables grow with the tiles: a call with
+// 2 600 000 edges 142 us with eight and 161 with four.
 constexpr int kTilePer = 4;
 constexpr int kTile = kThreads * kTilePer;
+constexpr int64_t kBigTiles = (int64_t)1 << 20;
 constexpr int kSamples = kCap;     // edges that are looked at for buckets that do not fit
 constexpr int kCutsPer = 3;        // buckets after the cuts, per thread
 constexpr int kCuts = kThreads * kCutsPer;   // kBuckets + kSamples / 2: a cut keeps at least two samples
@@ -128,6 +131,7 @@ constexpr int kLongWork = 1 << 19;
 
 struct BucketPlan {
   int shift, nb, eb, vb;   // bucket of a row = row >> shift; number of buckets; bits of an edge index and of a node index
+  int tile;                // edges of a workgroup in the counting and distributing passes
   int samples, heavy, cut;   // edges in the sample; samples of a bucket that is cut; samples per piece
 };
 
@@ -159,7 +163,7 @@ struct BucketWs {
   __host__ __device__ BucketInfo* info() const { return (BucketInfo*)at; }
   __host__ __device__ BucketSide side(int i) const { return {at + kSides + i * BucketSide::kBytes}; }   // 0 receivers, 1 senders
   __host__ __device__ int* cursor2() const { return (int*)(at + kCursor); }
-  __host__ __device__ int* before() const { return (int*)(at + kBefore); }    // [tiles][kCuts]
+  __host__ __device__ int* before() const { return (int*)(at + kBefore); }    // [tiles][kCuts], laid out for the small tiles
   __host__ __device__ static size_t rec1_at(int64_t E) { return kBefore + (size_t)((E + kTile - 1) / kTile) * (kCuts * 4); }
   __host__ __device__ static size_t rec2_at(int64_t E) { return rec1_at(E) + apart((size_t)E * 8); }
   __host__ __device__ uint64_t* rec1(int64_t E) const { return (uint64_t*)(at + rec1_at(E)); }
@@ -381,8 +385,8 @@ struct EdgeRun {
   int64_t end[kPer];
 };
 
-// Workgroup 0: receivers, 1: senders.  Clears the side's totals, counts the buckets of a sample of the edges (eight
-// neighbours from each of 512 equal parts) and cuts the buckets with too many at samples of theirs.
+// Workgroup 0: receivers, 1: senders.  Clears the side's totals, counts the buckets of a sample of the edges (four
+// neighbours from each of 1 024 equal parts) and cuts the buckets with too many at samples of theirs.
 __global__ void __launch_bounds__(kThreads) k_csr_cut(const int64_t* __restrict__ recv, const int64_t* __restrict__ send, int64_t E,
                                                       int64_t V, BucketPlan B, BucketWs w, int* __restrict__ bad) {
   __shared__ SortLds S;
@@ -398,14 +402,14 @@ __global__ void __launch_bounds__(kThreads) k_csr_cut(const int64_t* __restrict_
   hist[t] = 0;
   if (t == 0) S.any = 0;
   __syncthreads();
-  // this thread's sample: kPer edges in a row, two threads to a run of kRun (whole cache lines mostly: 4 096 single edges made
-  // this kernel 6.6 us on 800 000 edges, runs of four 4.0, of eight 3.4)
-  constexpr int kRun = 2 * kPer, kRuns = kSamples / kRun;
+  // this thread's sample: kPer edges in a row (4 096 single edges made this kernel 6.6 us on 800 000 edges, runs of four 4.0).
+  // Somewhere in the first half of the run's part of the list: in a list in the order of the keys the pieces between two runs
+  // are then at most one and a half parts long, and fit.
   auto place = [&](int i) -> int64_t {   // the edge that is sample i: ascending
     if (E <= kSamples) return i;
-    const int run = i / kRun;
-    const int64_t lo = run * E / kRuns, room = (run + 1) * E / kRuns - lo - (kRun - 1);
-    return lo + (int64_t)((((uint64_t)((unsigned)run * 2654435761u)) * (uint64_t)room) >> 32) + i % kRun;
+    const int run = i / kPer;
+    const int64_t lo = run * E / kThreads, room = ((run + 1) * E / kThreads - lo - kPer) / 2 + 1;
+    return lo + (int64_t)((((uint64_t)((unsigned)run * 2654435761u)) * (uint64_t)room) >> 32) + i % kPer;
   };
   const int64_t at = place(t * kPer);
   uint64_t row[kPer];
@@ -506,11 +510,11 @@ __global__ void __launch_bounds__(kThreads) k_csr_count(const int64_t* __restric
 #pragma unroll
   for (int i = t; i < kCuts; i += kThreads) h1[i] = h2[i] = 0;
   __syncthreads();
-  const int64_t e0 = (int64_t)blockIdx.x * kTile + t;
+  const int64_t e0 = (int64_t)blockIdx.x * B.tile + t, e_end = e0 - t + B.tile < E ? e0 - t + B.tile : E;
   if (__builtin_expect(!cut1 && !cut2, 1)) {
 #pragma unroll
-    for (int j = 0; j < kTilePer; ++j)
-      if (e0 + j * kThreads < E) {
+    for (int j = 0; j < 2 * kTilePer; ++j)
+      if (e0 + j * kThreads < e_end) {
         uint64_t r, s;
         (void)load_edge(recv, send, e0 + j * kThreads, V, r, s);
         atomicAdd(&h1[(int)(r >> B.shift)], 1);
@@ -518,7 +522,7 @@ __global__ void __launch_bounds__(kThreads) k_csr_count(const int64_t* __restric
       }
   } else {
 #pragma unroll 1
-    for (int64_t e = e0; e < E && e < e0 + kTile; e += kThreads) {
+    for (int64_t e = e0; e < e_end; e += kThreads) {
       uint64_t r1, s1;
       (void)load_edge(recv, send, e, V, r1, s1);
       const int b1 = (int)(r1 >> B.shift), b2 = (int)(s1 >> B.shift);
@@ -568,20 +572,20 @@ __global__ void __launch_bounds__(kThreads) k_csr_distribute(const int64_t* __re
   if (t == 0 && (second || blockIdx.x == 0)) side.base()[n] = (int)E;
   if (second) return;
   __syncthreads();
-  const int64_t e0 = (int64_t)blockIdx.x * kTile + t;
+  const int64_t e0 = (int64_t)blockIdx.x * B.tile + t, e_end = e0 - t + B.tile < E ? e0 - t + B.tile : E;
   if (__builtin_expect(!cut, 1)) {
 #pragma unroll
-    for (int j = 0; j < kTilePer; ++j) {
+    for (int j = 0; j < 2 * kTilePer; ++j) {
       const int64_t e = e0 + j * kThreads;
       uint64_t r, s;
-      if (e < E) {
+      if (e < e_end) {
         if (!load_edge(recv, send, e, V, r, s)) *bad = 1;
         w.rec1(E)[atomicAdd(&dst[(int)(r >> B.shift)], 1)] = edge_key(B, r, s, (uint64_t)e);
       }
     }
   } else {
 #pragma unroll 1
-    for (int64_t e = e0; e < E && e < e0 + kTile; e += kThreads) {
+    for (int64_t e = e0; e < e_end; e += kThreads) {
       uint64_t r1, s1;
       if (!load_edge(recv, send, e, V, r1, s1)) *bad = 1;
       const uint64_t key = edge_key(B, r1, s1, (uint64_t)e);
@@ -875,8 +879,10 @@ enum class CsrPath { kSmall, kBuckets, kSort };
 // One workgroup where rows and edges fit its LDS; buckets up to 2 560 edges for each of 1 024 (4 096 fit, so rows may
 // be uneven): as many buckets as leave each 512 edges (5 000 nodes of degree 32: 56 us a call, with 256 edges 69, with
 // 1 300 57), but no more than the chip holds at once, two workgroups a CU (20 000 nodes of degree 40: 313 buckets 81 us,
-// 625 buckets 87); with fewer rows than that, as many buckets as there are rows, and cuts.  Larger graphs take the sorts.
-constexpr int64_t kMostEdges = (int64_t)2560 * kBuckets, kMostNodes = (int64_t)kBuckets * kRows;
+// 625 buckets 87).  With fewer rows than that most buckets are cut; up to two million edges this is faster than the sorts (300
+// nodes, a million edges 200 us against 415; 20 000 nodes, 1.7 million 192 against 291), at 2.6 million it is not (1 000 nodes 407
+// against 332).  Larger graphs take the sorts.
+constexpr int64_t kMostEdges = (int64_t)2560 * kBuckets, kMostNodes = (int64_t)kBuckets * kRows, kMostCrowded = (int64_t)1 << 21;
 
 CsrPath csr_path(int64_t E, int64_t V, BucketPlan& B) {
   B.eb = (int)bits_for((uint64_t)(E > 1 ? E - 1 : 1));
@@ -884,13 +890,8 @@ CsrPath csr_path(int64_t E, int64_t V, BucketPlan& B) {
   if (E <= kCap && V <= kRows) return CsrPath::kSmall;
   if (E > kMostEdges || V > kMostNodes) return CsrPath::kSort;
   const int64_t least = 512, most = 2560, at_once = 512;
-  // A bucket is cut if its samples speak for more than fits: 3 500 records, or `most` and five standard deviations of the
-  // sample's count, whichever is more (buckets of `most` would be cut for nothing otherwise).  Pieces of about 1 536 records,
-  // but not of a single sample.
   B.samples = (int)std::min<int64_t>(E, kSamples);
-  const double share = (double)B.samples / (double)E;
-  B.heavy = (int)std::ceil(std::max(3500 * share, most * share + 5 * std::sqrt(most * share)));
-  B.cut = std::max(2, (int)(1536 * share));
+  B.tile = E > kBigTiles ? 2 * kTile : kTile;
   B.shift = 0;
   auto buckets = [&](int shift) { return (V + ((int64_t)1 << shift) - 1) >> shift; };
   while (buckets(B.shift) > kBuckets) ++B.shift;
@@ -899,6 +900,14 @@ CsrPath csr_path(int64_t E, int64_t V, BucketPlan& B) {
     if (half == nb || E > most * half || (E >= least * nb && nb <= at_once)) break;
   }
   B.nb = (int)buckets(B.shift);
+  if (E > kMostCrowded && E > most * B.nb) return CsrPath::kSort;
+  // A bucket is cut if its samples speak for more than fits: 3 500 records, or `most` and five standard deviations of the
+  // sample's count, whichever is more (buckets of `most` would be cut for nothing otherwise).  Where few rows leave more than
+  // `most` to the average bucket, every one of about 1 024 is cut.  Pieces of about 1 536 records, but not of a single sample.
+  const double share = (double)B.samples / (double)E;
+  B.heavy = E > most * B.nb ? std::max(2, (int)(1024 * share))
+                            : (int)std::ceil(std::max(3500 * share, most * share + 5 * std::sqrt(most * share)));
+  B.cut = std::max(2, (int)(1536 * share));
   return CsrPath::kBuckets;
 }
 
@@ -906,7 +915,7 @@ hipError_t csr_buckets(const int64_t* recv, const int64_t* send, int64_t E, int6
                        int64_t* t_row_ptr, int64_t* t_perm, char* block, const BucketPlan& B, int* bad_flag, hipStream_t st) {
   const BucketWs w{block};
   int* bad = bad_flag ? bad_flag : (int*)(block + BucketWs::bytes(E) - 256);
-  const int transpose = t_row_ptr != nullptr, tiles = (int)((E + kTile - 1) / kTile);
+  const int transpose = t_row_ptr != nullptr, tiles = (int)((E + B.tile - 1) / B.tile);
   const int groups = B.nb + B.samples / B.cut;   // a bucket with c samples has at most 1 + c / cut pieces
   hipLaunchKernelGGL(k_csr_cut, dim3(1 + transpose), dim3(kThreads), 0, st, recv, send, E, V, B, w, bad);
   hipLaunchKernelGGL(k_csr_count, dim3(tiles), dim3(kThreads), 0, st, recv, send, E, V, B, w, transpose);
@@ -919,15 +928,14 @@ hipError_t csr_buckets(const int64_t* recv, const int64_t* send, int64_t E, int6
 }  // namespace
 
 // Grows with E and with V, so that one buffer serves every smaller graph: nothing where one workgroup does it, what E makes of
-// the buckets' tables up to the largest graph that they take, and beyond that at least as much as there.
+// the buckets' tables as long as they take any number of rows, and beyond that at least as much as the sorts need too.
 hipError_t csr_workspace_bytes(int64_t E, int64_t V, size_t* bytes) {
   *bytes = 256;
   if (E <= 0) return hipSuccess;
   BucketPlan B;
-  const CsrPath path = csr_path(E, V, B);
-  if (path == CsrPath::kSmall) return hipSuccess;
+  if (csr_path(E, V, B) == CsrPath::kSmall) return hipSuccess;
   *bytes = BucketWs::bytes(std::min(E, kMostEdges));
-  if (path == CsrPath::kBuckets) return hipSuccess;
+  if (E <= kMostCrowded && V <= kMostNodes) return hipSuccess;
   CsrLayout L;
   CSR_TRY(csr_layout(E, V, L));
   *bytes = std::max(*bytes, L.total);

@@ -129,12 +129,12 @@ int main(int argc, char** argv) {
       if (!strcmp(how, "tail") && e >= E - E / 9) a[e] = V - 1;  // fewer of them
       if (!strcmp(how, "two") && e % 2) a[e] = e % 4 == 1 ? 0 : V - 1;
       if (!strcmp(how, "missed")) {                              // a row that no sampled edge enters
-        int64_t t = e * 512 / E;
-        while (t + 1 < 512 && (t + 1) * E / 512 <= e) ++t;
-        while (t * E / 512 > e) --t;
-        const int64_t lo = t * E / 512, room = (t + 1) * E / 512 - lo - 7;
+        int64_t t = e * 1024 / E;
+        while (t + 1 < 1024 && (t + 1) * E / 1024 <= e) ++t;
+        while (t * E / 1024 > e) --t;
+        const int64_t lo = t * E / 1024, room = ((t + 1) * E / 1024 - lo - 4) / 2 + 1;
         const int64_t hit = lo + (int64_t)((((uint64_t)((unsigned)t * 2654435761u)) * (uint64_t)room) >> 32);
-        if ((e < hit || e > hit + 7) && e % 3) a[e] = V / 2;
+        if ((e < hit || e > hit + 3) && e % 3) a[e] = V / 2;
       }
       if (!strcmp(how, "bad") && e % 97 == 5) a[e] = e % 2 ? -1 : V;
     }
@@ -150,12 +150,12 @@ int main(int argc, char** argv) {
     run_grid(1, [&] { k_csr_small(recv.data(), send.data(), (int)E, (int)V, B.eb, B.vb, rp.data(), col.data(), perm.data(), trp.data(), tp.data(), &bad); });
   } else if (path == CsrPath::kBuckets) {
     // one block as large as the path says, with the space between its tables poisoned
-    const int64_t tiles = (E + kTile - 1) / kTile;
+    const int64_t tiles = (E + B.tile - 1) / B.tile, rows = (E + kTile - 1) / kTile;
     const size_t bytes = BucketWs::bytes(E);
     char* const block = (char*)aligned_alloc(256, (bytes + 255) / 256 * 256);
     memset(block, 0x5a, bytes);
     const BucketWs w{block};
-    std::vector<std::pair<char*, size_t>> tables = {{block, sizeof(BucketInfo)}, {(char*)w.cursor2(), kCuts * 4}, {(char*)w.before(), tiles * kCuts * 4}, {(char*)w.rec1(E), E * 8}, {(char*)w.rec2(E), E * 8}};
+    std::vector<std::pair<char*, size_t>> tables = {{block, sizeof(BucketInfo)}, {(char*)w.cursor2(), kCuts * 4}, {(char*)w.before(), rows * kCuts * 4}, {(char*)w.rec1(E), E * 8}, {(char*)w.rec2(E), E * 8}};
     for (int s = 0; s < 2; ++s) {
       const BucketSide d = w.side(s);
       for (auto t : std::vector<std::pair<char*, size_t>>{{(char*)d.first(), (kBuckets + 1) * 4}, {(char*)d.owner(), kCuts * 4},

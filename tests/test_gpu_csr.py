@@ -27,12 +27,14 @@ CASES = [  # V, E, receivers, senders
     (20000, 800000, "sorted", "uniform"),
     (2, 4500, "one", "uniform"),             # a bucket of one row, cut into pieces
     (2, 4500, "one", "one"),                 # of equal edges
+    (60000, 2600000, "tail", "sorted"),      # the largest tiles; pieces between neighbouring samples
     (20000, 900000, "tail", "tail"),         # padding: equal edges at the end of the list
     (3000, 60000, "missed", "missed"),       # a row that no sampled edge enters: sorted in memory
     (4194304, 9000, "hub", "tail"),          # the most nodes of the bucket path
-    (2000, 2621440, "uniform", "hub"),       # the most edges that the buckets hold
-    (2000, 2621441, "uniform", "hub"),       # one more: sorts, 32-bit keys
-    (2000, 2700001, "uniform", "uniform"),
+    (1000, 2097152, "uniform", "hub"),       # the most edges that buckets of any number of rows take
+    (1000, 2097153, "uniform", "hub"),       # one more on few rows: sorts, 32-bit keys
+    (65536, 2621440, "tail", "uniform"),     # the most edges that the buckets take at all
+    (2000, 2700001, "uniform", "uniform"),   # more: sorts
     (70001, 2700001, "uniform", "uniform"),  # 64-bit keys
     (4194305, 4000, "uniform", "uniform"),   # more nodes than the buckets hold: sorts, 64-bit keys
 ]
@@ -50,12 +52,12 @@ def nodes(rng, V, E, how):
         a[:] = V - 1
     elif how == "tail":
         a[E - E // 9:] = V - 1
-    elif how == "missed":                            # the sample: eight neighbours from each of 512 equal parts
-        run = np.arange(512, dtype=np.int64)
-        lo, hi = run * E // 512, (run + 1) * E // 512
-        first = lo + ((((run * 2654435761) % 2 ** 32) * (hi - lo - 7)) >> 32)
+    elif how == "missed":                            # the sample: four neighbours from each of 1 024 equal parts
+        run = np.arange(1024, dtype=np.int64)
+        lo, hi = run * E // 1024, (run + 1) * E // 1024
+        first = lo + ((((run * 2654435761) % 2 ** 32) * ((hi - lo - 4) // 2 + 1)) >> 32)
         looked_at = np.zeros(E, bool)
-        looked_at[(first[:, None] + np.arange(8)).ravel()] = True
+        looked_at[(first[:, None] + np.arange(4)).ravel()] = True
         a[~looked_at & (np.arange(E) % 3 != 0)] = V // 2
     return a.astype(np.int64)
 
@@ -105,3 +107,16 @@ def test_csr_flags_out_of_range_indices_as_edge_zero_zero(V, E, value):
         recv[e] = send[e] = 0
     for n, g, r in zip(("row_ptr", "col", "perm", "t_row_ptr", "t_perm"), out, oconv.csr_from_coo(recv, send, V)):
         assert np.array_equal(g.cpu().numpy(), r), n
+
+
+def test_csr_workspace_grows_beyond_the_buckets():
+    from paper_2501_13986_amd import binding as b
+    edges = [4096, 100000, 2097152, 2097153, 2400000, 2621440, 2621441, 3000000, 8000001]
+    nodes = [1, 1000, 4096, 4097, 20000, 65536, 65537, 4194304, 4194305, 6000000]
+    size = [[b.cgtp_csr_workspace_bytes(E, V) for V in nodes] for E in edges]
+    print(size)
+    for i, row in enumerate(size):
+        assert row == sorted(row), (edges[i], row)
+    for j in range(len(nodes)):
+        col = [row[j] for row in size]
+        assert col == sorted(col), (nodes[j], col)
