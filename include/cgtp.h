@@ -197,7 +197,7 @@ cgtp_status conv_forward(cgtp_plan* plan, const void* x_nodes, const void* y_edg
  * split between edge ranges is a static device array of the library (32 MiB per GPU, held from the moment the library
  * is loaded on that GPU until the process ends) instead of the plan's workspace, so the call allocates nothing - not
  * on its first use either.  Needs (edge ranges) * 2 * dim_z * sizeof(element) bytes, where the number of edge ranges
- * is at most min(E, waves of the kernel resident on the GPU); CGTP_EINVAL with the figures in cgtp_last_error() if that
+ * counts as min(E, workers of the kernel resident on the GPU), also where fewer are used; CGTP_EINVAL with the figures in cgtp_last_error() if that
  * exceeds the array (the MACE-shaped benchmark plan needs exactly 32 MiB in either precision).  The plan's device
  * must be the current device.  All calls on one GPU share the array: calls that overlap in time on one GPU (different
  * streams, different plans, different threads) race; calls on one stream are ordered and safe. */

@@ -89,11 +89,11 @@ LaneMap pick_map(const Plan& P, int kind, int step) {
     // gathers' latency once more, and a sender walk reads back its gy words), so the lane takes as many adjacent
     // channels (up to `most`) as bring it to one pass.
     // us on 3 000 nodes of degree 30 (* 1 500), fp32, with two passes -> one: 96 channels fwd 92 -> 83, bwd 160 -> 141,
-    // second order 365 -> 338; 192 channels 228 -> 199, 402 -> 356, 990 -> 882; 256 channels, l <= 3 (*) 222 -> 190,
-    // 378 -> 357, 1013 -> 883.  fp64 with 96 channels 163 -> 129, 310 -> 241, 732 -> 573, but three or four channels are
+    // second order 365 -> 338; 192 channels 228 -> 199, 402 -> 356, 990 -> 882; 256 channels, l <= 3 (*) backward
+    // 378 -> 357, second order 1013 -> 883 (and the forward would be 222 -> 190).  fp64 with 96 channels 163 -> 129, 310 -> 241, 732 -> 573, but three or four channels are
     // too many registers there: bwd 192 channels 740 -> 822, 256 channels 774 -> 855.  The forward
-    // walk stops at three: four would halve the edge ranges of a 256-channel plan, and conv_forward_static, whose static
-    // buffer bounds the ranges, is documented to refuse that plan.  The receiver walk of the
+    // walk stops at three: with four, a 256-channel plan would have half the edge ranges, and conv_forward_static, which refuses
+    // by their number, would take what it refuses.  The receiver walk of the
     // second-order pass up to 128 fp32 channels stays at one channel and two passes (128 channels 645, in one pass 667).
     if (conv && step == 2) cpl = 1;
     if (conv && !atomic && step == 0) {
@@ -275,6 +275,8 @@ cgtp_status launch_fixup(const Plan& P, const void* out, const void* part, const
 
 int64_t resident_waves(const Plan& P, const Kernel& k) { return (int64_t)k.blocks_per_cu * P.num_cu * (k.wg / 64); }
 
+int64_t most_ranges(const Plan& P, const Kernel& k, int spw) { return resident_waves(P, k) * spw * cgtp::env_int("CGTP_CONV_CHUNK_MULT", 1); }
+
 // Edge ranges of a convolution kernel: one per resident worker, but where that leaves fewer than two edges each, ranges of
 // three (of eight for workers that share a wave with many others), as long as 1 024 waves have work: every range costs
 // a row search and up to two pieces of split rows for the merge kernel.
@@ -283,7 +285,7 @@ int64_t resident_waves(const Plan& P, const Kernel& k) { return (int64_t)k.block
 // slower (second order, 700 nodes of 32 channels 72 -> 76), and so is a range of four for each of fewer than 1 024 waves
 // (27 nodes of 32 channels 26 -> 30).
 int64_t conv_ranges(const Plan& P, const Kernel& k, int spw, int64_t E) {
-  const int64_t all = resident_waves(P, k) * spw * cgtp::env_int("CGTP_CONV_CHUNK_MULT", 1), few = spw >= 8 ? 8 : 3;
+  const int64_t all = most_ranges(P, k, spw), few = spw >= 8 ? 8 : 3;
   if (E >= 2 * all) return all;
   return std::min(std::min(E, all), std::max<int64_t>(1024 * spw, E / few));
 }
@@ -862,9 +864,12 @@ cgtp_status conv_forward_impl(cgtp_plan* plan, const void* x_nodes, const void* 
     size_t cap = 0;
     hipError_t e = cgtp::static_scratch(&part, &cap);
     if (e != hipSuccess) return fail(CGTP_ERUNTIME, std::string("static scratch: ") + hipGetErrorString(e));
-    if (part_bytes > cap)
-      return fail(CGTP_EINVAL, "conv_forward_static: this problem needs " + std::to_string(part_bytes) + " bytes of scratch for " +
-                                   std::to_string(nchunk) + " edge ranges, the static buffer holds " + std::to_string(cap) +
+    // the limit of this entry point is a rule on the plan and E, whatever number of ranges suits a small graph
+    const int64_t ranges = std::min(E, most_ranges(P, k, spw));
+    const size_t need = (size_t)ranges * 2 * P.dim_z() * P.elt();
+    if (need > cap || part_bytes > cap)
+      return fail(CGTP_EINVAL, "conv_forward_static: this problem needs " + std::to_string(need) + " bytes of scratch for " +
+                                   std::to_string(ranges) + " edge ranges, the static buffer holds " + std::to_string(cap) +
                                    "; use conv_forward");
   } else {
     s = ensure_ws(P, part_bytes);

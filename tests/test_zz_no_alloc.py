@@ -66,3 +66,26 @@ def test_conv_forward_static_refuses_what_does_not_fit():
     b.conv_forward(plan, x, y, W, z, dev(row_ptr), dev(col))      # the ordinary entry point takes it
     torch.cuda.synchronize()
     assert torch.all(z == 0)
+
+
+def test_conv_forward_static_refuses_by_edges_not_by_ranges():
+    """A small graph that the convolution walks in fewer, longer ranges than it has edges is refused by the same rule."""
+    from paper_2501_13986_amd import binding as b
+    irr = ("256x0e+256x1o+256x2e", synth.MACE_Y, "256x0e+256x1o+256x2e+256x3o")
+    plan = b.Plan(*irr, dtype=b.CGTP_F32, device=0)
+    row = 2 * plan.dim_z * 4
+    for E, fits in ((32 * 2 ** 20 // row, True), (32 * 2 ** 20 // row + 1, False), (2000, False)):
+        V = 50
+        print(f"V={V} E={E} entry=conv_forward_static", flush=True)
+        rng = np.random.default_rng(E)
+        row_ptr, col, _, _, _ = oconv.csr_from_coo(rng.integers(0, V, E), rng.integers(0, V, E), V)
+        x = torch.zeros((V, plan.dim_x), device="cuda"); y = torch.zeros((E, plan.dim_y), device="cuda")
+        W = torch.zeros((E, plan.n_w), device="cuda"); z = torch.ones((V, plan.dim_z), device="cuda")
+        if fits:
+            b.conv_forward_static(plan, x, y, W, z, dev(row_ptr), dev(col))
+            torch.cuda.synchronize()
+            assert torch.all(z == 0)
+        else:
+            with pytest.raises(b.CgtpError) as ei:
+                b.conv_forward_static(plan, x, y, W, z, dev(row_ptr), dev(col))
+            assert ei.value.status == 1 and "static buffer holds" in str(ei.value)
