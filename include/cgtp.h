@@ -137,10 +137,12 @@ cgtp_status cgtp_plan_get_path(const cgtp_plan* plan, int32_t p, cgtp_path* path
  * alpha.  Writes at most `cap` entries to each non-NULL array, returns the total count. */
 int32_t cgtp_plan_path_nonzeros(const cgtp_plan* plan, int32_t p, int32_t cap, int32_t* i, int32_t* j,
                                 int32_t* k, double* v);
-/* Nonzero-FLOP model per row (sample or edge): which 0 = forward, 1 = backward, 2 = second-order pass.  Forward counts 2 per nonzero per channel plus the weight multiply; backward 3x the
- * contraction + 1.5x the weight part (2x for uvw plans, whose backward is two GEMMs of the forward's size); the
- * second-order pass 8x the contraction + 3x the weight part (the seven separate dispatches of the paper would be
- * 3 forward + 4 backward = 15x + 9x; a count of the products as Sec. 3.4 lists them, the kernels share more: 5x); for uvw plans with per-sample weights 7x + 5x (seven dispatches: 15x + 11x). */
+/* Nonzero-FLOP model per row (sample or edge): which 0 = forward, 1 = backward, 2 = second-order pass.  Forward
+ * counts 2 per nonzero per channel plus the weight multiply; backward 3x the contraction + 1.5x the weight part (2x
+ * for uvw plans, whose backward is two GEMMs of the forward's size); the second-order pass 8x the contraction + 3x the
+ * weight part (the seven separate dispatches of the paper would be 3 forward + 4 backward = 15x + 9x; 8x counts the
+ * products as Sec. 3.4 lists them, the kernels share more and need 5x); for uvw plans with per-sample weights 7x + 5x
+ * (seven dispatches: 15x + 11x). */
 int64_t cgtp_plan_flops(const cgtp_plan* plan, int32_t which);
 /* Generated HIP source of a kernel (NUL-terminated, owned by the plan), or NULL. */
 const char* cgtp_plan_source(const cgtp_plan* plan, int32_t kernel);

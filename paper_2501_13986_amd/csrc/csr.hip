@@ -104,11 +104,11 @@ __device__ __forceinline__ void here_scalar(T v) { asm volatile("" ::"s"(v)); }
 // one workgroup with most of the graph: a sample of the edges finds the buckets that do not fit, and these are cut
 // further at keys of the sample, so that every workgroup has about the same to do whatever the degrees are.
 // What is left is the latency of dependent passes.  Synchronous call, sorts -> buckets: 27 nodes of degree 9 80 -> 28 us,
-// 300 nodes of degree 20 120 -> 45, 3 001 nodes of degree 32 178 -> 50, 20 000 nodes of degree 40 425 -> 78 us (kernels
-// 3 + 10 + 9 + 21 + 14); conv_forward_perm + conv_backward_perm with the preparation, 3 001 nodes of 32 channels 343 -> 222 us.
-// With a node connected to all others, sorts -> without cuts -> with them: 3 002 nodes 181 -> 542 -> 90 us, 20 001 nodes 422 ->
-// 618 -> 151; 100 000 equal edges at the end of 900 000 417 -> 3 322 -> 167; half of 800 000 edges in one row 404 -> 9 093 -> 169,
-// all of a million 396 -> 22 775 -> 207; degrees of a power law 411 -> 4 573 -> 231.
+// 300 nodes of degree 20 120 -> 45, 3 001 nodes of degree 32 178 -> 50, 20 000 nodes of degree 40 425 -> 80 us (kernels
+// 4 + 10 + 9 + 21 + 14); conv_forward_perm + conv_backward_perm with the preparation, 3 001 nodes of 32 channels 343 -> 221 us.
+// With a node connected to all others, sorts -> without cuts -> with them: 3 002 nodes 181 -> 542 -> 90 to 102 us, 20 001
+// nodes 422 -> 618 -> 154; 100 000 equal edges at the end of 900 000 417 -> 3 322 -> 164; half of 800 000 edges in one row 404 ->
+// 9 093 -> 170, all of a million 396 -> 22 775 -> 207; degrees of a power law 411 -> 4 573 -> 229.
 constexpr int kThreads = 1024;     // of every kernel of this path; one thread per bucket of rows in the scans
 constexpr int kBuckets = 1024;     // of consecutive rows
 constexpr int kPer = 4;            // records of a thread
