@@ -532,12 +532,19 @@ cgtp_status cgtp_plan_create_ex(const char* irreps_x, const char* irreps_y, cons
       Kernel& kf = P.k[CGTP_K_TP_FWD];
       cgtp::emit_uvw_forward(P, kf);
       if (device != -1) {
-        cgtp::jit_compile(kf, -2);
+        auto compile = [](Kernel& k) {
+          try {
+            cgtp::jit_compile(k, -2);
+          } catch (const std::exception& e) {
+            throw CompileError{e.what()};
+          }
+        };
+        compile(kf);
         if (kf.scratch > 0) {
           Kernel other;
           other.sched.x_form = 0;
           cgtp::emit_uvw_forward(P, other);
-          cgtp::jit_compile(other, -2);
+          compile(other);
           if (other.scratch < kf.scratch) kf = std::move(other);
         }
       }
