@@ -242,6 +242,58 @@ void build_kernel(cgtp::Plan& P, int kind, Emit emit, int device) {
   K = std::move(best);
 }
 
+// The kernels that walk row by row: with the schedule of the range kernels, or the one that needs the fewest registers; not
+// where that too needs private memory or fails the check of the compiled code, and not for plans of many paths.
+void build_rows(Plan& P, int device) {
+  if (P.paths.size() > kFewPaths || !cgtp::env_int("CGTP_CONV_ROWS", 1)) return;
+  for (int back = 0; back < 2; ++back) {
+    const LaneMap& m = P.map[back ? CGTP_K_CONV_BWD : CGTP_K_CONV_FWD];
+    cgtp::Schedule frugal;
+    frugal.w_upfront = frugal.upfront = 0;
+    frugal.pin = 2;
+    frugal.fresh_y = 1;
+    cgtp::Schedule first = P.k[back ? CGTP_K_CONV_BWD : CGTP_K_CONV_FWD].sched;
+    if (back) first.upfront = 1;
+    auto compiled = [&](Kernel& k, bool nt, int waves) {
+      if (!cgtp::emit_uvu_conv_row(P, back != 0, nt, waves, k)) return false;
+      try {
+        cgtp::jit_compile(k, device == -1 ? -1 : -2);
+      } catch (const cgtp::RefusedCode&) {
+        return false;
+      } catch (const std::exception& e) {
+        throw CompileError{e.what()};
+      }
+      return k.scratch == 0;
+    };
+    // Workers of a row (us per call, 128 channels unless given): eight, on eight waves; four waves where the registers leave
+    // room for one workgroup of eight (forward fp64, 5 000 nodes of degree 32, 617 -> 594).  For long streams fewer, so that
+    // more rows are in flight: four workers where they share waves (32 channels, 20 000 nodes of degree 9, forward 116 -> 102),
+    // four waves in the backward (96 channels, 20 000 of degree 32, 895 -> 841), half of that for kernels of more than 128
+    // registers whose workers share waves (32 channels fp64, 20 000 of degree 32, 1444 -> 1329).
+    for (const cgtp::Schedule& s : {first, frugal}) {
+      Kernel plain, nt;
+      const int full = std::max(1, 8 / m.spw), many = back ? 168 : 128;
+      auto attempt = [&](Kernel& k, bool stream, int waves) {
+        k = Kernel();
+        k.sched = s;
+        return compiled(k, stream, waves);
+      };
+      bool ok = attempt(plain, false, full);
+      if (full > 4 && (!ok || plain.vgprs > many)) ok = attempt(plain, false, 4);
+      // a backward with more registers is no faster than the ranges (128 channels fp64, 100 nodes of degree 32: 44 -> 55)
+      if (!ok || (back && plain.vgprs > 200)) continue;
+      int waves = plain.wg / 64;
+      if (m.spw > 1) waves = std::max(1, 4 / m.spw);
+      else if (back) waves = std::min(waves, 4);
+      if (back && m.spw > 1 && plain.vgprs > 128) waves = std::max(1, waves / 2);
+      if (!attempt(nt, true, waves)) continue;
+      P.k_row[back][0] = std::move(plain);
+      P.k_row[back][1] = std::move(nt);
+      break;
+    }
+  }
+}
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 cgtp_status launch(const Kernel& k, unsigned grid, void** args, hipStream_t st) {
@@ -288,6 +340,30 @@ int64_t conv_ranges(const Plan& P, const Kernel& k, int spw, int64_t E) {
   const int64_t all = most_ranges(P, k, spw), few = spw >= 8 ? 8 : 3;
   if (E >= 2 * all) return all;
   return std::min(std::min(E, all), std::max<int64_t>(1024 * spw, E / few));
+}
+
+// Rows of more than 2^lg edges are cut into windows of that size: 16 edges for each worker, and no more than 1 024 windows.
+constexpr int64_t kRowWindows = 1024;
+int row_lg(const Kernel& k, const LaneMap& m, int64_t E) {
+  int lg = 0;
+  while (((int64_t)1 << lg) < 16LL * (k.wg / 64) * m.spw || (E - 1) >> lg >= kRowWindows) ++lg;
+  return lg;
+}
+
+// The kernel that walks a graph row by row, or NULL if the edge ranges do.  Non-temporal streams where the weights do not
+// fit the Infinity Cache (128 channels, 300 nodes of degree 32, forward 25 us without the hint and 27 with it; 5 000 nodes 308
+// and 300).  The forward has gained at every size measured; the backward, whose weights come in the order of the senders, does
+// for short streams (one launch instead of three) and long ones (more even work); between them the last workgroups
+// leave the machine idle (128 channels, 1 000 nodes of degree 32, 140 us by ranges, 154 by rows; with more than 128 registers, so
+// one workgroup of eight waves a CU, already at 300 of degree 36, 60 and 62).  Where several workers' weights share a cache line
+// it always does (4 channels, 20 000 nodes of degree 32, 178 -> 97).
+const Kernel* conv_by_rows(const Plan& P, bool backward, int64_t E) {
+  const LaneMap& m = P.map[backward ? CGTP_K_CONV_BWD : CGTP_K_CONV_FWD];
+  const int64_t stream = E * P.n_w * (int64_t)P.elt(), mb = (int64_t)1 << 20;
+  const bool wide = m.G * m.cpl * (int64_t)P.elt() >= 128;
+  const Kernel& k = P.k_row[backward][stream > 256 * mb];
+  if (backward && wide && stream > (P.k_row[1][0].vgprs > 128 ? 72 : 96) * mb && stream <= 700 * mb) return nullptr;
+  return k.fn ? &k : nullptr;
 }
 
 // 64 words of pinned host memory, one per cache line, handed out to concurrent calls; allocated on first use and kept
@@ -500,6 +576,7 @@ cgtp_status cgtp_plan_create_ex(const char* irreps_x, const char* irreps_y, cons
       build_conv(CGTP_K_CONV_DBL_FWD, [&](Kernel& k) { cgtp::emit_uvu_conv_double(P, false, k); });
       build_conv(CGTP_K_CONV_DBL_BWD, [&](Kernel& k) { cgtp::emit_uvu_conv_double(P, true, k); });
       cgtp::emit_fixup(P, P.k_fix);
+      build_rows(P, device);
     } else if (!P.shared_w) {
       cgtp::emit_uvw_ps_forward(P, P.k[CGTP_K_TP_FWD]);
       cgtp::emit_uvw_ps_backward(P, P.k[CGTP_K_TP_BWD]);
@@ -571,10 +648,24 @@ cgtp_status cgtp_plan_create_ex(const char* irreps_x, const char* irreps_y, cons
   try {
     for (auto& k : P.k) cgtp::jit_compile(k, device);
     cgtp::jit_compile(P.k_fix, device);
+    for (auto& both : P.k_row)
+      for (auto& k : both) cgtp::jit_compile(k, device);
   } catch (const std::exception& e) {
     for (auto& k : P.k) cgtp::jit_unload(k);
     cgtp::jit_unload(P.k_fix);
+    for (auto& both : P.k_row)
+      for (auto& k : both) cgtp::jit_unload(k);
     return fail(CGTP_ECOMPILE, e.what());
+  }
+  if (P.k_row[0][0].fn || P.k_row[1][0].fn) {
+    const size_t n = kRowWindows * sizeof(int);
+    hipError_t e = hipMalloc((void**)&P.row_cnt, n);
+    if (e == hipSuccess) e = hipMemset(P.row_cnt, 0, n);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e != hipSuccess) {
+      cgtp_plan_destroy(H.release());
+      return fail(CGTP_ENOMEM, std::string("counters of the row kernels: ") + hipGetErrorString(e));
+    }
   }
   *out = H.release();
   return CGTP_OK;
@@ -584,6 +675,9 @@ cgtp_status cgtp_plan_destroy(cgtp_plan* plan) {
   if (!plan) return CGTP_OK;
   for (auto& k : plan->P.k) cgtp::jit_unload(k);
   cgtp::jit_unload(plan->P.k_fix);
+  for (auto& both : plan->P.k_row)
+    for (auto& k : both) cgtp::jit_unload(k);
+  if (plan->P.row_cnt) (void)hipFree(plan->P.row_cnt);
   if (plan->P.ws) (void)hipFree(plan->P.ws);
   delete plan;
   return CGTP_OK;
@@ -860,7 +954,9 @@ cgtp_status conv_forward_impl(cgtp_plan* plan, const void* x_nodes, const void* 
   const Kernel& k = P.k[CGTP_K_CONV_FWD];
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_FWD].spw;   // edge-range workers per wave
-  int64_t nchunk = conv_ranges(P, k, spw, E);
+  const Kernel* rows = conv_by_rows(P, false, E);
+  const int lg = rows ? row_lg(*rows, P.map[CGTP_K_CONV_FWD], E) : 0;
+  int64_t nchunk = rows ? ((E - 1) >> lg) + 1 : conv_ranges(P, k, spw, E);
   size_t part_bytes = (size_t)nchunk * 2 * P.dim_z() * P.elt();
   void* part = nullptr;
   cgtp_status s = CGTP_OK;
@@ -882,6 +978,11 @@ cgtp_status conv_forward_impl(cgtp_plan* plan, const void* x_nodes, const void* 
     s = ensure_ws(P, part_bytes);
     if (s != CGTP_OK) return s;
     part = P.ws;
+  }
+  if (rows) {
+    void* args[] = {(void*)&x_nodes, (void*)&y_edges, (void*)&W_edges,   (void*)&z_nodes, (void*)&row_ptr, (void*)&col,
+                    (void*)&V,       (void*)&part,    (void*)&P.row_cnt, (void*)&lg,      (void*)&edge_perm};
+    return launch(*rows, (unsigned)(V + nchunk - 1), args, st);
   }
   const int wpw = k.wg / 64;
   unsigned grid = (unsigned)((nchunk + (int64_t)wpw * spw - 1) / ((int64_t)wpw * spw));
@@ -938,6 +1039,20 @@ cgtp_status conv_backward_perm(cgtp_plan* plan, const void* x_nodes, const void*
   const Kernel& k = P.k[CGTP_K_CONV_BWD];
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_BWD].spw;   // edge-range workers per wave
+  if (const Kernel* rows = conv_by_rows(P, true, E)) {
+    const int lg = row_lg(*rows, P.map[CGTP_K_CONV_BWD], E);
+    const int64_t windows = ((E - 1) >> lg) + 1;
+    const size_t part_bytes = round_up((size_t)windows * 2 * P.dim_x() * P.elt(), 256);
+    const bool lookup = V > cgtp::kConvRowLookup || E > INT32_MAX;   // (2 000 nodes: 30 us either way)
+    const cgtp_status s = ensure_ws(P, part_bytes + (lookup ? (size_t)E * 8 : 0));
+    if (s != CGTP_OK) return s;
+    int64_t* t_recv = lookup ? (int64_t*)((char*)P.ws + part_bytes) : nullptr;
+    if (lookup) HIP_TRY(cgtp::launch_recv_of_tperm(row_ptr, t_perm, V, E, t_recv, st));
+    void* args[] = {(void*)&x_nodes,  (void*)&y_edges,   (void*)&W_edges, (void*)&gz_nodes,  (void*)&gx_nodes, (void*)&gy_edges,
+                    (void*)&gW_edges, (void*)&t_row_ptr, (void*)&t_perm,  (void*)&row_ptr,   (void*)&t_recv,   (void*)&V,
+                    (void*)&P.ws,     (void*)&P.row_cnt, (void*)&lg,      (void*)&edge_perm};
+    return launch(*rows, (unsigned)(V + windows - 1), args, st);
+  }
   int64_t nchunk = conv_ranges(P, k, spw, E);
   size_t part_bytes = round_up((size_t)nchunk * 2 * P.dim_x() * P.elt(), 256);
   const size_t recv_bytes = round_up((size_t)E * 8, 256);

@@ -1646,6 +1646,135 @@ void emit_uvu_backward(const Plan& P, bool conv, Kernel& K) {
   K.screen_divergence = true;
 }
 
+// ---------------------------------------------------------------------------------------
+// Convolution with one workgroup per row: the workers of a workgroup share the edges of one row, their sums meet in LDS and
+// the workgroup stores the row.  Against the walks over edge ranges:
+//  - nothing is left to merge, so a call is one launch (the walks: main kernel, merge of the split rows), and the backward of
+//    a graph of few rows looks its receivers up by itself, in a copy of row_ptr in LDS;
+//  - workgroups start in order, so the machine reads one window of the weights that moves through memory instead of two
+//    thousand places far apart (giving each XCD an eighth of the rows loses it again: 128 channels, 5 000 nodes, 310 -> 408 us).
+// A row of more than 2^lg edges (a hub) is cut at the multiples of 2^lg: further workgroups, one per multiple, take a window
+// each if it lies inside such a row; its pieces go to `part` (window h: [2h] the piece that began earlier, [2h + 1] the one
+// that begins there) and the workgroup that finishes last, by a counter that it clears again, adds them in order.
+// us per call, ranges -> rows.  Forward, 128 fp32 channels: 27 nodes of degree 9 12 -> 8, 300 of degree 32 35 -> 25, 5 000 of
+// degree 32 335 -> 300 (4.9 TB/s of algorithmic bytes), 20 000 of degree 36 1434 -> 1336; 32 channels, 10 007 nodes of degree 36
+// 203 -> 188; 4 channels, 20 000 of degree 32 91 -> 20.  Backward: 32 channels, 300 nodes of degree 9 19 -> 12, 20 000 of degree
+// 36 812 -> 768; 128 channels, 27 nodes 15 -> 13, 20 000 of degree 36 2786 -> 2714.
+bool emit_uvu_conv_row(const Plan& P, bool backward, bool nt, int waves, Kernel& K) {
+  const LaneMap& M = P.map[backward ? CGTP_K_CONV_BWD : CGTP_K_CONV_FWD];
+  // one pass and one phase (a worker keeps the whole row), plain sums
+  if (M.npass > 1 || K.sched.phases > 1 || P.kahan_conv) return false;
+  const int NWK = waves * M.spw;
+  K.wg = 64 * waves;
+  const int D = (int)(backward ? P.dim_x() : P.dim_z());
+  if ((int64_t)NWK * D * (int)P.elt() + (backward ? 4 * (kConvRowLookup + 1) + 12 * K.wg : 0) + 64 > 160 * 1024) return false;
+  K.name = backward ? "cgtp_conv_bwd_row" : "cgtp_conv_fwd_row";
+  Em E(P, M, K.sched);
+  E.preamble();
+  E.emit_row_of();
+  const int DX = (int)P.dim_x(), DY = (int)P.dim_y(), DZ = (int)P.dim_z();
+  const i64 NW = P.n_w;
+  auto& o = E.o;
+  const char* ptr = backward ? "t_row_ptr" : "row_ptr";
+  o << "extern \"C\" __global__ void __launch_bounds__(" << K.wg << ") " << occ_attr(M, K.sched) << K.name
+    << "(const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ W, ";
+  if (backward)
+    o << "const T* __restrict__ gz, T* __restrict__ out, T* __restrict__ gy, T* __restrict__ gW,\n"
+         "   const i64* __restrict__ t_row_ptr, const i64* __restrict__ t_perm, const i64* __restrict__ row_ptr, const i64* __restrict__ t_recv,";
+  else
+    o << "T* __restrict__ out,\n   const i64* __restrict__ row_ptr, const i64* __restrict__ col,";
+  o << " i64 V, T* part, int* cnt, int lg, const i64* __restrict__ eperm)\n{\n";
+  o << "  __shared__ __attribute__((aligned(16))) T red[" << (int64_t)NWK * D << "];\n";
+  if (backward) o << "  __shared__ int rp[" << kConvRowLookup + 1 << "], lj[" << K.wg << "];\n  __shared__ i64 le[" << K.wg << "];\n";
+  o << "  __shared__ int before;\n";
+  o << "  const int t = threadIdx.x, lane = t & 63;\n  int vz = 0; asm volatile(\"\" : \"+v\"(vz));\n  const int g_ = lane & " << M.G - 1 << ";\n";
+  if (M.spw == 1) o << "  const int wk = __builtin_amdgcn_readfirstlane(t >> 6);\n";
+  else o << "  const int wk = (t >> 6) * " << M.spw << " + lane / " << M.G << ";\n";
+  // the workgroup's row and its edges [lo, hi) of it
+  o << "  i64 r = blockIdx.x, lo, hi, rb, re, slot;\n";
+  o << "  if (r < V) {\n    rb = " << ptr << "[r]; re = " << ptr << "[r + 1]; lo = rb; hi = re; slot = 2 * (rb >> lg) + 1;\n"
+       "    if (re - rb > ((i64)1 << lg)) hi = ((rb >> lg) + 1) << lg;\n"
+       "  } else {\n    const i64 h = r - V + 1;\n    lo = h << lg; slot = 2 * h;\n"
+       "    r = row_of(" << ptr << ", V, lo); rb = " << ptr << "[r]; re = " << ptr << "[r + 1];\n"
+       "    if (re - rb <= ((i64)1 << lg) || rb >= lo) return;\n"
+       "    hi = re < lo + ((i64)1 << lg) ? re : lo + ((i64)1 << lg);\n  }\n";
+  o << "  const bool hub = re - rb > ((i64)1 << lg);\n";
+  o << "  const int n = (int)(hi - lo);\n  const int u0 = g_ * " << M.cpl << ", pass = 0;\n  (void)pass;\n";
+  E.dup = M.spw == 1;
+  E.stream_nt = nt && E.stream_hint();
+  E.pin_accumulators = backward;
+  std::string used;
+  if (backward) {
+    o << "  const T* xb = x + r * " << DX << ";\n";
+    E.load_x("xb", "  ");
+    // sender position q -> edge e = t_perm[q]; its receiver comes from t_recv or is the last row that begins at or before e
+    E.gy_lane_consts("  ");
+    E.declare_gx("  ");
+    o << "  if (n > 0 && !t_recv)\n"
+         "    for (int i = 0; i <= (int)V; i += " << K.wg << ") { const int v_ = i + t < (int)V ? i + t : (int)V; rp[v_] = (int)row_ptr[v_]; }\n";
+    o << "  #pragma unroll 1\n  for (int at = 0; at < n; at += " << K.wg << ") {\n"
+         "    const int m = n - at < " << K.wg << " ? n - at : " << K.wg << ", q_ = t < m ? t : m - 1;\n"
+         "    const i64 e_ = t_perm[lo + at + q_];\n    int j_;\n    __syncthreads();\n"
+         "    if (t_recv) {\n      j_ = (int)t_recv[lo + at + q_];\n    } else {\n"
+         "      int top = 1;\n      while (top < (int)V) top <<= 1;\n      j_ = 0;\n"
+         "      for (; top > 0; top >>= 1) { const int c_ = j_ + top; j_ = c_ < (int)V && rp[c_ < (int)V ? c_ : 0] <= (int)e_ ? c_ : j_; }\n    }\n"
+         "    lj[q_] = j_; le[q_] = eperm ? eperm[e_] : e_;\n    __syncthreads();\n"
+         "    const int each = (m + " << NWK - 1 << ") / " << NWK << ", s0 = wk * each, s1 = s0 + each < m ? s0 + each : m;\n";
+    if (M.spw == 1) o << "    #pragma unroll 1\n";
+    o << "    for (int s_ = s0; s_ < s1; ++s_) {\n";
+    if (M.spw == 1)
+      o << "      const i64 j = __builtin_amdgcn_readfirstlane(lj[s_]);\n"
+           "      const i64 e = (i64)(((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(le[s_] >> 32)) << 32) | (unsigned)__builtin_amdgcn_readfirstlane((int)le[s_]));\n";
+    else o << "      const i64 j = lj[s_], e = le[s_];\n";
+    o << "      const T* yb = y + e * " << DY << "; const T* wb = W + e * " << NW << "; const T* gzb = gz + j * " << DZ << ";\n"
+         "      T* gyb = gy + e * " << DY << "; T* gwb = gW + e * " << NW << ";\n";
+    E.load_y("yb", "      ");
+    E.declare_gy("      ", true);
+    E.gy_reduce_decls("      ");
+    E.backward_paths("wb", "gzb", "gwb", "      ");
+    E.reduce_store_gy("gyb", "      ");
+    o << "    }\n  }\n";
+  } else {
+    E.declare_z("  ");
+    o << "  const int each = (n + " << NWK - 1 << ") / " << NWK << ", s0 = wk * each, s1 = s0 + each < n ? s0 + each : n;\n";
+    if (M.spw == 1) o << "  #pragma unroll 1\n";
+    o << "  for (int s_ = s0; s_ < s1; ++s_) {\n"
+         "    const i64 e = lo + s_, c = col[e], er_ = eperm ? eperm[e] : e;\n"
+         "    const T* xb = x + c * " << DX << "; const T* yb = y + er_ * " << DY << "; const T* wb = W + er_ * " << NW << ";\n";
+    E.load_y("yb", "    ");
+    E.load_x("xb", "    ");
+    E.forward_paths("wb", "    ");
+    o << "  }\n";
+  }
+  // the workers that had an edge, and their sums in their order; the row's last words are added by several threads alike
+  o << "  const int m0 = n < " << K.wg << " ? n : " << K.wg << ", each0 = " << (backward ? "(m0" : "(n") << " + " << NWK - 1 << ") / " << NWK << ";\n"
+       "  const int used = each0 > 0 ? (" << (backward ? "m0" : "n") << " + each0 - 1) / each0 : 0;\n";
+  o << "  if (wk < used) { T* dst_ = red + wk * " << D << ";\n";
+  if (backward) E.store_gx("dst_", "    ");
+  else E.store_z("dst_", "    ");
+  o << "  }\n  __syncthreads();\n";
+  o << "  T* dst = hub ? part + slot * " << D << " : out + r * " << D << ";\n";
+  const int per = (D + K.wg - 1) / K.wg;
+  o << "  {\n    T s_[" << per << "]; int i_[" << per << "];\n    #pragma unroll\n    for (int k = 0; k < " << per << "; ++k) { i_[k] = k * " << K.wg
+    << " + t < " << D << " ? k * " << K.wg << " + t : " << D - 1 << "; s_[k] = (T)0; }\n"
+       "    #pragma unroll 4\n    for (int w = 0; w < used; ++w) {\n      #pragma unroll\n      for (int k = 0; k < " << per << "; ++k) s_[k] += red[w * " << D << " + i_[k]];\n    }\n"
+       "    #pragma unroll\n    for (int k = 0; k < " << per << "; ++k) dst[i_[k]] = s_[k];\n  }\n";
+  o << "  if (!hub) return;\n"
+       "  __builtin_amdgcn_fence(__ATOMIC_RELEASE, \"agent\");\n  __syncthreads();\n"
+       "  const i64 h0 = rb >> lg, pieces = ((re - 1) >> lg) - h0 + 1;\n"
+       "  if (t == 0) before = __hip_atomic_fetch_add(cnt + h0, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);\n"
+       "  __syncthreads();\n"
+       "  if (__builtin_amdgcn_readfirstlane(before) != (int)pieces - 1) return;\n"
+       "  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, \"agent\");\n";
+  o << "  #pragma unroll 1\n  for (int k = 0; k < " << per << "; ++k) {\n    const int i_ = k * " << K.wg << " + t < " << D << " ? k * " << K.wg << " + t : " << D - 1
+    << ";\n    T s_ = part[(2 * h0 + 1) * " << D << " + i_];\n    #pragma unroll 8\n    for (i64 h = h0 + 1; h < h0 + pieces; ++h) s_ += part[2 * h * " << D << " + i_];\n"
+       "    out[r * " << D << " + i_] = s_;\n  }\n"
+       "  if (t == 0) __hip_atomic_store(cnt + h0, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n}\n";
+  K.source = o.str();
+  K.screen_divergence = true;
+  return true;
+}
+
 // Nondeterministic convolution for unsorted edge lists (paper Sec. 3.5, the variant "omitted for
 // brevity"): one tensor product per edge as in the batched kernels, x gathered by sender, and the
 // result added to the receiver's row with one atomic per word; needs neither sorted edges nor the

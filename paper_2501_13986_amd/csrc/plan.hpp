@@ -99,6 +99,8 @@ struct Plan {
   int num_cu = 256;
   LaneMap map[9];  // indexed by cgtp_kernel
   Kernel k[9];  // indexed by cgtp_kernel
+  Kernel k_row[2][2];       // convolution with a workgroup per row: [forward, backward][plain, non-temporal streams] (no source: not for this plan)
+  int* row_cnt = nullptr;   // their counters of finished pieces, one per window; zero between calls
   Kernel k_fix;  // merges split rows after the conv kernels (uvu) / adds per-wave gW partial sums (uvw)
   // workspace for split-row partial sums and per-edge receiver ids (conv)
   void* ws = nullptr;
@@ -121,6 +123,10 @@ void emit_uvw_forward(const Plan& P, Kernel& out);
 void emit_uvw_backward(const Plan& P, Kernel& out, Kernel& reduce);
 int64_t uvw_tile_samples(const Plan& P);  // samples handled by one workgroup of the uvw kernel
 void emit_fixup(const Plan& P, Kernel& out);
+// Convolution with one workgroup of `waves` waves per row.  nt: the per-edge streams are marked non-temporal.  false: this
+// plan has no such kernel.
+bool emit_uvu_conv_row(const Plan& P, bool backward, bool nt, int waves, Kernel& out);
+constexpr int kConvRowLookup = 2048;   // rows whose row_ptr the backward keeps in LDS
 // uvw with per-sample weights (emit_uvw_ps.cpp): one wave per sample, VALU, fp32 and fp64
 void emit_uvw_ps_forward(const Plan& P, Kernel& out);
 void emit_uvw_ps_backward(const Plan& P, Kernel& out);

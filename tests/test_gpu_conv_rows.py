@@ -1,0 +1,84 @@
+"""The convolution of small graphs, one workgroup per row: rows cut at the windows of a piece (just below, at and above a
+piece, over many windows, two of them meeting in one window), no edge, one edge, the largest graph of the rule and one row
+more.  And the walks over edge ranges on the small graphs that the other tests take through the row kernels."""
+import numpy as np
+import pytest
+
+from oracle import conv as oconv
+from oracle.irreps import TPSpec
+from paper_2501_13986_amd import synth
+from tests._util import assert_close, memo
+from tests.test_gpu_conv import GRAPHS, SPECS, dev
+from tests.test_gpu_conv_shapes import check
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SPECS.update({
+    "mul8": ("8x0e+8x1o", "1x0e+1x1o", "8x0e+8x1o+8x1e"),
+    "mul20": ("20x0e+7x4e+12x1o", "1x0e+1x2e", "20x0e+3x7o+12x1o"),      # unequal: lanes beyond a multiplicity; segments of no path
+    "mul32": ("32x0e+32x1o", "1x0e+1x1o+1x2e", "32x0e+32x1o+32x2e"),
+})
+# degrees of the rows, receivers and senders alike: pieces are of 32 to 512 edges
+DEGREES = {
+    "around_a_piece": [0, 127, 128, 129, 0, 1, 255, 256, 257, 3, 511, 512, 513, 0],
+    "hubs": [5, 1500, 2, 0, 700, 130, 131, 9, 2600],
+    "no_edge_but_one": [0, 0, 1, 0],
+}
+
+
+def graph(name, seed=7):
+    deg = DEGREES[name]
+    recv = np.repeat(np.arange(len(deg)), deg)
+    rng = np.random.default_rng(seed)
+    return rng.permutation(recv).astype(np.int64), rng.permutation(recv).astype(np.int64), len(deg)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("name", list(DEGREES))
+@pytest.mark.parametrize("spec_name", ["small", "odd_row", "mul1", "mul8", "mul20", "mul32", "mul75", "mul96", "mace"])
+def test_rows_of_every_length(spec_name, name, prec):
+    from paper_2501_13986_amd import binding as b
+    if spec_name == "mace" and name == "hubs":
+        pytest.skip("the oracle takes minutes")
+    spec = TPSpec(*SPECS[spec_name])
+    plan = b.Plan(*SPECS[spec_name], dtype=b.CGTP_F64 if prec == "f64" else b.CGTP_F32, device=0)
+    recv, send, V = graph(name)
+    E = recv.shape[0]
+    print(f"spec={spec_name} graph={name} prec={prec} V={V} E={E}", flush=True)
+    row_ptr, col, perm, t_row_ptr, t_perm = oconv.csr_from_coo(recv, send, V)
+    npdt, tdt = (np.float64, torch.float64) if prec == "f64" else (np.float32, torch.float32)
+    x, gz = (synth.normal(i, (V, d)).astype(npdt) for i, d in ((1, spec.dim_x), (4, spec.dim_z)))
+    y, W = (synth.normal(i, (E, d)).astype(npdt) for i, d in ((2, spec.dim_y), (3, spec.n_w)))
+    new = lambda *shape: torch.full(shape, float("nan"), dtype=tdt, device="cuda")
+    g = [dev(a) for a in (row_ptr, col, t_row_ptr, t_perm)]
+    rz = memo(oconv.forward, spec, x, y, W, row_ptr, col)
+    rx, ry, rW = memo(oconv.backward, spec, x, y, W, gz, row_ptr, col)
+    back = np.empty_like(perm)      # the edge data in another order, reached through the permutation
+    back[perm] = np.arange(E)
+    for p in (None, dev(perm)):
+        for call in range(2):       # the second call finds the counters of the hubs as the first one left them
+            z, gx, gy, gW = new(V, spec.dim_z), new(V, spec.dim_x), new(E, spec.dim_y), new(E, spec.n_w)
+            ys, Ws = (dev(y), dev(W)) if p is None else (dev(y[back]), dev(W[back]))
+            if p is None:
+                b.conv_forward(plan, dev(x), ys, Ws, z, g[0], g[1])
+                b.conv_backward(plan, dev(x), ys, Ws, dev(gz), gx, gy, gW, *g)
+            else:
+                b.conv_forward_perm(plan, dev(x), ys, Ws, z, g[0], g[1], p)
+                b.conv_backward_perm(plan, dev(x), ys, Ws, dev(gz), gx, gy, gW, *g, p)
+            torch.cuda.synchronize()
+            assert_close(z.cpu().numpy(), rz, prec, "z")
+            assert_close(gx.cpu().numpy(), rx, prec, "gx")
+            assert_close(gy.cpu().numpy(), ry if p is None else ry[back], prec, "gy")
+            assert_close(gW.cpu().numpy(), rW if p is None else rW[back], prec, "gW")
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("name", list(GRAPHS))
+@pytest.mark.parametrize("spec_name", ["small", "mul32", "mul96", "mace"])
+def test_edge_ranges_of_small_graphs(spec_name, name, prec, monkeypatch):
+    if GRAPHS[name][1] > 3000:
+        pytest.skip("beyond the row kernels' rule in any case")
+    monkeypatch.setenv("CGTP_CONV_ROWS", "0")
+    check(spec_name, name, prec, double=False)
