@@ -242,6 +242,22 @@ void build_kernel(cgtp::Plan& P, int kind, Emit emit, int device) {
   K = std::move(best);
 }
 
+// false: the compiled code failed its check or needs private memory
+bool compiles_without_scratch(Kernel& k, int device) {
+  try {
+    cgtp::jit_compile(k, device == -1 ? -1 : -2);
+  } catch (const cgtp::RefusedCode&) {
+    return false;
+  } catch (const std::exception& e) {
+    throw CompileError{e.what()};
+  }
+  return k.scratch == 0;
+}
+
+std::vector<Kernel*> row_kernels(Plan& P) {
+  return {&P.k_row[0][0], &P.k_row[0][1], &P.k_row[1][0], &P.k_row[1][1], &P.k_dbl_row[0], &P.k_dbl_row[1], &P.k_dbl_row[2], &P.k_row_sums};
+}
+
 // The kernels that walk row by row: with the schedule of the range kernels, or the one that needs the fewest registers; not
 // where that too needs private memory or fails the check of the compiled code, and not for plans of many paths.
 void build_rows(Plan& P, int device) {
@@ -254,17 +270,7 @@ void build_rows(Plan& P, int device) {
     frugal.fresh_y = 1;
     cgtp::Schedule first = P.k[back ? CGTP_K_CONV_BWD : CGTP_K_CONV_FWD].sched;
     if (back) first.upfront = 1;
-    auto compiled = [&](Kernel& k, bool nt, int waves) {
-      if (!cgtp::emit_uvu_conv_row(P, back != 0, nt, waves, k)) return false;
-      try {
-        cgtp::jit_compile(k, device == -1 ? -1 : -2);
-      } catch (const cgtp::RefusedCode&) {
-        return false;
-      } catch (const std::exception& e) {
-        throw CompileError{e.what()};
-      }
-      return k.scratch == 0;
-    };
+    auto compiled = [&](Kernel& k, bool nt, int waves) { return cgtp::emit_uvu_conv_row(P, back != 0, nt, waves, k) && compiles_without_scratch(k, device); };
     // Workers of a row (us per call, 128 channels unless given): eight, on eight waves; four waves where the registers leave
     // room for one workgroup of eight (forward fp64, 5 000 nodes of degree 32, 617 -> 594).  For long streams fewer, so that
     // more rows are in flight: four workers where they share waves (32 channels, 20 000 nodes of degree 9, forward 116 -> 102),
@@ -292,6 +298,22 @@ void build_rows(Plan& P, int device) {
       break;
     }
   }
+}
+
+// The second-order pass in one walk: eight waves a row where there are few rows (32 channels, 300 nodes of degree 32, 66 us on
+// two waves and 38 on eight), four workers where there are many (2 000 nodes of degree 9, 56 and 68).
+void build_double_rows(Plan& P, int device) {
+  if (P.paths.size() > kFewPaths || !cgtp::env_int("CGTP_CONV_ROWS", 1)) return;
+  const int spw = P.map[CGTP_K_CONV_DBL_BWD].spw, many = std::max(1, 4 / spw), few = spw >= 16 ? 2 : 8;
+  Kernel k[3], sums;
+  for (int t = 0; t < 3; ++t) {
+    k[t].sched = P.k[CGTP_K_CONV_DBL_BWD].sched;
+    if (!cgtp::emit_uvu_conv_double_row(P, t == 2, t == 0 ? few : many, k[t]) || !compiles_without_scratch(k[t], device)) return;
+  }
+  cgtp::emit_row_sums(P, sums);
+  if (!compiles_without_scratch(sums, device)) return;
+  for (int t = 0; t < 3; ++t) P.k_dbl_row[t] = std::move(k[t]);
+  P.k_row_sums = std::move(sums);
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -344,9 +366,9 @@ int64_t conv_ranges(const Plan& P, const Kernel& k, int spw, int64_t E) {
 
 // Rows of more than 2^lg edges are cut into windows of that size: 16 edges for each worker, and no more than 1 024 windows.
 constexpr int64_t kRowWindows = 1024;
-int row_lg(const Kernel& k, const LaneMap& m, int64_t E) {
+int row_lg(const Kernel& k, int spw, int64_t E) {
   int lg = 0;
-  while (((int64_t)1 << lg) < 16LL * (k.wg / 64) * m.spw || (E - 1) >> lg >= kRowWindows) ++lg;
+  while (((int64_t)1 << lg) < 16LL * (k.wg / 64) * spw || (E - 1) >> lg >= kRowWindows) ++lg;
   return lg;
 }
 
@@ -577,6 +599,7 @@ cgtp_status cgtp_plan_create_ex(const char* irreps_x, const char* irreps_y, cons
       build_conv(CGTP_K_CONV_DBL_BWD, [&](Kernel& k) { cgtp::emit_uvu_conv_double(P, true, k); });
       cgtp::emit_fixup(P, P.k_fix);
       build_rows(P, device);
+      build_double_rows(P, device);
     } else if (!P.shared_w) {
       cgtp::emit_uvw_ps_forward(P, P.k[CGTP_K_TP_FWD]);
       cgtp::emit_uvw_ps_backward(P, P.k[CGTP_K_TP_BWD]);
@@ -648,16 +671,14 @@ cgtp_status cgtp_plan_create_ex(const char* irreps_x, const char* irreps_y, cons
   try {
     for (auto& k : P.k) cgtp::jit_compile(k, device);
     cgtp::jit_compile(P.k_fix, device);
-    for (auto& both : P.k_row)
-      for (auto& k : both) cgtp::jit_compile(k, device);
+    for (Kernel* k : row_kernels(P)) cgtp::jit_compile(*k, device);
   } catch (const std::exception& e) {
     for (auto& k : P.k) cgtp::jit_unload(k);
     cgtp::jit_unload(P.k_fix);
-    for (auto& both : P.k_row)
-      for (auto& k : both) cgtp::jit_unload(k);
+    for (Kernel* k : row_kernels(P)) cgtp::jit_unload(*k);
     return fail(CGTP_ECOMPILE, e.what());
   }
-  if (P.k_row[0][0].fn || P.k_row[1][0].fn) {
+  if (P.k_row[0][0].fn || P.k_row[1][0].fn || P.k_dbl_row[0].fn) {
     const size_t n = kRowWindows * sizeof(int);
     hipError_t e = hipMalloc((void**)&P.row_cnt, n);
     if (e == hipSuccess) e = hipMemset(P.row_cnt, 0, n);
@@ -675,8 +696,7 @@ cgtp_status cgtp_plan_destroy(cgtp_plan* plan) {
   if (!plan) return CGTP_OK;
   for (auto& k : plan->P.k) cgtp::jit_unload(k);
   cgtp::jit_unload(plan->P.k_fix);
-  for (auto& both : plan->P.k_row)
-    for (auto& k : both) cgtp::jit_unload(k);
+  for (Kernel* k : row_kernels(plan->P)) cgtp::jit_unload(*k);
   if (plan->P.row_cnt) (void)hipFree(plan->P.row_cnt);
   if (plan->P.ws) (void)hipFree(plan->P.ws);
   delete plan;
@@ -955,7 +975,7 @@ cgtp_status conv_forward_impl(cgtp_plan* plan, const void* x_nodes, const void* 
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_FWD].spw;   // edge-range workers per wave
   const Kernel* rows = conv_by_rows(P, false, E);
-  const int lg = rows ? row_lg(*rows, P.map[CGTP_K_CONV_FWD], E) : 0;
+  const int lg = rows ? row_lg(*rows, P.map[CGTP_K_CONV_FWD].spw, E) : 0;
   int64_t nchunk = rows ? ((E - 1) >> lg) + 1 : conv_ranges(P, k, spw, E);
   size_t part_bytes = (size_t)nchunk * 2 * P.dim_z() * P.elt();
   void* part = nullptr;
@@ -1040,7 +1060,7 @@ cgtp_status conv_backward_perm(cgtp_plan* plan, const void* x_nodes, const void*
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_BWD].spw;   // edge-range workers per wave
   if (const Kernel* rows = conv_by_rows(P, true, E)) {
-    const int lg = row_lg(*rows, P.map[CGTP_K_CONV_BWD], E);
+    const int lg = row_lg(*rows, P.map[CGTP_K_CONV_BWD].spw, E);
     const int64_t windows = ((E - 1) >> lg) + 1;
     const size_t part_bytes = round_up((size_t)windows * 2 * P.dim_x() * P.elt(), 256);
     const bool lookup = V > cgtp::kConvRowLookup || E > INT32_MAX;   // (2 000 nodes: 30 us either way)
@@ -1101,6 +1121,27 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
   const Kernel& kf = P.k[CGTP_K_CONV_DBL_FWD];
   const Kernel& kb = P.k[CGTP_K_CONV_DBL_BWD];
   if (!kf.fn || !kb.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
+  // One walk, if the rows of dL/dx of all edges are no more than a gigabyte and there is memory for them; non-temporal where the
+  // three streams of weights do not fit the Infinity Cache (32 channels, 1 000 nodes of degree 32, 94 us without the hint and 103
+  // with it; 2 000 nodes 178 and 173).
+  const size_t el = P.elt(), row_bytes = round_up((size_t)E * P.dim_x() * el, 256);
+  if (P.k_dbl_row[0].fn && row_bytes <= (size_t)1 << 30) {
+    const Kernel& k = P.k_dbl_row[V <= 768 ? 0 : 3 * E * P.n_w * (int64_t)el > (int64_t)256 << 20 ? 2 : 1];
+    const int lg = row_lg(k, P.map[CGTP_K_CONV_DBL_BWD].spw, E), lg2 = row_lg(P.k_row_sums, 1, E);
+    const int64_t windows = ((E - 1) >> lg) + 1, windows2 = ((E - 1) >> lg2) + 1;
+    if (ensure_ws(P, row_bytes + 2 * el * (size_t)std::max(windows * P.dim_z(), windows2 * P.dim_x())) == CGTP_OK) {
+      void *edge_rows = P.ws, *pieces = (char*)P.ws + row_bytes;
+      void* args[] = {(void*)&x_nodes,   (void*)&y_edges,  (void*)&W_edges, (void*)&gz_nodes,  (void*)&La_nodes,  (void*)&Lb_edges,
+                      (void*)&LC_edges,  (void*)&edge_rows, (void*)&Ly_edges, (void*)&LW_edges, (void*)&Lgz_nodes, (void*)&row_ptr,
+                      (void*)&col,       (void*)&V,        (void*)&pieces,  (void*)&P.row_cnt, (void*)&lg};
+      cgtp_status s = launch(k, (unsigned)(V + windows - 1), args, st);
+      if (s != CGTP_OK) return s;
+      void* sum_args[] = {(void*)&edge_rows, (void*)&Lx_nodes, (void*)&t_row_ptr, (void*)&t_perm,
+                          (void*)&V,         (void*)&pieces,   (void*)&P.row_cnt, (void*)&lg2};
+      return launch(P.k_row_sums, (unsigned)(V + windows2 - 1), sum_args, st);
+    }
+    (void)hipGetLastError();
+  }
   const int spwf = P.map[CGTP_K_CONV_DBL_FWD].spw, spwb = P.map[CGTP_K_CONV_DBL_BWD].spw;
   int64_t nf = conv_ranges(P, kf, spwf, E);
   int64_t nb = conv_ranges(P, kb, spwb, E);

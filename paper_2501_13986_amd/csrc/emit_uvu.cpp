@@ -117,6 +117,7 @@ struct Em {
   // 30: 86 -> 74, 189 -> 172, second order 448 -> 350.  From 128 bytes on the hint pays (16 fp64 channels, backward 215 us
   // with it, 242 without; 32 fp32 channels 424 and 457).
   bool stream_hint() const { return env_int("CGTP_STREAM_NT", 1) != 0 && M.G * M.cpl * (int)P.elt() >= 128; }
+  bool resident = false;          // double backward: gz and dL/dgz of the row live outside the sweep (one workgroup per receiver row)
   bool emit_lz = true;            // double backward: also form dL/dgz (the convolution's sender walk leaves it out)
   bool accumulate_store = false;  // add to what memory holds (plain read-modify-write by the owning lane)
   std::set<int> written_z;        // double backward with phases: dL/dgz segments an earlier phase has stored
@@ -796,7 +797,7 @@ struct Em {
     auto close_group = [&]() {
       // with phases over the x segments, a dL/dgz segment receives contributions from several phases: the
       // first one to reach it stores, the later ones add to what is there (same lane, same addresses)
-      if (emit_lz) {
+      if (emit_lz && !resident) {
         accumulate_store = written_z.count(open_iz) > 0;
         store_z_seg(lgzb, (size_t)open_iz, ind, &Em::LZ);
         accumulate_store = false;
@@ -811,13 +812,13 @@ struct Em {
         if (open_iz >= 0) close_group();
         if (open_iz >= 0 && sched_barrier) o << ind0 << "__builtin_amdgcn_sched_barrier(0);\n";
         o << ind0 << "{ // output segment " << q.iz << "\n";
-        if (upfront < 2) load_gz_seg(gzb, q.iz, ind);
+        if (upfront < 2 && !resident) load_gz_seg(gzb, q.iz, ind);
         if (upfront < 1)
           for (size_t oj = oi; oj < order.size() && P.paths[order[oj]].iz == q.iz; ++oj) {
             load_w_path(wb, order[oj], ind);
             load_w_path(cwb, order[oj], ind, "c");
           }
-        if (emit_lz) declare(seg_names(&Em::LZ, q.iz, P.irz[q.iz].l), ind, true);
+        if (emit_lz && !resident) declare(seg_names(&Em::LZ, q.iz, P.irz[q.iz].l), ind, true);
         open_iz = q.iz;
       }
       o << ind << "{ // path " << p << ": l=(" << q.l1 << "," << q.l2 << "," << q.l3 << ") nnz=" << q.nz.size() << "\n";
@@ -917,7 +918,7 @@ struct Em {
     }
     if (open_iz >= 0) close_group();
     // segments of dL/dgz that no path touches are zero
-    for (size_t s = 0; emit_lz && s < P.irz.size(); ++s)
+    for (size_t s = 0; emit_lz && !resident && s < P.irz.size(); ++s)
       if (!used_z().count((int)s)) store_z_seg(lgzb, s, ind0, &Em::LZ);
   }
 
@@ -1646,6 +1647,45 @@ void emit_uvu_backward(const Plan& P, bool conv, Kernel& K) {
   K.screen_divergence = true;
 }
 
+// The workgroup's row r of `ptr`, its ends rb and re, and the edges [lo, hi) of it that this workgroup takes (n of them).
+// In scope: V, lg.
+static void row_of_workgroup(Em& E, const char* ptr) {
+  auto& o = E.o;
+  o << "  i64 r = blockIdx.x, lo, hi, rb, re, slot;\n";
+  o << "  if (r < V) {\n    rb = " << ptr << "[r]; re = " << ptr << "[r + 1]; lo = rb; hi = re; slot = 2 * (rb >> lg) + 1;\n"
+       "    if (re - rb > ((i64)1 << lg)) hi = ((rb >> lg) + 1) << lg;\n"
+       "  } else {\n    const i64 h = r - V + 1;\n    lo = h << lg; slot = 2 * h;\n"
+       "    r = row_of(" << ptr << ", V, lo); rb = " << ptr << "[r]; re = " << ptr << "[r + 1];\n"
+       "    if (re - rb <= ((i64)1 << lg) || rb >= lo) return;\n"
+       "    hi = re < lo + ((i64)1 << lg) ? re : lo + ((i64)1 << lg);\n  }\n";
+  o << "  const bool hub = re - rb > ((i64)1 << lg);\n";
+  o << "  const int n = (int)(hi - lo);\n";
+}
+
+// out[r] (or the piece of a hub in part) = the sum of the D-word rows of the first `used` workers in `red`, in their order; the
+// row's last words are added by several threads alike.  In scope: what row_of_workgroup defines, t, part, cnt, out, the shared
+// word `before`.
+static void sum_of_workers(Em& E, int D, int wg) {
+  auto& o = E.o;
+  o << "  T* dst = hub ? part + slot * " << D << " : out + r * " << D << ";\n";
+  const int per = (D + wg - 1) / wg;
+  o << "  {\n    T s_[" << per << "]; int i_[" << per << "];\n    #pragma unroll\n    for (int k = 0; k < " << per << "; ++k) { i_[k] = k * " << wg
+    << " + t < " << D << " ? k * " << wg << " + t : " << D - 1 << "; s_[k] = (T)0; }\n"
+       "    #pragma unroll 4\n    for (int w = 0; w < used; ++w) {\n      #pragma unroll\n      for (int k = 0; k < " << per << "; ++k) s_[k] += red[w * " << D << " + i_[k]];\n    }\n"
+       "    #pragma unroll\n    for (int k = 0; k < " << per << "; ++k) dst[i_[k]] = s_[k];\n  }\n";
+  o << "  if (!hub) return;\n"
+       "  __builtin_amdgcn_fence(__ATOMIC_RELEASE, \"agent\");\n  __syncthreads();\n"
+       "  const i64 h0 = rb >> lg, pieces = ((re - 1) >> lg) - h0 + 1;\n"
+       "  if (t == 0) before = __hip_atomic_fetch_add(cnt + h0, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);\n"
+       "  __syncthreads();\n"
+       "  if (__builtin_amdgcn_readfirstlane(before) != (int)pieces - 1) return;\n"
+       "  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, \"agent\");\n";
+  o << "  #pragma unroll 1\n  for (int k = 0; k < " << per << "; ++k) {\n    const int i_ = k * " << wg << " + t < " << D << " ? k * " << wg << " + t : " << D - 1
+    << ";\n    T s_ = part[(2 * h0 + 1) * " << D << " + i_];\n    #pragma unroll 8\n    for (i64 h = h0 + 1; h < h0 + pieces; ++h) s_ += part[2 * h * " << D << " + i_];\n"
+       "    out[r * " << D << " + i_] = s_;\n  }\n"
+       "  if (t == 0) __hip_atomic_store(cnt + h0, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n";
+}
+
 // ---------------------------------------------------------------------------------------
 // Convolution with one workgroup per row: the workers of a workgroup share the edges of one row, their sums meet in LDS and
 // the workgroup stores the row.  Against the walks over edge ranges:
@@ -1690,20 +1730,11 @@ bool emit_uvu_conv_row(const Plan& P, bool backward, bool nt, int waves, Kernel&
   o << "  const int t = threadIdx.x, lane = t & 63;\n  int vz = 0; asm volatile(\"\" : \"+v\"(vz));\n  const int g_ = lane & " << M.G - 1 << ";\n";
   if (M.spw == 1) o << "  const int wk = __builtin_amdgcn_readfirstlane(t >> 6);\n";
   else o << "  const int wk = (t >> 6) * " << M.spw << " + lane / " << M.G << ";\n";
-  // the workgroup's row and its edges [lo, hi) of it
-  o << "  i64 r = blockIdx.x, lo, hi, rb, re, slot;\n";
-  o << "  if (r < V) {\n    rb = " << ptr << "[r]; re = " << ptr << "[r + 1]; lo = rb; hi = re; slot = 2 * (rb >> lg) + 1;\n"
-       "    if (re - rb > ((i64)1 << lg)) hi = ((rb >> lg) + 1) << lg;\n"
-       "  } else {\n    const i64 h = r - V + 1;\n    lo = h << lg; slot = 2 * h;\n"
-       "    r = row_of(" << ptr << ", V, lo); rb = " << ptr << "[r]; re = " << ptr << "[r + 1];\n"
-       "    if (re - rb <= ((i64)1 << lg) || rb >= lo) return;\n"
-       "    hi = re < lo + ((i64)1 << lg) ? re : lo + ((i64)1 << lg);\n  }\n";
-  o << "  const bool hub = re - rb > ((i64)1 << lg);\n";
-  o << "  const int n = (int)(hi - lo);\n  const int u0 = g_ * " << M.cpl << ", pass = 0;\n  (void)pass;\n";
+  row_of_workgroup(E, ptr);
+  o << "  const int u0 = g_ * " << M.cpl << ", pass = 0;\n  (void)pass;\n";
   E.dup = M.spw == 1;
   E.stream_nt = nt && E.stream_hint();
   E.pin_accumulators = backward;
-  std::string used;
   if (backward) {
     o << "  const T* xb = x + r * " << DX << ";\n";
     E.load_x("xb", "  ");
@@ -1746,33 +1777,115 @@ bool emit_uvu_conv_row(const Plan& P, bool backward, bool nt, int waves, Kernel&
     E.forward_paths("wb", "    ");
     o << "  }\n";
   }
-  // the workers that had an edge, and their sums in their order; the row's last words are added by several threads alike
+  // the workers that had an edge
   o << "  const int m0 = n < " << K.wg << " ? n : " << K.wg << ", each0 = " << (backward ? "(m0" : "(n") << " + " << NWK - 1 << ") / " << NWK << ";\n"
        "  const int used = each0 > 0 ? (" << (backward ? "m0" : "n") << " + each0 - 1) / each0 : 0;\n";
   o << "  if (wk < used) { T* dst_ = red + wk * " << D << ";\n";
   if (backward) E.store_gx("dst_", "    ");
   else E.store_z("dst_", "    ");
   o << "  }\n  __syncthreads();\n";
-  o << "  T* dst = hub ? part + slot * " << D << " : out + r * " << D << ";\n";
-  const int per = (D + K.wg - 1) / K.wg;
-  o << "  {\n    T s_[" << per << "]; int i_[" << per << "];\n    #pragma unroll\n    for (int k = 0; k < " << per << "; ++k) { i_[k] = k * " << K.wg
-    << " + t < " << D << " ? k * " << K.wg << " + t : " << D - 1 << "; s_[k] = (T)0; }\n"
-       "    #pragma unroll 4\n    for (int w = 0; w < used; ++w) {\n      #pragma unroll\n      for (int k = 0; k < " << per << "; ++k) s_[k] += red[w * " << D << " + i_[k]];\n    }\n"
-       "    #pragma unroll\n    for (int k = 0; k < " << per << "; ++k) dst[i_[k]] = s_[k];\n  }\n";
-  o << "  if (!hub) return;\n"
-       "  __builtin_amdgcn_fence(__ATOMIC_RELEASE, \"agent\");\n  __syncthreads();\n"
-       "  const i64 h0 = rb >> lg, pieces = ((re - 1) >> lg) - h0 + 1;\n"
-       "  if (t == 0) before = __hip_atomic_fetch_add(cnt + h0, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);\n"
-       "  __syncthreads();\n"
-       "  if (__builtin_amdgcn_readfirstlane(before) != (int)pieces - 1) return;\n"
-       "  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, \"agent\");\n";
-  o << "  #pragma unroll 1\n  for (int k = 0; k < " << per << "; ++k) {\n    const int i_ = k * " << K.wg << " + t < " << D << " ? k * " << K.wg << " + t : " << D - 1
-    << ";\n    T s_ = part[(2 * h0 + 1) * " << D << " + i_];\n    #pragma unroll 8\n    for (i64 h = h0 + 1; h < h0 + pieces; ++h) s_ += part[2 * h * " << D << " + i_];\n"
-       "    out[r * " << D << " + i_] = s_;\n  }\n"
-       "  if (t == 0) __hip_atomic_store(cnt + h0, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n}\n";
+  sum_of_workers(E, D, K.wg);
+  o << "}\n";
   K.source = o.str();
   K.screen_divergence = true;
   return true;
+}
+
+// Second-order pass of the convolution in one walk over the receiver rows, a workgroup per row as above: gz and the dL/dgz
+// sums of the row stay in registers, x and abar are gathered, W and cbar are read once (the two walks of emit_uvu_conv_double
+// read them twice, 1.1 of 3.9 GB on 2 000 nodes of degree 32 with 128 channels), and dL/dx of every edge goes to a row of its
+// own in `rows`, which emit_row_sums adds by senders.
+// Bound by the bytes in flight (252 to 256 registers, two waves per SIMD; held to three, or with gz read again for every edge,
+// the code needs accumulation registers).  us per call, two walks -> this: 128 channels, 27 nodes of degree 9 27 -> 25, 300 of
+// degree 32 127 -> 116, 2 000 of degree 32 643 -> 542, 5 000 of degree 32 1536 -> 1354; 32 channels, 27 nodes 23 -> 12, 300 of degree 9
+// 38 -> 23, 5 000 of degree 32 454 -> 384.
+bool emit_uvu_conv_double_row(const Plan& P, bool nt, int waves, Kernel& K) {
+  const LaneMap& M = P.map[CGTP_K_CONV_DBL_BWD];
+  if (M.npass > 1 || K.sched.phases > 1 || P.kahan_conv) return false;
+  const int NWK = waves * M.spw, DX = (int)P.dim_x(), DY = (int)P.dim_y(), DZ = (int)P.dim_z();
+  const i64 NW = P.n_w;
+  K.wg = 64 * waves;
+  if ((int64_t)NWK * DZ * (int)P.elt() + 64 > 160 * 1024) return false;
+  K.name = "cgtp_conv_dbl_row";
+  Em E(P, M, K.sched);
+  E.preamble();
+  E.emit_row_of();
+  auto& o = E.o;
+  o << "extern \"C\" __global__ void __launch_bounds__(" << K.wg << ") " << occ_attr(M, K.sched) << K.name
+    << "(const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ W, const T* __restrict__ gz,\n"
+       "   const T* __restrict__ La, const T* __restrict__ Lb, const T* __restrict__ LC, T* __restrict__ rows, T* __restrict__ Ly, T* __restrict__ LW,\n"
+       "   T* __restrict__ out, const i64* __restrict__ row_ptr, const i64* __restrict__ col, i64 V, T* part, int* cnt, int lg)\n{\n";
+  o << "  __shared__ __attribute__((aligned(16))) T red[" << (int64_t)NWK * DZ << "];\n  __shared__ int before;\n";
+  o << "  const int t = threadIdx.x, lane = t & 63;\n  int vz = 0; asm volatile(\"\" : \"+v\"(vz));\n  const int g_ = lane & " << M.G - 1 << ";\n";
+  if (M.spw == 1) o << "  const int wk = __builtin_amdgcn_readfirstlane(t >> 6);\n";
+  else o << "  const int wk = (t >> 6) * " << M.spw << " + lane / " << M.G << ";\n";
+  row_of_workgroup(E, "row_ptr");
+  o << "  const int u0 = g_ * " << M.cpl << ", pass = 0;\n  (void)pass;\n";
+  E.dup = M.spw == 1;
+  E.stream_nt = nt && E.stream_hint();
+  E.resident = true;
+  E.gy_lane_consts("  ");
+  o << "  const T* gzb = gz + r * " << DZ << ";\n";
+  for (int sz : E.used_z()) {
+    E.load_gz_seg("gzb", sz, "  ");
+    E.declare(E.seg_names(&Em::LZ, sz, P.irz[sz].l), "  ", true);
+  }
+  o << "  const int each = (n + " << NWK - 1 << ") / " << NWK << ", s0 = wk * each, s1 = s0 + each < n ? s0 + each : n;\n";
+  if (M.spw == 1) o << "  #pragma unroll 1\n";
+  o << "  for (int s_ = s0; s_ < s1; ++s_) {\n"
+       "    const i64 e = lo + s_, c = col[e];\n"
+       "    const T* xb = x + c * " << DX << "; const T* axb = La + c * " << DX << "; const T* yb = y + e * " << DY << "; const T* byb = Lb + e * " << DY
+    << ";\n    const T* wb = W + e * " << NW << "; const T* cwb = LC + e * " << NW << ";\n"
+       "    T* lxb = rows + e * " << DX << "; T* lyb = Ly + e * " << DY << "; T* lwb = LW + e * " << NW << ";\n";
+  E.load_y("yb", "    ");
+  E.load_y("byb", "    ", "b");
+  E.load_x("xb", "    ");
+  E.load_x("axb", "    ", true, true, &Em::AX);
+  E.declare_gy("    ", true);
+  E.gy_reduce_decls("    ");
+  E.declare_gx("    ");
+  E.double_backward_paths("wb", "cwb", "gzb", "lwb", "", "    ");
+  E.store_gx("lxb", "    ");
+  E.reduce_store_gy("lyb", "    ");
+  o << "  }\n";
+  o << "  const int used = each > 0 ? (n + each - 1) / each : 0;\n  if (wk < used) { T* dst_ = red + wk * " << DZ << ";\n";
+  for (size_t sz = 0; sz < P.irz.size(); ++sz) E.store_z_seg("dst_", sz, "    ", &Em::LZ);
+  o << "  }\n  __syncthreads();\n";
+  sum_of_workers(E, DZ, K.wg);
+  o << "}\n";
+  K.source = o.str();
+  K.screen_divergence = true;
+  return true;
+}
+
+// out[r] = the sum of the rows `rows[perm[q]]` (dim_x words) over the positions q of row r: a workgroup of four waves per row,
+// each a quarter of the positions, a lane as many vectors of the row as it takes (the last ones are added by several lanes
+// alike).  Bound by the reads of the rows, in the order of the senders.
+void emit_row_sums(const Plan& P, Kernel& K) {
+  const int D = (int)P.dim_x(), most = P.dtype == CGTP_F64 ? 2 : 4, v = D >= most ? most : 1, per = (D + 64 * v - 1) / (64 * v);
+  const std::string VT = v == 1 ? "T" : "V" + std::to_string(v);
+  K.wg = 256;
+  K.name = "cgtp_conv_row_sums";
+  Em E(P, P.map[CGTP_K_CONV_DBL_BWD]);
+  E.preamble();
+  E.emit_row_of();
+  auto& o = E.o;
+  o << "extern \"C\" __global__ void __launch_bounds__(256) " << K.name
+    << "(const T* __restrict__ rows, T* __restrict__ out, const i64* __restrict__ ptr, const i64* __restrict__ perm, i64 V, T* part, int* cnt, int lg)\n{\n"
+       "  __shared__ __attribute__((aligned(16))) T red[" << 4 * D << "];\n  __shared__ int before;\n"
+       "  const int t = threadIdx.x, lane = t & 63, wk = __builtin_amdgcn_readfirstlane(t >> 6);\n";
+  row_of_workgroup(E, "ptr");
+  o << "  const int each = (n + 3) / 4, s0 = wk * each, s1 = s0 + each < n ? s0 + each : n;\n";
+  o << "  int d[" << per << "];\n  " << VT << " acc[" << per << "];\n  #pragma unroll\n  for (int k = 0; k < " << per << "; ++k) { d[k] = (k * 64 + lane) * " << v << " < " << D - v
+    << " ? (k * 64 + lane) * " << v << " : " << D - v << "; acc[k] = (T)0; }\n";
+  o << "  #pragma unroll 4\n  for (int s_ = s0; s_ < s1; ++s_) {\n    const T* src = rows + perm[lo + s_] * " << D << ";\n    #pragma unroll\n    for (int k = 0; k < " << per
+    << "; ++k) acc[k] += *(const " << VT << "*)(src + d[k]);\n  }\n";
+  o << "  const int used = each > 0 ? (n + each - 1) / each : 0;\n  if (wk < used) {\n    #pragma unroll\n    for (int k = 0; k < " << per << "; ++k) *(" << VT << "*)(red + wk * "
+    << D << " + d[k]) = acc[k];\n  }\n  __syncthreads();\n";
+  sum_of_workers(E, D, K.wg);
+  o << "}\n";
+  K.source = o.str();
+  K.screen_divergence = true;
 }
 
 // Nondeterministic convolution for unsorted edge lists (paper Sec. 3.5, the variant "omitted for

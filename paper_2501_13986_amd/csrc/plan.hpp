@@ -100,6 +100,7 @@ struct Plan {
   LaneMap map[9];  // indexed by cgtp_kernel
   Kernel k[9];  // indexed by cgtp_kernel
   Kernel k_row[2][2];       // convolution with a workgroup per row: [forward, backward][plain, non-temporal streams] (no source: not for this plan)
+  Kernel k_dbl_row[3], k_row_sums;   // second-order pass in one walk: [few rows, many, non-temporal streams], sums of the edges' dL/dx
   int* row_cnt = nullptr;   // their counters of finished pieces, one per window; zero between calls
   Kernel k_fix;  // merges split rows after the conv kernels (uvu) / adds per-wave gW partial sums (uvw)
   // workspace for split-row partial sums and per-edge receiver ids (conv)
@@ -126,6 +127,8 @@ void emit_fixup(const Plan& P, Kernel& out);
 // Convolution with one workgroup of `waves` waves per row.  nt: the per-edge streams are marked non-temporal.  false: this
 // plan has no such kernel.
 bool emit_uvu_conv_row(const Plan& P, bool backward, bool nt, int waves, Kernel& out);
+bool emit_uvu_conv_double_row(const Plan& P, bool nt, int waves, Kernel& out);   // the second-order pass, dL/dx as one row per edge
+void emit_row_sums(const Plan& P, Kernel& out);                                  // ... and their sums by senders
 constexpr int kConvRowLookup = 2048;   // rows whose row_ptr the backward keeps in LDS
 // uvw with per-sample weights (emit_uvw_ps.cpp): one wave per sample, VALU, fp32 and fp64
 void emit_uvw_ps_forward(const Plan& P, Kernel& out);

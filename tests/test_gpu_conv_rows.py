@@ -81,4 +81,30 @@ def test_edge_ranges_of_small_graphs(spec_name, name, prec, monkeypatch):
     if GRAPHS[name][1] > 3000:
         pytest.skip("beyond the row kernels' rule in any case")
     monkeypatch.setenv("CGTP_CONV_ROWS", "0")
-    check(spec_name, name, prec, double=False)
+    check(spec_name, name, prec)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("name", list(DEGREES))
+@pytest.mark.parametrize("spec_name", ["small", "odd_row", "mul1", "mul8", "mul20", "mul32", "mul75", "mul96", "mace"])
+def test_second_order_pass_of_rows_of_every_length(spec_name, name, prec):
+    from paper_2501_13986_amd import binding as b
+    if spec_name in ("mace", "mul96") and name == "hubs":
+        pytest.skip("the oracle takes minutes")
+    spec = TPSpec(*SPECS[spec_name])
+    plan = b.Plan(*SPECS[spec_name], dtype=b.CGTP_F64 if prec == "f64" else b.CGTP_F32, device=0)
+    recv, send, V = graph(name)
+    E = recv.shape[0]
+    print(f"spec={spec_name} graph={name} prec={prec} V={V} E={E}", flush=True)
+    row_ptr, col, perm, t_row_ptr, t_perm = oconv.csr_from_coo(recv, send, V)
+    npdt, tdt = (np.float64, torch.float64) if prec == "f64" else (np.float32, torch.float32)
+    x, gz, La = (synth.normal(i, (V, d)).astype(npdt) for i, d in ((1, spec.dim_x), (4, spec.dim_z), (5, spec.dim_x)))
+    y, W, Lb, LC = (synth.normal(i, (E, d)).astype(npdt) for i, d in ((2, spec.dim_y), (3, spec.n_w), (6, spec.dim_y), (7, spec.n_w)))
+    new = lambda *shape: torch.full(shape, float("nan"), dtype=tdt, device="cuda")
+    ref = memo(oconv.double_backward, spec, x, y, W, gz, La, Lb, LC, row_ptr, col)
+    for call in range(2):       # the second call finds the counters of the hubs as the first one left them
+        out = [new(V, spec.dim_x), new(E, spec.dim_y), new(E, spec.n_w), new(V, spec.dim_z)]
+        b.conv_double_backward(plan, *(dev(a) for a in (x, y, W, gz, La, Lb, LC)), *out, *(dev(a) for a in (row_ptr, col, t_row_ptr, t_perm)))
+        torch.cuda.synchronize()
+        for got, want, what in zip(out, ref, ("Lx", "Ly", "LW", "Lgz")):
+            assert_close(got.cpu().numpy(), want, prec, what)
