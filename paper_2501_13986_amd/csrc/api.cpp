@@ -274,8 +274,9 @@ void build_rows(Plan& P, int device) {
     // Workers of a row (us per call, 128 channels unless given): eight, on eight waves; four waves where the registers leave
     // room for one workgroup of eight (forward fp64, 5 000 nodes of degree 32, 617 -> 594).  For long streams fewer, so that
     // more rows are in flight: four workers where they share waves (32 channels, 20 000 nodes of degree 9, forward 116 -> 102),
-    // four waves in the backward (96 channels, 20 000 of degree 32, 895 -> 841), half of that for kernels of more than 128
-    // registers whose workers share waves (32 channels fp64, 20 000 of degree 32, 1444 -> 1329).
+    // three or four waves in the backward (96 channels, 20 000 of degree 32, 895 on eight, 841 on four and on three; of degree 9
+    // 337, 275, 268), half of that for kernels of more than 128 registers whose workers share waves (32 channels fp64, 20 000 of
+    // degree 32, 1444 -> 1329).
     for (const cgtp::Schedule& s : {first, frugal}) {
       Kernel plain, nt;
       const int full = std::max(1, 8 / m.spw), many = back ? 168 : 128;
@@ -290,7 +291,7 @@ void build_rows(Plan& P, int device) {
       if (!ok || (back && plain.vgprs > 200)) continue;
       int waves = plain.wg / 64;
       if (m.spw > 1) waves = std::max(1, 4 / m.spw);
-      else if (back) waves = std::min(waves, 4);
+      else if (back) waves = std::min(waves, plain.vgprs > 128 ? 4 : 3);
       if (back && m.spw > 1 && plain.vgprs > 128) waves = std::max(1, waves / 2);
       if (!attempt(nt, true, waves)) continue;
       P.k_row[back][0] = std::move(plain);
@@ -374,18 +375,28 @@ int row_lg(const Kernel& k, int spw, int64_t E) {
 
 // The kernel that walks a graph row by row, or NULL if the edge ranges do.  Non-temporal streams where the weights do not
 // fit the Infinity Cache (128 channels, 300 nodes of degree 32, forward 25 us without the hint and 27 with it; 5 000 nodes 308
-// and 300).  The forward has gained at every size measured; the backward, whose weights come in the order of the senders, does
-// for short streams (one launch instead of three) and long ones (more even work); between them the last workgroups
-// leave the machine idle (128 channels, 1 000 nodes of degree 32, 140 us by ranges, 154 by rows; with more than 128 registers, so
-// one workgroup of eight waves a CU, already at 300 of degree 36, 60 and 62).  Where several workers' weights share a cache line
-// it always does (4 channels, 20 000 nodes of degree 32, 178 -> 97).
-const Kernel* conv_by_rows(const Plan& P, bool backward, int64_t E) {
+// and 300).  The forward has gained at every size measured.  The backward, whose weights come in the order of the senders, does
+//  - where several workers' weights share a cache line (4 channels, 20 000 nodes of degree 32, 178 -> 97 us);
+//  - for short streams: one launch instead of three.  The limit is where the last workgroups leave the machine idle for as long:
+//    64 channels fp64, 1 500 nodes of degree 36, 104 us by ranges, 112 by rows; where workers share waves, 32 channels, 3 000
+//    nodes of degree 18, 77 and 66, of degree 36, 134 and 135; with more than 128 registers, so one workgroup of eight waves a CU,
+//    32 channels fp64, 800 of degree 18, 52 and 44, of degree 36, 81 and 87; 128 channels, 300 of degree 9, 31 and 28, of degree
+//    18, 38 and 40;
+//  - for many rows, when the workgroups of fewer waves come in two and a half rounds or more: 96 channels fp64, 5 000 nodes of
+//    degree 9, 138 -> 129, fp32 3 000 of degree 36 160 and 162, 5 000 255 and 250; 128 channels, 3 000 of degree 18, 227 -> 224
+//    (1 500 123 -> 126).  One fp64 channel a lane needs four rounds and rows worth the workgroup: 32 channels, 5 000 of degree
+//    36, 396 -> 409, 12 000 931 -> 912; 48 channels, 20 000 of degree 9, 273 -> 293, of degree 36, 1029 -> 1013.
+const Kernel* conv_by_rows(const Plan& P, bool backward, int64_t V, int64_t E) {
   const LaneMap& m = P.map[backward ? CGTP_K_CONV_BWD : CGTP_K_CONV_FWD];
   const int64_t stream = E * P.n_w * (int64_t)P.elt(), mb = (int64_t)1 << 20;
-  const bool wide = m.G * m.cpl * (int64_t)P.elt() >= 128;
-  const Kernel& k = P.k_row[backward][stream > 256 * mb];
-  if (backward && wide && stream > (P.k_row[1][0].vgprs > 128 ? 72 : 96) * mb && stream <= 700 * mb) return nullptr;
-  return k.fn ? &k : nullptr;
+  const Kernel &plain = P.k_row[backward][0], &nt = P.k_row[backward][1];
+  if (!plain.fn) return nullptr;
+  if (!backward || m.G * m.cpl * (int64_t)P.elt() < 128) return stream > 256 * mb ? &nt : &plain;
+  const int64_t few = plain.vgprs > 128 ? (m.cpl > 1 ? 40 : 72) : m.spw > 1 ? 144 : 96;
+  if (stream <= few * mb) return &plain;
+  const int64_t resident = (int64_t)nt.blocks_per_cu * P.num_cu;
+  if (P.dtype == CGTP_F64 && m.cpl == 1 ? V >= 4 * resident && E >= 16 * V : 2 * V >= 5 * resident) return &nt;
+  return nullptr;
 }
 
 // 64 words of pinned host memory, one per cache line, handed out to concurrent calls; allocated on first use and kept
@@ -974,7 +985,7 @@ cgtp_status conv_forward_impl(cgtp_plan* plan, const void* x_nodes, const void* 
   const Kernel& k = P.k[CGTP_K_CONV_FWD];
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_FWD].spw;   // edge-range workers per wave
-  const Kernel* rows = conv_by_rows(P, false, E);
+  const Kernel* rows = conv_by_rows(P, false, V, E);
   const int lg = rows ? row_lg(*rows, P.map[CGTP_K_CONV_FWD].spw, E) : 0;
   int64_t nchunk = rows ? ((E - 1) >> lg) + 1 : conv_ranges(P, k, spw, E);
   size_t part_bytes = (size_t)nchunk * 2 * P.dim_z() * P.elt();
@@ -1059,7 +1070,7 @@ cgtp_status conv_backward_perm(cgtp_plan* plan, const void* x_nodes, const void*
   const Kernel& k = P.k[CGTP_K_CONV_BWD];
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_BWD].spw;   // edge-range workers per wave
-  if (const Kernel* rows = conv_by_rows(P, true, E)) {
+  if (const Kernel* rows = conv_by_rows(P, true, V, E)) {
     const int lg = row_lg(*rows, P.map[CGTP_K_CONV_BWD].spw, E);
     const int64_t windows = ((E - 1) >> lg) + 1;
     const size_t part_bytes = round_up((size_t)windows * 2 * P.dim_x() * P.elt(), 256);
