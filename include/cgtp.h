@@ -198,8 +198,8 @@ cgtp_status conv_forward(cgtp_plan* plan, const void* x_nodes, const void* y_edg
  * harnesses that forbid hipMalloc.  Same arguments, same kernels and bit-identical results; the side buffer for rows
  * split between edge ranges is a static device array of the library (32 MiB per GPU, held from the moment the library
  * is loaded on that GPU until the process ends) instead of the plan's workspace, so the call allocates nothing - not
- * on its first use either.  Needs (edge ranges) * 2 * dim_z * sizeof(element) bytes, where the number of edge ranges
- * counts as min(E, workers of the kernel resident on the GPU), also where fewer are used; CGTP_EINVAL with the figures in cgtp_last_error() if that
+ * on its first use either.  May need (edge ranges) * 2 * dim_z * sizeof(element) bytes, where the number of edge ranges
+ * counts as min(E, workers of the range kernel resident on the GPU), also where fewer or none are used; CGTP_EINVAL with the figures in cgtp_last_error() if that
  * exceeds the array (the MACE-shaped benchmark plan needs exactly 32 MiB in either precision).  The plan's device
  * must be the current device.  All calls on one GPU share the array: calls that overlap in time on one GPU (different
  * streams, different plans, different threads) race; calls on one stream are ordered and safe. */
@@ -219,8 +219,10 @@ cgtp_status conv_backward(cgtp_plan* plan, const void* x_nodes, const void* y_ed
  * (gx_nodes, gy_edges, gW_edges) and a scalar L(a, b, C): given La_nodes = dL/da [V,dim_x], Lb_edges = dL/db
  * [E,dim_y], LC_edges = dL/dC [E,n_w], writes Lx_nodes = dL/dx [V,dim_x], Ly_edges = dL/dy [E,dim_y], LW_edges =
  * dL/dW [E,n_w], Lgz_nodes = dL/dgz [V,dim_z].  Equal to the paper's combination of seven convolution forward /
- * backward dispatches; evaluated by two fused kernels (one walk over receiver rows for dL/dgz, one over sender
- * rows for the rest).  Deterministic; same graph arrays, layouts, workspace rule and errors as conv_backward. */
+ * backward dispatches; evaluated in one walk over receiver rows, with dL/dx as one row per edge in the workspace (up
+ * to one gigabyte of them, if that can be allocated) and their sums by senders, or in two walks (receiver rows for
+ * dL/dgz, sender rows for the rest).  Deterministic; same graph arrays, layouts, workspace rule and errors as
+ * conv_backward. */
 cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,
                                  const void* gz_nodes, const void* La_nodes, const void* Lb_edges,
                                  const void* LC_edges, void* Lx_nodes, void* Ly_edges, void* LW_edges,

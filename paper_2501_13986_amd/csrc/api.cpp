@@ -365,13 +365,19 @@ int64_t conv_ranges(const Plan& P, const Kernel& k, int spw, int64_t E) {
   return std::min(std::min(E, all), std::max<int64_t>(1024 * spw, E / few));
 }
 
-// Rows of more than 2^lg edges are cut into windows of that size: 16 edges for each worker, and no more than 1 024 windows.
+// Rows of more than 2^lg edges are cut into windows of that size: 16 edges for each worker, and no more than 1 024 windows,
+// nor than leave the pieces (two rows of `row_bytes` a window) within the static array of conv_forward_static, so that it cuts
+// as conv_forward does.
 constexpr int64_t kRowWindows = 1024;
-int row_lg(const Kernel& k, int spw, int64_t E) {
+constexpr int64_t kRowPieceBytes = (int64_t)32 << 20;
+int row_lg(const Kernel& k, int spw, int64_t E, int64_t row_bytes) {
   int lg = 0;
-  while (((int64_t)1 << lg) < 16LL * (k.wg / 64) * spw || (E - 1) >> lg >= kRowWindows) ++lg;
+  while (((int64_t)1 << lg) < 16LL * (k.wg / 64) * spw || (E - 1) >> lg >= kRowWindows || (((E - 1) >> lg) + 1) * 2 * row_bytes > kRowPieceBytes) ++lg;
   return lg;
 }
+
+// A launch holds fewer than 2^32 work-items.
+bool rows_launch(const Kernel& k, int64_t V) { return k.fn && V < ((int64_t)1 << 32) / k.wg - kRowWindows; }
 
 // The kernel that walks a graph row by row, or NULL if the edge ranges do.  Non-temporal streams where the weights do not
 // fit the Infinity Cache (128 channels, 300 nodes of degree 32, forward 25 us without the hint and 27 with it; 5 000 nodes 308
@@ -390,7 +396,7 @@ const Kernel* conv_by_rows(const Plan& P, bool backward, int64_t V, int64_t E) {
   const LaneMap& m = P.map[backward ? CGTP_K_CONV_BWD : CGTP_K_CONV_FWD];
   const int64_t stream = E * P.n_w * (int64_t)P.elt(), mb = (int64_t)1 << 20;
   const Kernel &plain = P.k_row[backward][0], &nt = P.k_row[backward][1];
-  if (!plain.fn) return nullptr;
+  if (!rows_launch(plain, V) || !rows_launch(nt, V)) return nullptr;
   if (!backward || m.G * m.cpl * (int64_t)P.elt() < 128) return stream > 256 * mb ? &nt : &plain;
   const int64_t few = plain.vgprs > 128 ? (m.cpl > 1 ? 40 : 72) : m.spw > 1 ? 144 : 96;
   if (stream <= few * mb) return &plain;
@@ -986,7 +992,7 @@ cgtp_status conv_forward_impl(cgtp_plan* plan, const void* x_nodes, const void* 
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_FWD].spw;   // edge-range workers per wave
   const Kernel* rows = conv_by_rows(P, false, V, E);
-  const int lg = rows ? row_lg(*rows, P.map[CGTP_K_CONV_FWD].spw, E) : 0;
+  const int lg = rows ? row_lg(*rows, P.map[CGTP_K_CONV_FWD].spw, E, P.dim_z() * (int64_t)P.elt()) : 0;
   int64_t nchunk = rows ? ((E - 1) >> lg) + 1 : conv_ranges(P, k, spw, E);
   size_t part_bytes = (size_t)nchunk * 2 * P.dim_z() * P.elt();
   void* part = nullptr;
@@ -1071,7 +1077,7 @@ cgtp_status conv_backward_perm(cgtp_plan* plan, const void* x_nodes, const void*
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_BWD].spw;   // edge-range workers per wave
   if (const Kernel* rows = conv_by_rows(P, true, V, E)) {
-    const int lg = row_lg(*rows, P.map[CGTP_K_CONV_BWD].spw, E);
+    const int lg = row_lg(*rows, P.map[CGTP_K_CONV_BWD].spw, E, P.dim_x() * (int64_t)P.elt());
     const int64_t windows = ((E - 1) >> lg) + 1;
     const size_t part_bytes = round_up((size_t)windows * 2 * P.dim_x() * P.elt(), 256);
     const bool lookup = V > cgtp::kConvRowLookup || E > INT32_MAX;   // (2 000 nodes: 30 us either way)
@@ -1136,9 +1142,9 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
   // three streams of weights do not fit the Infinity Cache (32 channels, 1 000 nodes of degree 32, 94 us without the hint and 103
   // with it; 2 000 nodes 178 and 173).
   const size_t el = P.elt(), row_bytes = round_up((size_t)E * P.dim_x() * el, 256);
-  if (P.k_dbl_row[0].fn && row_bytes <= (size_t)1 << 30) {
+  if (rows_launch(P.k_dbl_row[0], V) && rows_launch(P.k_row_sums, V) && row_bytes <= (size_t)1 << 30) {
     const Kernel& k = P.k_dbl_row[V <= 768 ? 0 : 3 * E * P.n_w * (int64_t)el > (int64_t)256 << 20 ? 2 : 1];
-    const int lg = row_lg(k, P.map[CGTP_K_CONV_DBL_BWD].spw, E), lg2 = row_lg(P.k_row_sums, 1, E);
+    const int lg = row_lg(k, P.map[CGTP_K_CONV_DBL_BWD].spw, E, P.dim_z() * (int64_t)el), lg2 = row_lg(P.k_row_sums, 1, E, P.dim_x() * (int64_t)el);
     const int64_t windows = ((E - 1) >> lg) + 1, windows2 = ((E - 1) >> lg2) + 1;
     if (ensure_ws(P, row_bytes + 2 * el * (size_t)std::max(windows * P.dim_z(), windows2 * P.dim_x())) == CGTP_OK) {
       void *edge_rows = P.ws, *pieces = (char*)P.ws + row_bytes;
