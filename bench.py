@@ -167,15 +167,17 @@ def main() -> int:
         """The roofline that binds a launch (the one with the larger minimum time) and both fractions."""
         dbytes = bytes_model(kind, prec, n, V)
         dflops = n * (F_FWD if kind.endswith("fwd") else F_BWD)
+        # the walk by rows or by edge ranges, whichever kernel the step runs
+        name = next((k for k in ("cgtp_" + kind + "_row", "cgtp_" + kind) if measured_traffic(k, prec)), "cgtp_" + kind)
         hbm_frac = dbytes / ms / 1e6 / HBM_PEAK_GBS
         alu_frac = dflops / ms / 1e9 / VALU_PEAK_TFLOPS[prec]
         if alu_frac > hbm_frac:
-            r = {"bound": "alu", "kernel": "cgtp_" + kind, "achieved": round(dflops / ms / 1e9, 2),
+            r = {"bound": "alu", "kernel": name, "achieved": round(dflops / ms / 1e9, 2),
                  "peak": VALU_PEAK_TFLOPS[prec], "unit": "TFLOP/s", "frac": round(alu_frac, 4)}
         else:
-            r = {"bound": "hbm", "kernel": "cgtp_" + kind, "achieved": round(dbytes / ms / 1e6, 1),
+            r = {"bound": "hbm", "kernel": name, "achieved": round(dbytes / ms / 1e6, 1),
                  "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(hbm_frac, 4)}
-        r.update({"traffic": measured_traffic("cgtp_" + kind, prec), "traffic_source": "profiles/" + TRAFFIC_FILE[prec],
+        r.update({"traffic": measured_traffic(name, prec), "traffic_source": "profiles/" + TRAFFIC_FILE[prec],
                   "dtype": prec, "alg_bytes_per_launch": dbytes, "alg_flops_per_launch": dflops, "avg_ms": round(ms, 4),
                   "frac_hbm": round(hbm_frac, 4), "frac_alu": round(alu_frac, 4)})
         return r

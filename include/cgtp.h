@@ -220,7 +220,7 @@ cgtp_status conv_backward(cgtp_plan* plan, const void* x_nodes, const void* y_ed
  * [E,dim_y], LC_edges = dL/dC [E,n_w], writes Lx_nodes = dL/dx [V,dim_x], Ly_edges = dL/dy [E,dim_y], LW_edges =
  * dL/dW [E,n_w], Lgz_nodes = dL/dgz [V,dim_z].  Equal to the paper's combination of seven convolution forward /
  * backward dispatches; evaluated in one walk over receiver rows, with dL/dx as one row per edge in the workspace (up
- * to one gigabyte of them, if that can be allocated) and their sums by senders, or in two walks (receiver rows for
+ * to four gigabytes of them, if that can be allocated) and their sums by senders, or in two walks (receiver rows for
  * dL/dgz, sender rows for the rest).  Deterministic; same graph arrays, layouts, workspace rule and errors as
  * conv_backward. */
 cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,

@@ -388,9 +388,9 @@ bool rows_launch(const Kernel& k, int64_t V) { return k.fn && V < ((int64_t)1 <<
 //    nodes of degree 18, 77 and 66, of degree 36, 134 and 135; with more than 128 registers, so one workgroup of eight waves a CU,
 //    32 channels fp64, 800 of degree 18, 52 and 44, of degree 36, 81 and 87; 128 channels, 300 of degree 9, 31 and 28, of degree
 //    18, 38 and 40;
-//  - for many rows, when the workgroups of fewer waves come in two and a half rounds or more: 96 channels fp64, 5 000 nodes of
+//  - for many rows, when the workgroups of fewer waves come in three rounds or more: 96 channels fp64, 5 000 nodes of
 //    degree 9, 138 -> 129, fp32 3 000 of degree 36 160 and 162, 5 000 255 and 250; 128 channels, 3 000 of degree 18, 227 -> 224
-//    (1 500 123 -> 126).  One fp64 channel a lane needs four rounds and rows worth the workgroup: 32 channels, 5 000 of degree
+//    (2 000 of degree 32 261 -> 266).  One fp64 channel a lane needs four rounds and rows worth the workgroup: 32 channels, 5 000 of degree
 //    36, 396 -> 409, 12 000 931 -> 912; 48 channels, 20 000 of degree 9, 273 -> 293, of degree 36, 1029 -> 1013.
 const Kernel* conv_by_rows(const Plan& P, bool backward, int64_t V, int64_t E) {
   const LaneMap& m = P.map[backward ? CGTP_K_CONV_BWD : CGTP_K_CONV_FWD];
@@ -401,7 +401,7 @@ const Kernel* conv_by_rows(const Plan& P, bool backward, int64_t V, int64_t E) {
   const int64_t few = plain.vgprs > 128 ? (m.cpl > 1 ? 40 : 72) : m.spw > 1 ? 144 : 96;
   if (stream <= few * mb) return &plain;
   const int64_t resident = (int64_t)nt.blocks_per_cu * P.num_cu;
-  if (P.dtype == CGTP_F64 && m.cpl == 1 ? V >= 4 * resident && E >= 16 * V : 2 * V >= 5 * resident) return &nt;
+  if (P.dtype == CGTP_F64 && m.cpl == 1 ? V >= 4 * resident && E >= 16 * V : V >= 3 * resident) return &nt;
   return nullptr;
 }
 
@@ -1138,11 +1138,12 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
   const Kernel& kf = P.k[CGTP_K_CONV_DBL_FWD];
   const Kernel& kb = P.k[CGTP_K_CONV_DBL_BWD];
   if (!kf.fn || !kb.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
-  // One walk, if the rows of dL/dx of all edges are no more than a gigabyte and there is memory for them; non-temporal where the
-  // three streams of weights do not fit the Infinity Cache (32 channels, 1 000 nodes of degree 32, 94 us without the hint and 103
-  // with it; 2 000 nodes 178 and 173).
+  // One walk, if the rows of dL/dx of all edges are no more than four gigabytes (about half of one of the weight streams) and
+  // there is memory for them: 128 channels, 16 000 nodes of degree 40, 2.9 GB, two walks 6043 us, one 5229.  Non-temporal where
+  // the three streams of weights do not fit the Infinity Cache (32 channels, 1 000 nodes of degree 32, 94 us without the hint and
+  // 103 with it; 2 000 nodes 178 and 173).
   const size_t el = P.elt(), row_bytes = round_up((size_t)E * P.dim_x() * el, 256);
-  if (rows_launch(P.k_dbl_row[0], V) && rows_launch(P.k_row_sums, V) && row_bytes <= (size_t)1 << 30) {
+  if (rows_launch(P.k_dbl_row[0], V) && rows_launch(P.k_row_sums, V) && row_bytes <= (size_t)4 << 30) {
     const Kernel& k = P.k_dbl_row[V <= 768 ? 0 : 3 * E * P.n_w * (int64_t)el > (int64_t)256 << 20 ? 2 : 1];
     const int lg = row_lg(k, P.map[CGTP_K_CONV_DBL_BWD].spw, E, P.dim_z() * (int64_t)el), lg2 = row_lg(P.k_row_sums, 1, E, P.dim_x() * (int64_t)el);
     const int64_t windows = ((E - 1) >> lg) + 1, windows2 = ((E - 1) >> lg2) + 1;
