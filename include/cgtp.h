@@ -220,9 +220,9 @@ cgtp_status conv_backward(cgtp_plan* plan, const void* x_nodes, const void* y_ed
  * [E,dim_y], LC_edges = dL/dC [E,n_w], writes Lx_nodes = dL/dx [V,dim_x], Ly_edges = dL/dy [E,dim_y], LW_edges =
  * dL/dW [E,n_w], Lgz_nodes = dL/dgz [V,dim_z].  Equal to the paper's combination of seven convolution forward /
  * backward dispatches; evaluated in one walk over receiver rows, with dL/dx as one row per edge in the workspace (up
- * to four gigabytes of them, if that can be allocated) and their sums by senders, or in two walks (receiver rows for
- * dL/dgz, sender rows for the rest).  Deterministic; same graph arrays, layouts, workspace rule and errors as
- * conv_backward. */
+ * to four gigabytes of them, if it has room or can grow, which it does not while hip_stream is being captured) and
+ * their sums by senders, or in two walks (receiver rows for dL/dgz, sender rows for the rest).  Deterministic; same
+ * graph arrays, layouts, workspace rule and errors as conv_backward. */
 cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,
                                  const void* gz_nodes, const void* La_nodes, const void* Lb_edges,
                                  const void* LC_edges, void* Lx_nodes, void* Ly_edges, void* LW_edges,

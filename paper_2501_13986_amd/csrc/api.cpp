@@ -339,6 +339,21 @@ cgtp_status ensure_ws(Plan& P, size_t bytes) {
   return CGTP_OK;
 }
 
+// ensure_ws for a workspace that a call can do without: false also where the call is being captured, which forbids growing it,
+// or where as much was refused before (each attempt waits for the device and gives up the workspace there is).
+bool optional_ws(Plan& P, size_t bytes, hipStream_t st) {
+  if (bytes <= P.ws_bytes) return true;
+  if (bytes >= P.ws_refused) return false;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const hipError_t e = hipStreamIsCapturing(st, &capture);
+  if (e == hipSuccess && capture == hipStreamCaptureStatusNone) {
+    if (ensure_ws(P, bytes) == CGTP_OK) return true;
+    P.ws_refused = bytes;
+  }
+  (void)hipGetLastError();
+  return false;
+}
+
 // The merge kernel of the convolution's split rows: one wave per edge range and slice of a row (emit_fixup).
 cgtp_status launch_fixup(const Plan& P, const void* out, const void* part, const int64_t* ptr, int64_t V, int64_t E, int64_t nchunk,
                          int64_t row, hipStream_t st) {
@@ -1139,15 +1154,15 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
   const Kernel& kb = P.k[CGTP_K_CONV_DBL_BWD];
   if (!kf.fn || !kb.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   // One walk, if the rows of dL/dx of all edges are no more than four gigabytes (about half of one of the weight streams) and
-  // there is memory for them: 128 channels, 16 000 nodes of degree 40, 2.9 GB, two walks 6043 us, one 5229.  Non-temporal where
-  // the three streams of weights do not fit the Infinity Cache (32 channels, 1 000 nodes of degree 32, 94 us without the hint and
-  // 103 with it; 2 000 nodes 178 and 173).
+  // the workspace has or gets room for them: 128 channels, 16 000 nodes of degree 40, 2.9 GB, two walks 6043 us, one 5229.
+  // Non-temporal where the three streams of weights do not fit the Infinity Cache (32 channels, 1 000 nodes of degree 32, 94 us
+  // without the hint and 103 with it; 2 000 nodes 178 and 173).
   const size_t el = P.elt(), row_bytes = round_up((size_t)E * P.dim_x() * el, 256);
   if (rows_launch(P.k_dbl_row[0], V) && rows_launch(P.k_row_sums, V) && row_bytes <= (size_t)4 << 30) {
     const Kernel& k = P.k_dbl_row[V <= 768 ? 0 : 3 * E * P.n_w * (int64_t)el > (int64_t)256 << 20 ? 2 : 1];
     const int lg = row_lg(k, P.map[CGTP_K_CONV_DBL_BWD].spw, E, P.dim_z() * (int64_t)el), lg2 = row_lg(P.k_row_sums, 1, E, P.dim_x() * (int64_t)el);
     const int64_t windows = ((E - 1) >> lg) + 1, windows2 = ((E - 1) >> lg2) + 1;
-    if (ensure_ws(P, row_bytes + 2 * el * (size_t)std::max(windows * P.dim_z(), windows2 * P.dim_x())) == CGTP_OK) {
+    if (optional_ws(P, row_bytes + 2 * el * (size_t)std::max(windows * P.dim_z(), windows2 * P.dim_x()), st)) {
       void *edge_rows = P.ws, *pieces = (char*)P.ws + row_bytes;
       void* args[] = {(void*)&x_nodes,   (void*)&y_edges,  (void*)&W_edges, (void*)&gz_nodes,  (void*)&La_nodes,  (void*)&Lb_edges,
                       (void*)&LC_edges,  (void*)&edge_rows, (void*)&Ly_edges, (void*)&LW_edges, (void*)&Lgz_nodes, (void*)&row_ptr,
@@ -1158,7 +1173,6 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
                           (void*)&V,         (void*)&pieces,   (void*)&P.row_cnt, (void*)&lg2};
       return launch(P.k_row_sums, (unsigned)(V + windows2 - 1), sum_args, st);
     }
-    (void)hipGetLastError();
   }
   const int spwf = P.map[CGTP_K_CONV_DBL_FWD].spw, spwb = P.map[CGTP_K_CONV_DBL_BWD].spw;
   int64_t nf = conv_ranges(P, kf, spwf, E);

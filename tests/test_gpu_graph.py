@@ -58,3 +58,51 @@ def test_step_replays_from_a_hip_graph():
         torch.cuda.synchronize()
         for k in outs:
             assert torch.equal(outs[k], eager[k]), (rep, k)
+
+
+def test_second_order_pass_captured_on_a_larger_graph():
+    """The one-walk form wants a row of dL/dx per edge in the workspace.  Where a capture finds less, the pass takes the two
+    walks, whose need a smaller graph's call has covered (40 000 rows of 128 words, against two for each of at most 16 384
+    workers and 44 000 receiver ids)."""
+    from paper_2501_13986_amd import binding as b
+    plan = b.Plan("32x0e+32x1o", "1x0e+1x1o", "32x0e+32x1o", dtype=b.CGTP_F32, device=0)
+    DX, DY, DZ, NW = plan.dim_x, plan.dim_y, plan.dim_z, plan.n_w
+
+    def problem(E, V=500):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(E)
+        rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+        recv, send = (torch.randint(0, V, (E,), generator=g, device="cuda") for _ in range(2))
+        row_ptr, col, _, t_row_ptr, t_perm = b.cgtp_csr_from_coo(recv, send, V)
+        ins = [rnd(V, DX), rnd(E, DY), rnd(E, NW), rnd(V, DZ), rnd(V, DX), rnd(E, DY), rnd(E, NW)]
+        outs = [torch.full(s, float("nan"), device="cuda") for s in ((V, DX), (E, DY), (E, NW), (V, DZ))]
+        return ins, outs, (row_ptr, col, t_row_ptr, t_perm)
+
+    small, large = problem(40000), problem(44000)
+    call = lambda p, plan=plan: b.conv_double_backward(plan, *p[0], *p[1], *p[2])
+    print("capture of conv_double_backward E=44000 after E=40000", flush=True)
+    side = torch.cuda.Stream()   # default priority
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        call(small)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            call(large)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    replays = []
+    for rep in range(3):
+        for v in large[1]:
+            v.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        replays.append([v.clone() for v in large[1]])
+    call(large, b.Plan("32x0e+32x1o", "1x0e+1x1o", "32x0e+32x1o", dtype=b.CGTP_F32, device=0))
+    torch.cuda.synchronize()
+    for got in replays:
+        for a, first, eager in zip(got, replays[0], large[1]):
+            assert torch.equal(a, first)
+            # fp32 sums of about 100 edges (and 32 channels) in two orders: 2^-24 sqrt(3200 * terms) < 1e-5 of the norm
+            assert float((a - eager).norm()) <= 1e-5 * float(eager.norm())
