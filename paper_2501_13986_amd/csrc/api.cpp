@@ -13,6 +13,7 @@
 #include <string>
 #include <tuple>
 
+#include "conv_split.hpp"
 #include "csr.hpp"
 #include "plan.hpp"
 
@@ -367,32 +368,23 @@ int64_t resident_waves(const Plan& P, const Kernel& k) { return (int64_t)k.block
 
 int64_t most_ranges(const Plan& P, const Kernel& k, int spw) { return resident_waves(P, k) * spw * cgtp::env_int("CGTP_CONV_CHUNK_MULT", 1); }
 
-// Edge ranges of a convolution kernel: one per resident worker, but where that leaves fewer than two edges each, ranges of
-// three (of eight for workers that share a wave with many others), as long as 1 024 waves have work: every range costs
-// a row search and up to two pieces of split rows for the merge kernel.
-// forward + backward, one edge range per worker -> this: 3 000 nodes of 4 channels 136 -> 69 us, 300 nodes of 96 channels
-// 46 -> 39, 300 nodes of 128 channels 69 -> 67 (second order 93 -> 85).  With two edges per worker already, three are
-// slower (second order, 700 nodes of 32 channels 72 -> 76), and so is a range of four for each of fewer than 1 024 waves
-// (27 nodes of 32 channels 26 -> 30).
-int64_t conv_ranges(const Plan& P, const Kernel& k, int spw, int64_t E) {
-  const int64_t all = most_ranges(P, k, spw), few = spw >= 8 ? 8 : 3;
-  if (E >= 2 * all) return all;
-  return std::min(std::min(E, all), std::max<int64_t>(1024 * spw, E / few));
-}
+int64_t conv_ranges(const Plan& P, const Kernel& k, int spw, int64_t E) { return cgtp::conv_ranges(most_ranges(P, k, spw), spw, E); }
 
-// Rows of more than 2^lg edges are cut into windows of that size: 16 edges for each worker, and no more than 1 024 windows,
-// nor than leave the pieces (two rows of `row_bytes` a window) within the static array of conv_forward_static, so that it cuts
-// as conv_forward does.
-constexpr int64_t kRowWindows = 1024;
-constexpr int64_t kRowPieceBytes = (int64_t)32 << 20;
-int row_lg(const Kernel& k, int spw, int64_t E, int64_t row_bytes) {
-  int lg = 0;
-  while (((int64_t)1 << lg) < 16LL * (k.wg / 64) * spw || (E - 1) >> lg >= kRowWindows || (((E - 1) >> lg) + 1) * 2 * row_bytes > kRowPieceBytes) ++lg;
-  return lg;
+// Workers of a row in a kernel that walks row by row; 0 if the plan has none.
+int64_t row_workers(const Kernel& k, int spw) { return k.fn ? (int64_t)(k.wg / 64) * spw : 0; }
+
+int row_lg(const Kernel& k, int spw, int64_t E, int64_t row_bytes) { return cgtp::row_lg(row_workers(k, spw), E, row_bytes); }
+
+// Bytes of the pieces of split rows in the workspace of conv_forward or conv_backward: the same whichever kernel walks the graph.
+size_t piece_bytes(const Plan& P, bool backward, int64_t E) {
+  const int kind = backward ? CGTP_K_CONV_BWD : CGTP_K_CONV_FWD, spw = P.map[kind].spw;
+  const int64_t row = (backward ? P.dim_x() : P.dim_z()) * (int64_t)P.elt();
+  const Kernel* rows = P.k_row[backward];
+  return (size_t)(cgtp::most_pieces(most_ranges(P, P.k[kind], spw), spw, {row_workers(rows[0], spw), row_workers(rows[1], spw)}, E, row) * row);
 }
 
 // A launch holds fewer than 2^32 work-items.
-bool rows_launch(const Kernel& k, int64_t V) { return k.fn && V < ((int64_t)1 << 32) / k.wg - kRowWindows; }
+bool rows_launch(const Kernel& k, int64_t V) { return k.fn && V < ((int64_t)1 << 32) / k.wg - cgtp::kRowWindows; }
 
 // The kernel that walks a graph row by row, or NULL if the edge ranges do.  Non-temporal streams where the weights do not
 // fit the Infinity Cache (128 channels, 300 nodes of degree 32, forward 25 us without the hint and 27 with it; 5 000 nodes 308
@@ -711,7 +703,7 @@ cgtp_status cgtp_plan_create_ex(const char* irreps_x, const char* irreps_y, cons
     return fail(CGTP_ECOMPILE, e.what());
   }
   if (P.k_row[0][0].fn || P.k_row[1][0].fn || P.k_dbl_row[0].fn) {
-    const size_t n = kRowWindows * sizeof(int);
+    const size_t n = cgtp::kRowWindows * sizeof(int);
     hipError_t e = hipMalloc((void**)&P.row_cnt, n);
     if (e == hipSuccess) e = hipMemset(P.row_cnt, 0, n);
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -1007,9 +999,8 @@ cgtp_status conv_forward_impl(cgtp_plan* plan, const void* x_nodes, const void* 
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_FWD].spw;   // edge-range workers per wave
   const Kernel* rows = conv_by_rows(P, false, V, E);
-  const int lg = rows ? row_lg(*rows, P.map[CGTP_K_CONV_FWD].spw, E, P.dim_z() * (int64_t)P.elt()) : 0;
-  int64_t nchunk = rows ? ((E - 1) >> lg) + 1 : conv_ranges(P, k, spw, E);
-  size_t part_bytes = (size_t)nchunk * 2 * P.dim_z() * P.elt();
+  const int lg = rows ? row_lg(*rows, spw, E, P.dim_z() * (int64_t)P.elt()) : 0;
+  int64_t nchunk = rows ? cgtp::row_windows(lg, E) : conv_ranges(P, k, spw, E);
   void* part = nullptr;
   cgtp_status s = CGTP_OK;
   if (use_static) {
@@ -1022,12 +1013,12 @@ cgtp_status conv_forward_impl(cgtp_plan* plan, const void* x_nodes, const void* 
     // the limit of this entry point is a rule on the plan and E, whatever number of ranges suits a small graph
     const int64_t ranges = std::min(E, most_ranges(P, k, spw));
     const size_t need = (size_t)ranges * 2 * P.dim_z() * P.elt();
-    if (need > cap || part_bytes > cap)
+    if (need > cap || (size_t)nchunk * 2 * P.dim_z() * P.elt() > cap)
       return fail(CGTP_EINVAL, "conv_forward_static: this problem needs " + std::to_string(need) + " bytes of scratch for " +
                                    std::to_string(ranges) + " edge ranges, the static buffer holds " + std::to_string(cap) +
                                    "; use conv_forward");
   } else {
-    s = ensure_ws(P, part_bytes);
+    s = ensure_ws(P, piece_bytes(P, false, E));
     if (s != CGTP_OK) return s;
     part = P.ws;
   }
@@ -1091,23 +1082,8 @@ cgtp_status conv_backward_perm(cgtp_plan* plan, const void* x_nodes, const void*
   const Kernel& k = P.k[CGTP_K_CONV_BWD];
   if (!k.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
   const int spw = P.map[CGTP_K_CONV_BWD].spw;   // edge-range workers per wave
-  if (const Kernel* rows = conv_by_rows(P, true, V, E)) {
-    const int lg = row_lg(*rows, P.map[CGTP_K_CONV_BWD].spw, E, P.dim_x() * (int64_t)P.elt());
-    const int64_t windows = ((E - 1) >> lg) + 1;
-    const size_t part_bytes = round_up((size_t)windows * 2 * P.dim_x() * P.elt(), 256);
-    const bool lookup = V > cgtp::kConvRowLookup || E > INT32_MAX;   // (2 000 nodes: 30 us either way)
-    const cgtp_status s = ensure_ws(P, part_bytes + (lookup ? (size_t)E * 8 : 0));
-    if (s != CGTP_OK) return s;
-    int64_t* t_recv = lookup ? (int64_t*)((char*)P.ws + part_bytes) : nullptr;
-    if (lookup) HIP_TRY(cgtp::launch_recv_of_tperm(row_ptr, t_perm, V, E, t_recv, st));
-    void* args[] = {(void*)&x_nodes,  (void*)&y_edges,   (void*)&W_edges, (void*)&gz_nodes,  (void*)&gx_nodes, (void*)&gy_edges,
-                    (void*)&gW_edges, (void*)&t_row_ptr, (void*)&t_perm,  (void*)&row_ptr,   (void*)&t_recv,   (void*)&V,
-                    (void*)&P.ws,     (void*)&P.row_cnt, (void*)&lg,      (void*)&edge_perm};
-    return launch(*rows, (unsigned)(V + windows - 1), args, st);
-  }
-  int64_t nchunk = conv_ranges(P, k, spw, E);
-  size_t part_bytes = round_up((size_t)nchunk * 2 * P.dim_x() * P.elt(), 256);
-  const size_t recv_bytes = round_up((size_t)E * 8, 256);
+  // the same workspace whichever kernel walks the graph
+  const size_t part_bytes = round_up(piece_bytes(P, true, E), 256), recv_bytes = round_up((size_t)E * 8, 256);
   // one scratch row for the gy / gW words of the pipelined kernel's phantom edge (odd edge ranges)
   const size_t dummy_bytes = (round_up((size_t)P.dim_y(), 64) + (size_t)P.n_w) * P.elt();
   cgtp_status s = ensure_ws(P, part_bytes + recv_bytes + dummy_bytes);
@@ -1115,6 +1091,16 @@ cgtp_status conv_backward_perm(cgtp_plan* plan, const void* x_nodes, const void*
   void* part = P.ws;
   int64_t* t_recv = (int64_t*)((char*)P.ws + part_bytes);
   void* dummy = (char*)P.ws + part_bytes + recv_bytes;
+  if (const Kernel* rows = conv_by_rows(P, true, V, E)) {
+    const int lg = row_lg(*rows, spw, E, P.dim_x() * (int64_t)P.elt());
+    if (V > cgtp::kConvRowLookup || E > INT32_MAX) HIP_TRY(cgtp::launch_recv_of_tperm(row_ptr, t_perm, V, E, t_recv, st));
+    else t_recv = nullptr;   // the kernel looks them up (2 000 nodes: 30 us either way)
+    void* args[] = {(void*)&x_nodes,  (void*)&y_edges,   (void*)&W_edges, (void*)&gz_nodes,  (void*)&gx_nodes, (void*)&gy_edges,
+                    (void*)&gW_edges, (void*)&t_row_ptr, (void*)&t_perm,  (void*)&row_ptr,   (void*)&t_recv,   (void*)&V,
+                    (void*)&part,     (void*)&P.row_cnt, (void*)&lg,      (void*)&edge_perm};
+    return launch(*rows, (unsigned)(V + cgtp::row_windows(lg, E) - 1), args, st);
+  }
+  int64_t nchunk = conv_ranges(P, k, spw, E);
   HIP_TRY(cgtp::launch_recv_of_tperm(row_ptr, t_perm, V, E, t_recv, st));
   const int wpw = k.wg / 64;
   unsigned grid = (unsigned)((nchunk + (int64_t)wpw * spw - 1) / ((int64_t)wpw * spw));

@@ -106,3 +106,59 @@ def test_second_order_pass_captured_on_a_larger_graph():
             assert torch.equal(a, first)
             # fp32 sums of about 100 edges (and 32 channels) in two orders: 2^-24 sqrt(3200 * terms) < 1e-5 of the norm
             assert float((a - eager).norm()) <= 1e-5 * float(eager.norm())
+
+
+# larger and smaller graph: either side of a doubling of the windows (513 and 1 024 of them), and the backward by rows (15 000 of
+# them) against the one by edge ranges, which leave more pieces
+@pytest.mark.parametrize("large,small", [((500, 131073), (500, 131072)), ((15000, 420000), (500, 400000))])
+def test_a_larger_graphs_workspace_serves_a_smaller_one(large, small):
+    """A capture of the smaller graph after an eager call on the larger one allocates nothing; an eager call on the smaller
+    one leaves the buffer that a captured step on the larger one uses."""
+    from paper_2501_13986_amd import binding as b
+    plan = b.Plan("32x0e+32x1o", "1x0e+1x1o", "32x0e+32x1o", dtype=b.CGTP_F32, device=0)
+    DX, DY, DZ, NW = plan.dim_x, plan.dim_y, plan.dim_z, plan.n_w
+    print(f"capture and eager calls of conv_forward/conv_backward {large} {small}", flush=True)
+
+    def problem(V, E):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(E)
+        rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+        recv, send = (torch.randint(0, V, (E,), generator=g, device="cuda") for _ in range(2))
+        row_ptr, col, _, t_row_ptr, t_perm = b.cgtp_csr_from_coo(recv, send, V)
+        ins, gz = [rnd(V, DX), rnd(E, DY), rnd(E, NW)], rnd(V, DZ)
+        outs = [torch.full(s, float("nan"), device="cuda") for s in ((V, DZ), (V, DX), (E, DY), (E, NW))]
+
+        def step():
+            b.conv_forward(plan, *ins, outs[0], row_ptr, col)
+            b.conv_backward(plan, *ins, gz, *outs[1:], row_ptr, col, t_row_ptr, t_perm)
+        return step, outs
+
+    def clear(outs):
+        for v in outs:
+            v.fill_(float("nan"))
+        torch.cuda.synchronize()
+
+    (step_l, out_l), (step_s, out_s) = problem(*large), problem(*small)
+    step_l()
+    torch.cuda.synchronize()
+    want_l = [v.clone() for v in out_l]
+    side = torch.cuda.Stream()   # default priority
+    side.wait_stream(torch.cuda.current_stream())
+    graph_s, graph_l = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph_s, stream=side):
+        step_s()
+    with torch.cuda.graph(graph_l, stream=side):
+        step_l()
+    torch.cuda.synchronize()
+    clear(out_s)
+    step_s()
+    torch.cuda.synchronize()
+    want_s = [v.clone() for v in out_s]
+    assert all(bool(torch.isfinite(v).all()) for v in want_l + want_s)
+    for rep in range(3):
+        for graph, out, want in ((graph_l, out_l, want_l), (graph_s, out_s, want_s)):
+            clear(out)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, w) for a, w in zip(out, want)), rep
+        step_s()      # eager work between the replays
