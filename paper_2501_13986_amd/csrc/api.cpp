@@ -243,14 +243,12 @@ void build_kernel(cgtp::Plan& P, int kind, Emit emit, int device) {
   K = std::move(best);
 }
 
-// false: the compiled code failed its check or needs private memory
+// For kernels that a plan can do without.  false: the code did not compile, failed its check or needs private memory
 bool compiles_without_scratch(Kernel& k, int device) {
   try {
     cgtp::jit_compile(k, device == -1 ? -1 : -2);
-  } catch (const cgtp::RefusedCode&) {
+  } catch (const std::exception&) {
     return false;
-  } catch (const std::exception& e) {
-    throw CompileError{e.what()};
   }
   return k.scratch == 0;
 }
@@ -312,8 +310,7 @@ void build_double_rows(Plan& P, int device) {
     k[t].sched = P.k[CGTP_K_CONV_DBL_BWD].sched;
     if (!cgtp::emit_uvu_conv_double_row(P, t == 2, t == 0 ? few : many, k[t]) || !compiles_without_scratch(k[t], device)) return;
   }
-  cgtp::emit_row_sums(P, sums);
-  if (!compiles_without_scratch(sums, device)) return;
+  if (!cgtp::emit_row_sums(P, sums) || !compiles_without_scratch(sums, device)) return;
   for (int t = 0; t < 3; ++t) P.k_dbl_row[t] = std::move(k[t]);
   P.k_row_sums = std::move(sums);
 }
@@ -695,12 +692,16 @@ cgtp_status cgtp_plan_create_ex(const char* irreps_x, const char* irreps_y, cons
   try {
     for (auto& k : P.k) cgtp::jit_compile(k, device);
     cgtp::jit_compile(P.k_fix, device);
-    for (Kernel* k : row_kernels(P)) cgtp::jit_compile(*k, device);
   } catch (const std::exception& e) {
     for (auto& k : P.k) cgtp::jit_unload(k);
     cgtp::jit_unload(P.k_fix);
-    for (Kernel* k : row_kernels(P)) cgtp::jit_unload(*k);
     return fail(CGTP_ECOMPILE, e.what());
+  }
+  try {
+    for (Kernel* k : row_kernels(P)) cgtp::jit_compile(*k, device);
+  } catch (const std::exception&) {   // the walks by ranges take their place
+    for (Kernel* k : row_kernels(P)) cgtp::jit_unload(*k);
+    (void)hipGetLastError();
   }
   if (P.k_row[0][0].fn || P.k_row[1][0].fn || P.k_dbl_row[0].fn) {
     const size_t n = cgtp::kRowWindows * sizeof(int);

@@ -1707,7 +1707,7 @@ bool emit_uvu_conv_row(const Plan& P, bool backward, bool nt, int waves, Kernel&
   const int NWK = waves * M.spw;
   K.wg = 64 * waves;
   const int D = (int)(backward ? P.dim_x() : P.dim_z());
-  if ((int64_t)NWK * D * (int)P.elt() + (backward ? 4 * (kConvRowLookup + 1) + 12 * K.wg : 0) + 64 > 160 * 1024) return false;
+  if ((int64_t)NWK * D * (int)P.elt() + (backward ? 4 * (kConvRowLookup + 1) + 12 * K.wg : 0) + 64 > kLdsBytes) return false;
   K.name = backward ? "cgtp_conv_bwd_row" : "cgtp_conv_fwd_row";
   Em E(P, M, K.sched);
   E.preamble();
@@ -1805,7 +1805,7 @@ bool emit_uvu_conv_double_row(const Plan& P, bool nt, int waves, Kernel& K) {
   const int NWK = waves * M.spw, DX = (int)P.dim_x(), DY = (int)P.dim_y(), DZ = (int)P.dim_z();
   const i64 NW = P.n_w;
   K.wg = 64 * waves;
-  if ((int64_t)NWK * DZ * (int)P.elt() + 64 > 160 * 1024) return false;
+  if ((int64_t)NWK * DZ * (int)P.elt() + 64 > kLdsBytes) return false;
   K.name = "cgtp_conv_dbl_row";
   Em E(P, M, K.sched);
   E.preamble();
@@ -1861,7 +1861,8 @@ bool emit_uvu_conv_double_row(const Plan& P, bool nt, int waves, Kernel& K) {
 // out[r] = the sum of the rows `rows[perm[q]]` (dim_x words) over the positions q of row r: a workgroup of four waves per row,
 // each a quarter of the positions, a lane as many vectors of the row as it takes (the last ones are added by several lanes
 // alike).  Bound by the reads of the rows, in the order of the senders.
-void emit_row_sums(const Plan& P, Kernel& K) {
+bool emit_row_sums(const Plan& P, Kernel& K) {
+  if (4 * P.dim_x() * (int64_t)P.elt() + 64 > kLdsBytes) return false;
   const int D = (int)P.dim_x(), most = P.dtype == CGTP_F64 ? 2 : 4, v = D >= most ? most : 1, per = (D + 64 * v - 1) / (64 * v);
   const std::string VT = v == 1 ? "T" : "V" + std::to_string(v);
   K.wg = 256;
@@ -1886,6 +1887,7 @@ void emit_row_sums(const Plan& P, Kernel& K) {
   o << "}\n";
   K.source = o.str();
   K.screen_divergence = true;
+  return true;
 }
 
 // Nondeterministic convolution for unsorted edge lists (paper Sec. 3.5, the variant "omitted for

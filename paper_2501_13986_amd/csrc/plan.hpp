@@ -129,7 +129,8 @@ void emit_fixup(const Plan& P, Kernel& out);
 // plan has no such kernel.
 bool emit_uvu_conv_row(const Plan& P, bool backward, bool nt, int waves, Kernel& out);
 bool emit_uvu_conv_double_row(const Plan& P, bool nt, int waves, Kernel& out);   // the second-order pass, dL/dx as one row per edge
-void emit_row_sums(const Plan& P, Kernel& out);                                  // ... and their sums by senders
+bool emit_row_sums(const Plan& P, Kernel& out);                                  // ... and their sums by senders
+constexpr int64_t kLdsBytes = 160 * 1024;   // of a compute unit, the most that one workgroup can have
 constexpr int kConvRowLookup = 2048;   // rows whose row_ptr the backward keeps in LDS
 // uvw with per-sample weights (emit_uvw_ps.cpp): one wave per sample, VALU, fp32 and fp64
 void emit_uvw_ps_forward(const Plan& P, Kernel& out);
