@@ -219,15 +219,28 @@ cgtp_status conv_backward(cgtp_plan* plan, const void* x_nodes, const void* y_ed
  * (gx_nodes, gy_edges, gW_edges) and a scalar L(a, b, C): given La_nodes = dL/da [V,dim_x], Lb_edges = dL/db
  * [E,dim_y], LC_edges = dL/dC [E,n_w], writes Lx_nodes = dL/dx [V,dim_x], Ly_edges = dL/dy [E,dim_y], LW_edges =
  * dL/dW [E,n_w], Lgz_nodes = dL/dgz [V,dim_z].  Equal to the paper's combination of seven convolution forward /
- * backward dispatches; evaluated in one walk over receiver rows, with dL/dx as one row per edge in the workspace (up
- * to four gigabytes of them, if it has room or can grow, which it does not while hip_stream is being captured) and
- * their sums by senders, or in two walks (receiver rows for dL/dgz, sender rows for the rest).  Deterministic; same
- * graph arrays, layouts, workspace rule and errors as conv_backward. */
+ * backward dispatches; evaluated in two walks (receiver rows for dL/dgz, sender rows for the rest), or, on graphs so
+ * small that the rows fit the workspace of those, in one walk over receiver rows with dL/dx as one row per edge, and
+ * their sums by senders.  Which of them follows from the plan, V and E alone.  Deterministic; same graph arrays,
+ * layouts, workspace rule and errors as conv_backward. */
 cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,
                                  const void* gz_nodes, const void* La_nodes, const void* Lb_edges,
                                  const void* LC_edges, void* Lx_nodes, void* Ly_edges, void* LW_edges,
                                  void* Lgz_nodes, int64_t V, int64_t E, const int64_t* row_ptr, const int64_t* col,
                                  const int64_t* t_row_ptr, const int64_t* t_perm, void* hip_stream);
+
+/* conv_double_backward with memory for the one walk on larger graphs: `scratch` is caller-owned device memory of at
+ * least cgtp_conv_double_workspace_bytes(plan, V, E) bytes, 256-byte aligned (CGTP_EINVAL if it is smaller), free
+ * again for other work on hip_stream after the call; its contents are scratch.  The size is 0 where the pass needs
+ * none (the rows fit the plan's workspace) or goes in two walks whatever is given (rows beyond four gigabytes).  NULL:
+ * conv_double_backward.  The sums are in another order than in two walks; each form is deterministic. */
+size_t cgtp_conv_double_workspace_bytes(const cgtp_plan* plan, int64_t V, int64_t E);
+cgtp_status conv_double_backward_ws(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,
+                                    const void* gz_nodes, const void* La_nodes, const void* Lb_edges,
+                                    const void* LC_edges, void* Lx_nodes, void* Ly_edges, void* LW_edges,
+                                    void* Lgz_nodes, int64_t V, int64_t E, const int64_t* row_ptr, const int64_t* col,
+                                    const int64_t* t_row_ptr, const int64_t* t_perm, void* scratch, size_t scratch_bytes,
+                                    void* hip_stream);
 
 /* conv_forward / conv_backward for edge data that stays in the caller's own (unsorted) order: y_edges / W_edges /
  * gy_edges / gW_edges row edge_perm[c] belongs to CSR position c, with edge_perm the `perm` array that

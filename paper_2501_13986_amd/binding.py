@@ -1,6 +1,6 @@
 """ctypes binding of libcgtp.so: the functions of include/cgtp.h under the same names.
 
-Argument marshalling only: torch tensors supply device memory and the current stream, every
+Argument marshalling only: torch tensors supply device memory (scratch too) and the current stream, every
 step of the computation runs in the library's kernels.  There is no fallback: if the shared
 library is missing or a call fails, an exception is raised.
 """
@@ -23,7 +23,8 @@ STATUS = {0: "CGTP_OK", 1: "CGTP_EINVAL", 2: "CGTP_EUNSUPPORTED", 3: "CGTP_ECOMP
 EXPORTS = [
     "cgtp_plan_create", "cgtp_plan_create_ex", "cgtp_plan_destroy", "cgtp_plan_dim", "cgtp_plan_num_paths", "cgtp_plan_get_path",
     "cgtp_plan_path_nonzeros", "cgtp_plan_flops", "cgtp_plan_source", "cgtp_plan_kernel_info",
-    "tp_forward", "tp_backward", "tp_double_backward", "conv_forward", "conv_forward_static", "conv_backward", "conv_forward_perm", "conv_backward_perm", "conv_double_backward", "conv_forward_atomic", "conv_backward_atomic",
+    "tp_forward", "tp_backward", "tp_double_backward", "conv_forward", "conv_forward_static", "conv_backward", "conv_forward_perm", "conv_backward_perm", "conv_double_backward", "conv_double_backward_ws",
+    "cgtp_conv_double_workspace_bytes", "conv_forward_atomic", "conv_backward_atomic",
     "cgtp_csr_from_coo", "cgtp_csr_from_coo_async", "cgtp_csr_workspace_bytes", "cgtp_last_error", "cgtp_check_code_object",
 ]
 
@@ -80,6 +81,9 @@ def lib() -> C.CDLL:
     L.conv_forward_perm.argtypes = [vp, vp, vp, vp, vp, i64, i64, vp, vp, vp, vp]
     L.conv_backward_perm.argtypes = [vp] + [vp] * 7 + [i64, i64, vp, vp, vp, vp, vp, vp]
     L.conv_double_backward.argtypes = [vp] + [vp] * 11 + [i64, i64, vp, vp, vp, vp, vp]
+    L.conv_double_backward_ws.argtypes = [vp] + [vp] * 11 + [i64, i64, vp, vp, vp, vp, vp, C.c_size_t, vp]
+    L.cgtp_conv_double_workspace_bytes.argtypes = [vp, i64, i64]
+    L.cgtp_conv_double_workspace_bytes.restype = C.c_size_t
     L.conv_forward_atomic.argtypes = [vp, vp, vp, vp, vp, i64, i64, vp, vp, vp]
     L.conv_backward_atomic.argtypes = [vp] + [vp] * 7 + [i64, i64, vp, vp, vp]
     L.cgtp_csr_from_coo.argtypes = [vp, vp, i64, i64, vp, vp, vp, vp, vp, vp]
@@ -236,11 +240,22 @@ def conv_backward_perm(plan: Plan, x_nodes, y_edges, W_edges, gz_nodes, gx_nodes
 
 def conv_double_backward(plan: Plan, x_nodes, y_edges, W_edges, gz_nodes, La_nodes, Lb_edges, LC_edges, Lx_nodes, Ly_edges,
                          LW_edges, Lgz_nodes, row_ptr, col, t_row_ptr, t_perm):
+    """The memory of the one walk is torch's for the time of the call: shared by all plans, given back to its allocator on the
+    current stream, part of a captured graph's pool where the call is captured.  Where torch has none left the pass goes in
+    two walks, whose sums are in another order."""
     V, E = x_nodes.shape[0], y_edges.shape[0]
-    _check(lib().conv_double_backward(plan._h, _ptr(x_nodes), _ptr(y_edges), _ptr(W_edges), _ptr(gz_nodes), _ptr(La_nodes),
-                                      _ptr(Lb_edges), _ptr(LC_edges), _ptr(Lx_nodes), _ptr(Ly_edges), _ptr(LW_edges),
-                                      _ptr(Lgz_nodes), V, E, _ptr(row_ptr), _ptr(col), _ptr(t_row_ptr), _ptr(t_perm),
-                                      _stream()))
+    L, scratch = lib(), None
+    n = L.cgtp_conv_double_workspace_bytes(plan._h, V, E) if E >= 1024 else 0   # the rows of fewer edges fit the plan's workspace
+    if n:
+        import torch
+        try:
+            scratch = torch.empty(n, dtype=torch.uint8, device=x_nodes.device)
+        except torch.cuda.OutOfMemoryError:
+            n = 0
+    _check(L.conv_double_backward_ws(plan._h, _ptr(x_nodes), _ptr(y_edges), _ptr(W_edges), _ptr(gz_nodes), _ptr(La_nodes),
+                                     _ptr(Lb_edges), _ptr(LC_edges), _ptr(Lx_nodes), _ptr(Ly_edges), _ptr(LW_edges),
+                                     _ptr(Lgz_nodes), V, E, _ptr(row_ptr), _ptr(col), _ptr(t_row_ptr), _ptr(t_perm),
+                                     _ptr(scratch), n, _stream()))
     return Lx_nodes, Ly_edges, LW_edges, Lgz_nodes
 
 

@@ -337,21 +337,6 @@ cgtp_status ensure_ws(Plan& P, size_t bytes) {
   return CGTP_OK;
 }
 
-// ensure_ws for a workspace that a call can do without: false also where the call is being captured, which forbids growing it,
-// or where as much was refused before (each attempt waits for the device and gives up the workspace there is).
-bool optional_ws(Plan& P, size_t bytes, hipStream_t st) {
-  if (bytes <= P.ws_bytes) return true;
-  if (bytes >= P.ws_refused) return false;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  const hipError_t e = hipStreamIsCapturing(st, &capture);
-  if (e == hipSuccess && capture == hipStreamCaptureStatusNone) {
-    if (ensure_ws(P, bytes) == CGTP_OK) return true;
-    P.ws_refused = bytes;
-  }
-  (void)hipGetLastError();
-  return false;
-}
-
 // The merge kernel of the convolution's split rows: one wave per edge range and slice of a row (emit_fixup).
 cgtp_status launch_fixup(const Plan& P, const void* out, const void* part, const int64_t* ptr, int64_t V, int64_t E, int64_t nchunk,
                          int64_t row, hipStream_t st) {
@@ -409,6 +394,45 @@ const Kernel* conv_by_rows(const Plan& P, bool backward, int64_t V, int64_t E) {
   return nullptr;
 }
 
+size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+
+// The second-order pass of the convolution.  One walk over the receiver rows with a row of dL/dx per edge in memory, if the plan
+// has the kernels and those rows are no more than four gigabytes (about half of one of the weight streams): 128 channels, 16 000
+// nodes of degree 40, 2.9 GB, two walks 6043 us, one 5229.  Non-temporal where the three streams of weights do not fit the
+// Infinity Cache (32 channels, 1 000 nodes of degree 32, 94 us without the hint and 103 with it; 2 000 nodes 178 and 173).
+// The rows stand in the plan's workspace where the pieces and receivers of the two walks take as much anyway, else in memory
+// that the caller hands over; without it the pass goes in two walks.  All of it follows from the plan, V and E, so that a call
+// gives the same bits whatever was called before and whether it is captured or not.
+struct DoubleWalk {
+  int64_t nf = 0, nb = 0;                         // edge ranges of the two walks
+  size_t part_b = 0, ws = 0;                      // their workspace, which never falls with E
+  const Kernel* rows = nullptr;                   // one walk (NULL: none for this plan and graph)
+  int lg = 0, lg2 = 0;
+  size_t row_bytes = 0, one = 0;                  // bytes of the edges' rows, and with the pieces of cut rows
+};
+
+DoubleWalk double_walk(const Plan& P, int64_t V, int64_t E) {
+  const int spwf = P.map[CGTP_K_CONV_DBL_FWD].spw, spwb = P.map[CGTP_K_CONV_DBL_BWD].spw;
+  const size_t el = P.elt();
+  DoubleWalk d;
+  d.nf = conv_ranges(P, P.k[CGTP_K_CONV_DBL_FWD], spwf, E);
+  d.nb = conv_ranges(P, P.k[CGTP_K_CONV_DBL_BWD], spwb, E);
+  // the two walks run one after the other on the stream and share the side buffer; the receivers of somewhat more edges fit, as
+  // neighbour lists breathe
+  size_t receivers = 1024;
+  while (receivers < (size_t)E) receivers *= 2;
+  d.part_b = round_up((size_t)d.nb * 2 * P.dim_x() * el, 256);
+  d.ws = std::max((size_t)d.nf * 2 * P.dim_z() * el, d.part_b + receivers * 8);
+  if (!rows_launch(P.k_dbl_row[0], V) || !rows_launch(P.k_row_sums, V) || (size_t)E > ((size_t)4 << 30) / (P.dim_x() * el)) return d;
+  d.row_bytes = round_up((size_t)E * P.dim_x() * el, 256);
+  d.rows = &P.k_dbl_row[V <= 768 ? 0 : 3 * E * P.n_w * (int64_t)el > (int64_t)256 << 20 ? 2 : 1];
+  d.lg = row_lg(*d.rows, spwb, E, P.dim_z() * (int64_t)el);
+  d.lg2 = row_lg(P.k_row_sums, 1, E, P.dim_x() * (int64_t)el);
+  const int64_t w = cgtp::row_windows(d.lg, E), w2 = cgtp::row_windows(d.lg2, E);   // one window: no row is cut
+  d.one = d.row_bytes + 2 * el * (size_t)std::max(w > 1 ? w * P.dim_z() : 0, w2 > 1 ? w2 * P.dim_x() : 0);
+  return d;
+}
+
 // 64 words of pinned host memory, one per cache line, handed out to concurrent calls; allocated on first use and kept
 // until the process ends.  take() answers -1 if none is free or the allocation failed.
 struct HostFlags {
@@ -436,7 +460,6 @@ HostFlags& host_flags() {
   return *h;
 }
 
-size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 }  // namespace
 
@@ -1114,15 +1137,17 @@ cgtp_status conv_backward_perm(cgtp_plan* plan, const void* x_nodes, const void*
   return launch_fixup(P, gx_nodes, part, t_row_ptr, V, E, nchunk, P.dim_x(), st);
 }
 
-cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,
-                                 const void* gz_nodes, const void* La_nodes, const void* Lb_edges,
-                                 const void* LC_edges, void* Lx_nodes, void* Ly_edges, void* LW_edges,
-                                 void* Lgz_nodes, int64_t V, int64_t E, const int64_t* row_ptr, const int64_t* col,
-                                 const int64_t* t_row_ptr, const int64_t* t_perm, void* hip_stream) {
+cgtp_status conv_double_backward_ws(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,
+                                    const void* gz_nodes, const void* La_nodes, const void* Lb_edges,
+                                    const void* LC_edges, void* Lx_nodes, void* Ly_edges, void* LW_edges,
+                                    void* Lgz_nodes, int64_t V, int64_t E, const int64_t* row_ptr, const int64_t* col,
+                                    const int64_t* t_row_ptr, const int64_t* t_perm, void* scratch, size_t scratch_bytes,
+                                    void* hip_stream) {
   if (!plan) return fail(CGTP_EINVAL, "plan is NULL");
   if (V < 0 || E < 0) return fail(CGTP_EINVAL, "negative size");
   Plan& P = plan->P;
   if (P.mode != CGTP_UVU) return fail(CGTP_EUNSUPPORTED, "convolution is implemented for uvu plans only");
+  if (scratch && ((uintptr_t)scratch & 255)) return fail(CGTP_EINVAL, "scratch must be 256-byte aligned");
   if (V == 0) return E == 0 ? CGTP_OK : fail(CGTP_EINVAL, "edges without nodes");
   if (!Lx_nodes || !Lgz_nodes) return fail(CGTP_EINVAL, "NULL data pointer");
   hipStream_t st = (hipStream_t)hip_stream;
@@ -1140,35 +1165,25 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
   const Kernel& kf = P.k[CGTP_K_CONV_DBL_FWD];
   const Kernel& kb = P.k[CGTP_K_CONV_DBL_BWD];
   if (!kf.fn || !kb.fn) return fail(CGTP_EUNSUPPORTED, "kernel is not loaded (plan created without a device?)");
-  // One walk, if the rows of dL/dx of all edges are no more than four gigabytes (about half of one of the weight streams) and
-  // the workspace has or gets room for them: 128 channels, 16 000 nodes of degree 40, 2.9 GB, two walks 6043 us, one 5229.
-  // Non-temporal where the three streams of weights do not fit the Infinity Cache (32 channels, 1 000 nodes of degree 32, 94 us
-  // without the hint and 103 with it; 2 000 nodes 178 and 173).
-  const size_t el = P.elt(), row_bytes = round_up((size_t)E * P.dim_x() * el, 256);
-  if (rows_launch(P.k_dbl_row[0], V) && rows_launch(P.k_row_sums, V) && row_bytes <= (size_t)4 << 30) {
-    const Kernel& k = P.k_dbl_row[V <= 768 ? 0 : 3 * E * P.n_w * (int64_t)el > (int64_t)256 << 20 ? 2 : 1];
-    const int lg = row_lg(k, P.map[CGTP_K_CONV_DBL_BWD].spw, E, P.dim_z() * (int64_t)el), lg2 = row_lg(P.k_row_sums, 1, E, P.dim_x() * (int64_t)el);
-    const int64_t windows = ((E - 1) >> lg) + 1, windows2 = ((E - 1) >> lg2) + 1;
-    if (optional_ws(P, row_bytes + 2 * el * (size_t)std::max(windows * P.dim_z(), windows2 * P.dim_x()), st)) {
-      void *edge_rows = P.ws, *pieces = (char*)P.ws + row_bytes;
-      void* args[] = {(void*)&x_nodes,   (void*)&y_edges,  (void*)&W_edges, (void*)&gz_nodes,  (void*)&La_nodes,  (void*)&Lb_edges,
-                      (void*)&LC_edges,  (void*)&edge_rows, (void*)&Ly_edges, (void*)&LW_edges, (void*)&Lgz_nodes, (void*)&row_ptr,
-                      (void*)&col,       (void*)&V,        (void*)&pieces,  (void*)&P.row_cnt, (void*)&lg};
-      cgtp_status s = launch(k, (unsigned)(V + windows - 1), args, st);
-      if (s != CGTP_OK) return s;
-      void* sum_args[] = {(void*)&edge_rows, (void*)&Lx_nodes, (void*)&t_row_ptr, (void*)&t_perm,
-                          (void*)&V,         (void*)&pieces,   (void*)&P.row_cnt, (void*)&lg2};
-      return launch(P.k_row_sums, (unsigned)(V + windows2 - 1), sum_args, st);
-    }
+  const DoubleWalk d = double_walk(P, V, E);
+  cgtp_status s = ensure_ws(P, d.ws);
+  if (s != CGTP_OK) return s;
+  const bool fits = d.rows && d.one <= d.ws;
+  if (scratch && d.rows && !fits && scratch_bytes < d.one)
+    return fail(CGTP_EINVAL, "scratch of " + std::to_string(scratch_bytes) + " bytes, " + std::to_string(d.one) + " needed");
+  if (fits || (scratch && d.rows)) {
+    void *edge_rows = fits ? P.ws : scratch, *pieces = (char*)edge_rows + d.row_bytes;
+    void* args[] = {(void*)&x_nodes,   (void*)&y_edges,  (void*)&W_edges, (void*)&gz_nodes,  (void*)&La_nodes,  (void*)&Lb_edges,
+                    (void*)&LC_edges,  (void*)&edge_rows, (void*)&Ly_edges, (void*)&LW_edges, (void*)&Lgz_nodes, (void*)&row_ptr,
+                    (void*)&col,       (void*)&V,        (void*)&pieces,  (void*)&P.row_cnt, (void*)&d.lg};
+    s = launch(*d.rows, (unsigned)(V + cgtp::row_windows(d.lg, E) - 1), args, st);
+    if (s != CGTP_OK) return s;
+    void* sum_args[] = {(void*)&edge_rows, (void*)&Lx_nodes, (void*)&t_row_ptr, (void*)&t_perm,
+                        (void*)&V,         (void*)&pieces,   (void*)&P.row_cnt, (void*)&d.lg2};
+    return launch(P.k_row_sums, (unsigned)(V + cgtp::row_windows(d.lg2, E) - 1), sum_args, st);
   }
   const int spwf = P.map[CGTP_K_CONV_DBL_FWD].spw, spwb = P.map[CGTP_K_CONV_DBL_BWD].spw;
-  int64_t nf = conv_ranges(P, kf, spwf, E);
-  int64_t nb = conv_ranges(P, kb, spwb, E);
-  // the two walks run one after the other on the stream and share the side buffer
-  size_t part_f = (size_t)nf * 2 * P.dim_z() * P.elt();
-  size_t part_b = round_up((size_t)nb * 2 * P.dim_x() * P.elt(), 256);
-  cgtp_status s = ensure_ws(P, std::max(part_f, part_b + (size_t)E * 8));
-  if (s != CGTP_OK) return s;
+  const int64_t nf = d.nf, nb = d.nb;
   void* part = P.ws;
   {
     const int wpw = kf.wg / 64;
@@ -1181,7 +1196,7 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
     s = launch_fixup(P, Lgz_nodes, part, row_ptr, V, E, nf, P.dim_z(), st);
     if (s != CGTP_OK) return s;
   }
-  int64_t* t_recv = (int64_t*)((char*)P.ws + part_b);
+  int64_t* t_recv = (int64_t*)((char*)P.ws + d.part_b);
   HIP_TRY(cgtp::launch_recv_of_tperm(row_ptr, t_perm, V, E, t_recv, st));
   {
     const int wpw = kb.wg / 64;
@@ -1193,6 +1208,21 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
     if (s != CGTP_OK) return s;
     return launch_fixup(P, Lx_nodes, part, t_row_ptr, V, E, nb, P.dim_x(), st);
   }
+}
+
+cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,
+                                 const void* gz_nodes, const void* La_nodes, const void* Lb_edges,
+                                 const void* LC_edges, void* Lx_nodes, void* Ly_edges, void* LW_edges,
+                                 void* Lgz_nodes, int64_t V, int64_t E, const int64_t* row_ptr, const int64_t* col,
+                                 const int64_t* t_row_ptr, const int64_t* t_perm, void* hip_stream) {
+  return conv_double_backward_ws(plan, x_nodes, y_edges, W_edges, gz_nodes, La_nodes, Lb_edges, LC_edges, Lx_nodes, Ly_edges, LW_edges,
+                                 Lgz_nodes, V, E, row_ptr, col, t_row_ptr, t_perm, nullptr, 0, hip_stream);
+}
+
+size_t cgtp_conv_double_workspace_bytes(const cgtp_plan* plan, int64_t V, int64_t E) {
+  if (!plan || plan->P.mode != CGTP_UVU || V <= 0 || E <= 0 || !plan->P.k[CGTP_K_CONV_DBL_BWD].fn) return 0;
+  const DoubleWalk d = double_walk(plan->P, V, E);
+  return d.rows && d.one > d.ws ? d.one : 0;
 }
 
 cgtp_status conv_forward_atomic(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,

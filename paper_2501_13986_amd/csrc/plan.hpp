@@ -106,7 +106,6 @@ struct Plan {
   // workspace for split-row partial sums and per-edge receiver ids (conv)
   void* ws = nullptr;
   size_t ws_bytes = 0;
-  size_t ws_refused = SIZE_MAX;   // the smallest optional workspace that could not be allocated
 
   int64_t dim_x() const { return offx.back(); }
   int64_t dim_y() const { return offy.back(); }

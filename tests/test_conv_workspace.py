@@ -43,11 +43,13 @@ def test_reserved_pieces_hold_every_form_and_never_fall(exe, plan):
     out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")[:-1]
     assert len(out) == len(edges)
     before, falls = 0, 0
-    windows = 0
+    windows = most = 0
     for E, line in zip(edges, out):
         reserved, ranges, *rows = map(int, line.split())
         assert reserved >= max(ranges, *rows), (E, line)
         assert reserved >= before, (E, reserved, before)
+        assert ranges >= most, (E, ranges, most)      # all that the two walks of the second-order pass reserve by
+        most = ranges
         assert all(2 * r <= 2 * 2 * 1024 and r * plan[4] <= 32 << 20 for r in rows), (E, line)
         falls += rows[0] < windows
         before, windows = reserved, rows[0]

@@ -91,3 +91,64 @@ def test_conv_double_backward_is_deterministic_and_handles_empty_graphs():
                                   V, 0, zero_ptr.data_ptr(), zero_ptr.data_ptr(), zero_ptr.data_ptr(), zero_ptr.data_ptr(), None) == 0
     torch.cuda.synchronize()
     assert float(Lx.abs().max()) == 0.0 and float(Lgz.abs().max()) == 0.0
+
+
+def test_one_walk_in_the_callers_scratch_and_two_without(monkeypatch):
+    """A graph whose edges' rows do not fit the plan's workspace (30 000 rows of 512 words): one walk in memory that is torch's
+    again after the call, two walks where torch has none left or through the entry point without scratch; either way the same
+    bits every time, and scratch that is too small or misaligned is refused."""
+    from paper_2501_13986_amd import binding as b
+    plan = b.Plan("128x0e+128x1o", "1x0e+1x1o", "128x0e+128x1o", dtype=b.CGTP_F32, device=0)
+    V, E = 200, 30000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    rnd = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    recv, send = (torch.randint(0, V, (E,), generator=g, device="cuda") for _ in range(2))
+    row_ptr, col, _, t_row_ptr, t_perm = b.cgtp_csr_from_coo(recv, send, V)
+    DX, DY, DZ, NW = plan.dim_x, plan.dim_y, plan.dim_z, plan.n_w
+    ins = [rnd(V, DX), rnd(E, DY), rnd(E, NW), rnd(V, DZ), rnd(V, DX), rnd(E, DY), rnd(E, NW)]
+    shapes = ((V, DX), (E, DY), (E, NW), (V, DZ))
+    L = b.lib()
+    need = L.cgtp_conv_double_workspace_bytes(plan._h, V, E)
+    print(f"V={V} E={E} scratch={need} entry=conv_double_backward/conv_double_backward_ws", flush=True)
+    assert need >= E * DX * 4
+
+    def run(call):
+        outs = [torch.full(s, float("nan"), device="cuda") for s in shapes]
+        torch.cuda.synchronize()
+        call(outs)
+        torch.cuda.synchronize()
+        return outs
+
+    def binding(outs):
+        before = torch.cuda.memory_allocated()
+        b.conv_double_backward(plan, *ins, *outs, row_ptr, col, t_row_ptr, t_perm)
+        assert torch.cuda.memory_allocated() == before
+
+    def c_call(name, *scratch):
+        return lambda outs: getattr(L, name)(plan._h, *(t.data_ptr() for t in ins + outs), V, E, *(t.data_ptr() for t in (row_ptr, col, t_row_ptr, t_perm)),
+                                             *scratch, torch.cuda.current_stream().cuda_stream)
+    run(lambda outs: None)                            # (torch's own memory for the outputs)
+    free = torch.cuda.mem_get_info()[0]
+    two = run(c_call("conv_double_backward"))
+    assert free - torch.cuda.mem_get_info()[0] < need      # kept with the plan: two rows of 2 KB for each of at most 8 192 waves
+    one = run(binding)
+    own = torch.empty(need + 256, dtype=torch.uint8, device="cuda")
+    given = run(c_call("conv_double_backward_ws", own.data_ptr(), need))
+    no_scratch = run(c_call("conv_double_backward_ws", None, 0))
+    with monkeypatch.context() as m:
+        def refuse(*a, **k):
+            raise torch.cuda.OutOfMemoryError("none left")
+        m.setattr(torch, "empty", refuse)
+        refused = [torch.full(s, float("nan"), device="cuda") for s in shapes]
+        b.conv_double_backward(plan, *ins, *refused, row_ptr, col, t_row_ptr, t_perm)
+        torch.cuda.synchronize()
+    again = run(binding)
+    for k in range(4):
+        assert torch.equal(one[k], given[k]) and torch.equal(one[k], again[k])
+        assert torch.equal(two[k], no_scratch[k]) and torch.equal(two[k], refused[k])
+        # fp32 sums of about 150 edges and 128 channels in two orders: 2^-24 sqrt(128 * 150 * terms) < 2e-5 of the norm
+        assert float((one[k] - two[k]).norm()) <= 2e-5 * float(two[k].norm())
+    outs = [torch.empty(s, device="cuda") for s in shapes]
+    for bad in ((own.data_ptr(), need - 1), (own.data_ptr() + 16, need)):
+        assert c_call("conv_double_backward_ws", *bad)(outs) == 1
