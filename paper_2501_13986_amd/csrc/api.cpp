@@ -368,30 +368,21 @@ size_t piece_bytes(const Plan& P, bool backward, int64_t E) {
 // A launch holds fewer than 2^32 work-items.
 bool rows_launch(const Kernel& k, int64_t V) { return k.fn && V < ((int64_t)1 << 32) / k.wg - cgtp::kRowWindows; }
 
+int64_t resident_groups(const Plan& P, const Kernel& k) { return (int64_t)k.blocks_per_cu * P.num_cu; }
+
 // The kernel that walks a graph row by row, or NULL if the edge ranges do.  Non-temporal streams where the weights do not
 // fit the Infinity Cache (128 channels, 300 nodes of degree 32, forward 25 us without the hint and 27 with it; 5 000 nodes 308
-// and 300).  The forward has gained at every size measured.  The backward, whose weights come in the order of the senders, does
-//  - where several workers' weights share a cache line (4 channels, 20 000 nodes of degree 32, 178 -> 97 us);
-//  - for short streams: one launch instead of three.  The limit is where the last workgroups leave the machine idle for as long:
-//    64 channels fp64, 1 500 nodes of degree 36, 104 us by ranges, 112 by rows; where workers share waves, 32 channels, 3 000
-//    nodes of degree 18, 77 and 66, of degree 36, 134 and 135; with more than 128 registers, so one workgroup of eight waves a CU,
-//    32 channels fp64, 800 of degree 18, 52 and 44, of degree 36, 81 and 87; 128 channels, 300 of degree 9, 31 and 28, of degree
-//    18, 38 and 40;
-//  - for many rows, when the workgroups of fewer waves come in three rounds or more: 96 channels fp64, 5 000 nodes of
-//    degree 9, 138 -> 129, fp32 3 000 of degree 36 160 and 162, 5 000 255 and 250; 128 channels, 3 000 of degree 18, 227 -> 224
-//    (2 000 of degree 32 261 -> 266).  One fp64 channel a lane needs four rounds and rows worth the workgroup: 32 channels, 5 000 of degree
-//    36, 396 -> 409, 12 000 931 -> 912; 48 channels, 20 000 of degree 9, 273 -> 293, of degree 36, 1029 -> 1013.
+// and 300).
 const Kernel* conv_by_rows(const Plan& P, bool backward, int64_t V, int64_t E) {
   const LaneMap& m = P.map[backward ? CGTP_K_CONV_BWD : CGTP_K_CONV_FWD];
-  const int64_t stream = E * P.n_w * (int64_t)P.elt(), mb = (int64_t)1 << 20;
+  const int64_t stream = E * P.n_w * (int64_t)P.elt();
   const Kernel &plain = P.k_row[backward][0], &nt = P.k_row[backward][1];
   if (!rows_launch(plain, V) || !rows_launch(nt, V)) return nullptr;
-  if (!backward || m.G * m.cpl * (int64_t)P.elt() < 128) return stream > 256 * mb ? &nt : &plain;
-  const int64_t few = plain.vgprs > 128 ? (m.cpl > 1 ? 40 : 72) : m.spw > 1 ? 144 : 96;
-  if (stream <= few * mb) return &plain;
-  const int64_t resident = (int64_t)nt.blocks_per_cu * P.num_cu;
-  if (P.dtype == CGTP_F64 && m.cpl == 1 ? V >= 4 * resident && E >= 16 * V : V >= 3 * resident) return &nt;
-  return nullptr;
+  const bool few_channels = m.G * m.cpl * (int64_t)P.elt() < 128;
+  if (!backward) return !few_channels && !cgtp::forward_by_rows(V, E) ? nullptr : stream > (int64_t)256 << 20 ? &nt : &plain;
+  const cgtp::BackwardRows k{few_channels, P.dtype == CGTP_F64, m.cpl, m.spw, plain.vgprs > 128, resident_groups(P, plain), resident_groups(P, nt)};
+  const int form = cgtp::backward_by_rows(k, V, E, stream);
+  return form == 0 ? nullptr : form == 2 ? &nt : &plain;
 }
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -423,6 +414,9 @@ DoubleWalk double_walk(const Plan& P, int64_t V, int64_t E) {
   while (receivers < (size_t)E) receivers *= 2;
   d.part_b = round_up((size_t)d.nb * 2 * P.dim_x() * el, 256);
   d.ws = std::max((size_t)d.nf * 2 * P.dim_z() * el, d.part_b + receivers * 8);
+  const LaneMap& m = P.map[CGTP_K_CONV_DBL_BWD];
+  const bool few_channels = m.G * m.cpl * (int64_t)el < 128;
+  if (!few_channels && !cgtp::double_by_rows(V, E, resident_groups(P, P.k_dbl_row[1]))) return d;
   if (!rows_launch(P.k_dbl_row[0], V) || !rows_launch(P.k_row_sums, V) || (size_t)E > ((size_t)4 << 30) / (P.dim_x() * el)) return d;
   d.row_bytes = round_up((size_t)E * P.dim_x() * el, 256);
   d.rows = &P.k_dbl_row[V <= 768 ? 0 : 3 * E * P.n_w * (int64_t)el > (int64_t)256 << 20 ? 2 : 1];

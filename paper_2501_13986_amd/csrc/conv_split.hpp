@@ -47,4 +47,50 @@ inline int64_t most_pieces(int64_t all, int spw, std::initializer_list<int64_t> 
   return 2 * most;
 }
 
+// Which convolutions go row by row (a workgroup per row) and which by edge ranges.  V rows, E edges, `resident`: workgroups
+// that the machine holds at once.
+//
+// Forward and second order: by rows, but for many rows of a few edges each, most of whose workgroup is idle.  (Rows without an
+// edge cost little again.)  us, ranges -> rows.  Forward, 128 channels, 20 000 nodes: degree 0.1 82 -> 54, 0.5 84 -> 98, 1
+// 96 -> 128, 2 130 -> 158, 4 210 -> 212, 7 328 -> 298; 9 000 nodes of degree 2 71 -> 69; 96 channels, 20 000 of
+// degree 4 83 -> 90; 32 channels fp64, 20 000 of degree 2 80 -> 110, 9 000 52 -> 43.
+// Second order, 128 channels (512 resident), 9 000 nodes: degree 1 162 -> 185, 4 422 -> 380; 20 000 of degree 0.1 160 -> 138, 0.25
+// 169 -> 196; 5 000 of degree 1 101 -> 103; 32 channels (1 024 resident), 20 000 nodes: degree 1 110 -> 134, 2 163 -> 190, 4 269 -> 266;
+// 9 000 of degree 1 73 -> 59.
+inline bool forward_by_rows(int64_t V, int64_t E) { return V <= 10000 || E / 5 >= V || E <= V / 8; }
+inline bool double_by_rows(int64_t V, int64_t E, int64_t resident) { return V <= 10 * resident || E / 4 >= V || E <= V / 8; }
+
+// The backward, whose weights come in the order of the senders: 0 by ranges, 1 by rows, 2 by rows with non-temporal streams.
+//  - Where several workers' weights share a cache line (`few_channels`: 4 channels, 20 000 nodes of degree 32, 178 -> 97 us; degree
+//    0.5 22 -> 16): rows.
+//  - For short streams: one launch instead of three.  The limit is where the last workgroups leave the machine idle for as long:
+//    64 channels fp64, 1 500 nodes of degree 36, 104 us by ranges, 112 by rows; where workers share waves, 32 channels, 3 000
+//    nodes of degree 18, 77 and 66, of degree 36, 134 and 135, 9 000 of degree 7 94 and 103; with more than 128 registers, so one
+//    workgroup of eight waves a CU, 32 channels fp64, 800 of degree 18, 52 and 44, of degree 36, 81 and 87; 128 channels, 300 of
+//    degree 9, 31 and 28, of degree 18, 38 and 40.
+//    Rows of fewer than six edges leave waves idle: by rows only as many of them as the launches cost.  128 channels (256
+//    resident), 400 nodes of degree 3 27 -> 23, 800 32 -> 36, of degree 1 20 -> 26; 32 channels fp64 (512), 800 of degree 1 20 -> 18,
+//    1 500 21 -> 26, 5 000 of degree 3 60 -> 76; 96 channels (512), 1 500 of degree 1 18 -> 18.5, 5 000 32 -> 40, 9 000 of degree 4
+//    77 -> 93, but 3 300 of degree 6 48 -> 45; 32 channels (1 024), 5 000 of degree 1 32 -> 30, 9 000 39 -> 45.
+//  - For many rows, when the workgroups of fewer waves come in three rounds or more: 96 channels fp64, 5 000 nodes of
+//    degree 9, 138 -> 129, fp32 3 000 of degree 36 160 and 162, 5 000 255 and 250; 128 channels, 3 000 of degree 18, 227 -> 224
+//    (2 000 of degree 32 261 -> 266).  One fp64 channel a lane needs four rounds and rows worth the workgroup: 32 channels, 5 000 of degree
+//    36, 396 -> 409, 12 000 931 -> 912; 48 channels, 20 000 of degree 9, 273 -> 293, of degree 36, 1029 -> 1013.  The others six edges a
+//    row: 128 channels, 20 000 nodes of degree 1 132 -> 182, 4 374 -> 380, 7 598 -> 594.
+struct BackwardRows {
+  bool few_channels, f64;
+  int cpl, spw;                          // channels per lane, workers per wave
+  bool many_registers;                   // more than 128
+  int64_t resident, resident_nt;         // of the plain and of the non-temporal kernel
+};
+inline int backward_by_rows(const BackwardRows& k, int64_t V, int64_t E, int64_t stream_bytes) {
+  const int64_t mb = (int64_t)1 << 20;
+  if (k.few_channels) return stream_bytes > 256 * mb ? 2 : 1;
+  const int64_t few = k.many_registers ? (k.cpl > 1 ? 40 : 72) : k.spw > 1 ? 120 : 96;
+  const bool filled = E / 6 >= V;
+  if (stream_bytes <= few * mb) return filled || V <= (k.many_registers ? 2 : k.spw > 1 ? 5 : 3) * k.resident;
+  const bool many = k.f64 && k.cpl == 1 ? V >= 4 * k.resident_nt && E / 16 >= V : V >= 3 * k.resident_nt && filled;
+  return many ? 2 : 0;
+}
+
 }  // namespace cgtp
