@@ -187,9 +187,12 @@ cgtp_status tp_double_backward(cgtp_plan* plan, const void* x, const void* y, co
 
 /* z_nodes[j] = sum over CSR row j of TP(P, x_nodes[col[e]], y_edges[e], W_edges[e]).
  * x_nodes [V,dim_x], y_edges [E,dim_y], W_edges [E,n_w], z_nodes [V,dim_z]; row_ptr [V+1] and
- * col [E] are int64 device arrays.  Deterministic: no atomics, run-to-run bit-identical.
+ * col [E] are int64 device arrays.  Deterministic: run-to-run bit-identical (no sum is formed by atomics; the pieces of
+ * long rows are counted by them, and added in order by the workgroup that finishes last).
  * Uses a plan-owned workspace that grows on demand (hipMalloc on the first call and when
- * a larger problem arrives); calls on one plan must not overlap.  uvu plans only. */
+ * a larger problem arrives, never on a smaller one), and plan-owned counters.  Calls on one plan must not overlap,
+ * conv_forward_static included: overlapping calls spoil each other's results, and, where one of them is a replay of a
+ * captured graph, may spoil later replays of the same graph until another convolution has run on the plan.  uvu plans only. */
 cgtp_status conv_forward(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,
                          void* z_nodes, int64_t V, int64_t E, const int64_t* row_ptr, const int64_t* col,
                          void* hip_stream);
@@ -202,7 +205,8 @@ cgtp_status conv_forward(cgtp_plan* plan, const void* x_nodes, const void* y_edg
  * counts as min(E, workers of the range kernel resident on the GPU), also where fewer or none are used; CGTP_EINVAL with the figures in cgtp_last_error() if that
  * exceeds the array (the MACE-shaped benchmark plan needs exactly 32 MiB in either precision).  The plan's device
  * must be the current device.  All calls on one GPU share the array: calls that overlap in time on one GPU (different
- * streams, different plans, different threads) race; calls on one stream are ordered and safe. */
+ * streams, different plans, different threads) race, as do calls that overlap any other convolution on the same plan;
+ * calls on one stream are ordered and safe. */
 cgtp_status conv_forward_static(cgtp_plan* plan, const void* x_nodes, const void* y_edges, const void* W_edges,
                                 void* z_nodes, int64_t V, int64_t E, const int64_t* row_ptr, const int64_t* col,
                                 void* hip_stream);

@@ -721,9 +721,9 @@ cgtp_status cgtp_plan_create_ex(const char* irreps_x, const char* irreps_y, cons
     (void)hipGetLastError();
   }
   if (P.k_row[0][0].fn || P.k_row[1][0].fn || P.k_dbl_row[0].fn) {
-    const size_t n = cgtp::kRowWindows * sizeof(int);
+    const size_t n = cgtp::kRowWindows * sizeof(*P.row_cnt);
     hipError_t e = hipMalloc((void**)&P.row_cnt, n);
-    if (e == hipSuccess) e = hipMemset(P.row_cnt, 0, n);
+    if (e == hipSuccess) e = hipMemset(P.row_cnt, cgtp::env_int("CGTP_ROW_CNT_FILL", 0), n);   // (tests: counts left behind)
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
       cgtp_plan_destroy(H.release());
@@ -1041,8 +1041,9 @@ cgtp_status conv_forward_impl(cgtp_plan* plan, const void* x_nodes, const void* 
     part = P.ws;
   }
   if (rows) {
+    ++P.row_call;
     void* args[] = {(void*)&x_nodes, (void*)&y_edges, (void*)&W_edges,   (void*)&z_nodes, (void*)&row_ptr, (void*)&col,
-                    (void*)&V,       (void*)&part,    (void*)&P.row_cnt, (void*)&lg,      (void*)&edge_perm};
+                    (void*)&V,       (void*)&part,    (void*)&P.row_cnt, (void*)&P.row_call, (void*)&lg, (void*)&edge_perm};
     return launch(*rows, (unsigned)(V + nchunk - 1), args, st);
   }
   const int wpw = k.wg / 64;
@@ -1113,9 +1114,10 @@ cgtp_status conv_backward_perm(cgtp_plan* plan, const void* x_nodes, const void*
     const int lg = row_lg(*rows, spw, E, P.dim_x() * (int64_t)P.elt());
     if (V > cgtp::kConvRowLookup || E > INT32_MAX) HIP_TRY(cgtp::launch_recv_of_tperm(row_ptr, t_perm, V, E, t_recv, st));
     else t_recv = nullptr;   // the kernel looks them up (2 000 nodes: 30 us either way)
+    ++P.row_call;
     void* args[] = {(void*)&x_nodes,  (void*)&y_edges,   (void*)&W_edges, (void*)&gz_nodes,  (void*)&gx_nodes, (void*)&gy_edges,
                     (void*)&gW_edges, (void*)&t_row_ptr, (void*)&t_perm,  (void*)&row_ptr,   (void*)&t_recv,   (void*)&V,
-                    (void*)&part,     (void*)&P.row_cnt, (void*)&lg,      (void*)&edge_perm};
+                    (void*)&part,     (void*)&P.row_cnt, (void*)&P.row_call, (void*)&lg,     (void*)&edge_perm};
     return launch(*rows, (unsigned)(V + cgtp::row_windows(lg, E) - 1), args, st);
   }
   int64_t nchunk = conv_ranges(P, k, spw, E);
@@ -1166,14 +1168,16 @@ cgtp_status conv_double_backward_ws(cgtp_plan* plan, const void* x_nodes, const 
   if (scratch && d.rows && !fits && scratch_bytes < d.one)
     return fail(CGTP_EINVAL, "scratch of " + std::to_string(scratch_bytes) + " bytes, " + std::to_string(d.one) + " needed");
   if (fits || (scratch && d.rows)) {
+    ++P.row_call;
     void *edge_rows = fits ? P.ws : scratch, *pieces = (char*)edge_rows + d.row_bytes;
     void* args[] = {(void*)&x_nodes,   (void*)&y_edges,  (void*)&W_edges, (void*)&gz_nodes,  (void*)&La_nodes,  (void*)&Lb_edges,
                     (void*)&LC_edges,  (void*)&edge_rows, (void*)&Ly_edges, (void*)&LW_edges, (void*)&Lgz_nodes, (void*)&row_ptr,
-                    (void*)&col,       (void*)&V,        (void*)&pieces,  (void*)&P.row_cnt, (void*)&d.lg};
+                    (void*)&col,       (void*)&V,        (void*)&pieces,  (void*)&P.row_cnt, (void*)&P.row_call, (void*)&d.lg};
     s = launch(*d.rows, (unsigned)(V + cgtp::row_windows(d.lg, E) - 1), args, st);
     if (s != CGTP_OK) return s;
+    ++P.row_call;
     void* sum_args[] = {(void*)&edge_rows, (void*)&Lx_nodes, (void*)&t_row_ptr, (void*)&t_perm,
-                        (void*)&V,         (void*)&pieces,   (void*)&P.row_cnt, (void*)&d.lg2};
+                        (void*)&V,         (void*)&pieces,   (void*)&P.row_cnt, (void*)&P.row_call, (void*)&d.lg2};
     return launch(P.k_row_sums, (unsigned)(V + cgtp::row_windows(d.lg2, E) - 1), sum_args, st);
   }
   const int spwf = P.map[CGTP_K_CONV_DBL_FWD].spw, spwb = P.map[CGTP_K_CONV_DBL_BWD].spw;

@@ -1667,6 +1667,8 @@ static void row_of_workgroup(Em& E, const char* ptr) {
 // word `before`.
 static void sum_of_workers(Em& E, int D, int wg) {
   auto& o = E.o;
+  // A counter holds the number of its call above its count, so that what an earlier call left behind (none does, unless calls on
+  // one plan overlap, which is not allowed) is no count of this one.  The loop has one lane and ends when that has added.
   o << "  T* dst = hub ? part + slot * " << D << " : out + r * " << D << ";\n";
   const int per = (D + wg - 1) / wg;
   o << "  {\n    T s_[" << per << "]; int i_[" << per << "];\n    #pragma unroll\n    for (int k = 0; k < " << per << "; ++k) { i_[k] = k * " << wg
@@ -1676,14 +1678,17 @@ static void sum_of_workers(Em& E, int D, int wg) {
   o << "  if (!hub) return;\n"
        "  __builtin_amdgcn_fence(__ATOMIC_RELEASE, \"agent\");\n  __syncthreads();\n"
        "  const i64 h0 = rb >> lg, pieces = ((re - 1) >> lg) - h0 + 1;\n"
-       "  if (t == 0) before = __hip_atomic_fetch_add(cnt + h0, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);\n"
+       "  if (t == 0) {\n    unsigned long long have = __hip_atomic_load(cnt + h0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), want;\n    int done;\n    do {\n"
+       "      want = ((unsigned)(have >> 32) == call ? have : (unsigned long long)call << 32) + 1;\n"
+       "      done = __hip_atomic_compare_exchange_strong(cnt + h0, &have, want, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n"
+       "    } while (!__builtin_amdgcn_readfirstlane(done));\n    before = (int)(unsigned)want - 1;\n  }\n"
        "  __syncthreads();\n"
        "  if (__builtin_amdgcn_readfirstlane(before) != (int)pieces - 1) return;\n"
        "  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, \"agent\");\n";
   o << "  #pragma unroll 1\n  for (int k = 0; k < " << per << "; ++k) {\n    const int i_ = k * " << wg << " + t < " << D << " ? k * " << wg << " + t : " << D - 1
     << ";\n    T s_ = part[(2 * h0 + 1) * " << D << " + i_];\n    #pragma unroll 8\n    for (i64 h = h0 + 1; h < h0 + pieces; ++h) s_ += part[2 * h * " << D << " + i_];\n"
        "    out[r * " << D << " + i_] = s_;\n  }\n"
-       "  if (t == 0) __hip_atomic_store(cnt + h0, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n";
+       "  if (t == 0) __hip_atomic_store(cnt + h0, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n";
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1723,7 +1728,7 @@ bool emit_uvu_conv_row(const Plan& P, bool backward, bool nt, int waves, Kernel&
          "   const i64* __restrict__ t_row_ptr, const i64* __restrict__ t_perm, const i64* __restrict__ row_ptr, const i64* __restrict__ t_recv,";
   else
     o << "T* __restrict__ out,\n   const i64* __restrict__ row_ptr, const i64* __restrict__ col,";
-  o << " i64 V, T* part, int* cnt, int lg, const i64* __restrict__ eperm)\n{\n";
+  o << " i64 V, T* part, unsigned long long* cnt, unsigned call, int lg, const i64* __restrict__ eperm)\n{\n";
   o << "  __shared__ __attribute__((aligned(16))) T red[" << (int64_t)NWK * D << "];\n";
   if (backward) o << "  __shared__ int rp[" << kConvRowLookup + 1 << "], lj[" << K.wg << "];\n  __shared__ i64 le[" << K.wg << "];\n";
   o << "  __shared__ int before;\n";
@@ -1814,7 +1819,7 @@ bool emit_uvu_conv_double_row(const Plan& P, bool nt, int waves, Kernel& K) {
   o << "extern \"C\" __global__ void __launch_bounds__(" << K.wg << ") " << occ_attr(M, K.sched) << K.name
     << "(const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ W, const T* __restrict__ gz,\n"
        "   const T* __restrict__ La, const T* __restrict__ Lb, const T* __restrict__ LC, T* __restrict__ rows, T* __restrict__ Ly, T* __restrict__ LW,\n"
-       "   T* __restrict__ out, const i64* __restrict__ row_ptr, const i64* __restrict__ col, i64 V, T* part, int* cnt, int lg)\n{\n";
+       "   T* __restrict__ out, const i64* __restrict__ row_ptr, const i64* __restrict__ col, i64 V, T* part, unsigned long long* cnt, unsigned call, int lg)\n{\n";
   o << "  __shared__ __attribute__((aligned(16))) T red[" << (int64_t)NWK * DZ << "];\n  __shared__ int before;\n";
   o << "  const int t = threadIdx.x, lane = t & 63;\n  int vz = 0; asm volatile(\"\" : \"+v\"(vz));\n  const int g_ = lane & " << M.G - 1 << ";\n";
   if (M.spw == 1) o << "  const int wk = __builtin_amdgcn_readfirstlane(t >> 6);\n";
@@ -1872,7 +1877,7 @@ bool emit_row_sums(const Plan& P, Kernel& K) {
   E.emit_row_of();
   auto& o = E.o;
   o << "extern \"C\" __global__ void __launch_bounds__(256) " << K.name
-    << "(const T* __restrict__ rows, T* __restrict__ out, const i64* __restrict__ ptr, const i64* __restrict__ perm, i64 V, T* part, int* cnt, int lg)\n{\n"
+    << "(const T* __restrict__ rows, T* __restrict__ out, const i64* __restrict__ ptr, const i64* __restrict__ perm, i64 V, T* part, unsigned long long* cnt, unsigned call, int lg)\n{\n"
        "  __shared__ __attribute__((aligned(16))) T red[" << 4 * D << "];\n  __shared__ int before;\n"
        "  const int t = threadIdx.x, lane = t & 63, wk = __builtin_amdgcn_readfirstlane(t >> 6);\n";
   row_of_workgroup(E, "ptr");

@@ -101,7 +101,8 @@ struct Plan {
   Kernel k[9];  // indexed by cgtp_kernel
   Kernel k_row[2][2];       // convolution with a workgroup per row: [forward, backward][plain, non-temporal streams] (no source: not for this plan)
   Kernel k_dbl_row[3], k_row_sums;   // second-order pass in one walk: [few rows, many, non-temporal streams], sums of the edges' dL/dx
-  int* row_cnt = nullptr;   // their counters of finished pieces, one per window; zero between calls
+  uint64_t* row_cnt = nullptr;   // their counters of finished pieces, one per window: call << 32 | count; zero between calls
+  uint32_t row_call = 0;         // number of their launches so far
   Kernel k_fix;  // merges split rows after the conv kernels (uvu) / adds per-wave gW partial sums (uvw)
   // workspace for split-row partial sums and per-edge receiver ids (conv)
   void* ws = nullptr;

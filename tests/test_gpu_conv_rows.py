@@ -101,3 +101,12 @@ def test_second_order_pass_of_rows_of_every_length(spec_name, name, prec):
         torch.cuda.synchronize()
         for got, want, what in zip(out, ref, ("Lx", "Ly", "LW", "Lgz")):
             assert_close(got.cpu().numpy(), want, prec, what)
+
+
+@pytest.mark.parametrize("fill", [0, 1, 255])
+@pytest.mark.parametrize("spec_name", ["mul8", "mul32"])
+def test_counts_left_behind_are_none_of_the_next_call(spec_name, fill, monkeypatch):
+    """The counters of finished pieces as calls that overlapped (which is not allowed) would leave them: later calls are right."""
+    monkeypatch.setenv("CGTP_ROW_CNT_FILL", str(fill))
+    test_rows_of_every_length(spec_name, "hubs", "f32")
+    test_second_order_pass_of_rows_of_every_length(spec_name, "hubs", "f32")
