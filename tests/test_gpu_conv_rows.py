@@ -7,6 +7,7 @@ from oracle import conv as oconv
 from oracle.irreps import TPSpec
 from paper_2501_13986_amd import synth
 from tests._util import assert_close, memo
+from tests import test_gpu_conv as conv_tests
 from tests.test_gpu_conv import SPECS, dev
 from tests.test_gpu_conv_shapes import check
 
@@ -80,6 +81,13 @@ def test_edge_ranges_of_small_graphs(spec_name, name, prec, monkeypatch):
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("name", ["typical", "few_long_rows", "many_empty", "hub"])
+def test_edge_ranges_of_two_workers_a_wave_through_the_permutation(name, prec, monkeypatch):
+    monkeypatch.setenv("CGTP_CONV_ROWS", "0")
+    conv_tests.test_conv_on_unsorted_edge_data_through_the_edge_permutation("mul32", name, prec)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
 @pytest.mark.parametrize("name", list(DEGREES))
 @pytest.mark.parametrize("spec_name", ["small", "odd_row", "mul8", "mul20", "mul32", "mul75", "mul96"])
 def test_second_order_pass_of_rows_of_every_length(spec_name, name, prec):
@@ -110,3 +118,60 @@ def test_counts_left_behind_are_none_of_the_next_call(spec_name, fill, monkeypat
     monkeypatch.setenv("CGTP_ROW_CNT_FILL", str(fill))
     test_rows_of_every_length(spec_name, "hubs", "f32")
     test_second_order_pass_of_rows_of_every_length(spec_name, "hubs", "f32")
+
+
+# degrees of the ordinary rows, then of a few long ones.  Rows above 2 048 take their receivers from memory, above 768 the
+# second-order kernel of fewer waves; 140 000 edges are more than 1 024 of the smallest windows; with 340 000 edges the weights
+# exceed the Infinity Cache (non-temporal streams) and 8 000 rows come in three rounds of workgroups or more
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("spec_name,V,degree,hubs", [("small", 2100, 3, (600, 1500, 257)), ("mul32", 2100, 3, (600, 1500, 257)), ("mul32", 1000, 5, (1200,)),
+                                                     ("mul8", 900, 40, (70000, 30000)), ("small", 900, 40, (70000, 200000)),
+                                                     ("mul32", 8000, 40, (20000, 600)), ("mul96", 8000, 12, (20000, 600))])
+def test_long_rows_in_every_kind_of_row_kernel(spec_name, V, degree, hubs, prec, monkeypatch):
+    """Against the walks by edge ranges in fp64 (which the oracle checks on smaller graphs), on graphs too large for the oracle."""
+    from paper_2501_13986_amd import binding as b
+    f64 = b.CGTP_F64
+    plan = b.Plan(*SPECS[spec_name], dtype=f64 if prec == "f64" else b.CGTP_F32, device=0)
+    with monkeypatch.context() as m:
+        m.setenv("CGTP_CONV_ROWS", "0")
+        ranges = b.Plan(*SPECS[spec_name], dtype=f64, device=0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V + degree)
+    deg = torch.full((V,), degree, device="cuda", dtype=torch.int64)
+    for k, d in enumerate(hubs):
+        deg[(k * V) // len(hubs) + 5] = d
+    recv = torch.repeat_interleave(torch.arange(V, device="cuda"), deg)
+    E = recv.shape[0]
+    order = lambda: torch.randperm(E, generator=g, device="cuda")
+    recv, send = recv[order()], recv[order()]
+    print(f"spec={spec_name} V={V} E={E} prec={prec} entry=conv_forward/conv_backward/conv_double_backward(_perm)", flush=True)
+    row_ptr, col, perm, t_row_ptr, t_perm = b.cgtp_csr_from_coo(recv, send, V)
+    dims = [plan.dim_x, plan.dim_y, plan.n_w, plan.dim_z, plan.dim_x, plan.dim_y, plan.n_w]
+    ins = [torch.randn((V if k in (0, 3, 4) else E, d), generator=g, device="cuda") for k, d in enumerate(dims)]
+
+    def run(p, dt, x, y, W, gz, La, Lb, LC):
+        new = lambda *shape: torch.full(shape, float("nan"), dtype=dt, device="cuda")
+        x, y, W, gz, La, Lb, LC = (t.to(dt) for t in (x, y, W, gz, La, Lb, LC))
+        out = {"z": new(V, p.dim_z), "gx": torch.empty_like(x), "gy": torch.empty_like(y), "gW": torch.empty_like(W), "zp": new(V, p.dim_z),
+               "gxp": torch.empty_like(x), "gyp": torch.empty_like(y), "gWp": torch.empty_like(W), "Lx": torch.empty_like(x),
+               "Ly": torch.empty_like(y), "LW": torch.empty_like(W), "Lgz": new(V, p.dim_z)}
+        for t in out.values():
+            t.fill_(float("nan"))
+        o = list(out.values())
+        b.conv_forward(p, x, y, W, o[0], row_ptr, col)
+        b.conv_backward(p, x, y, W, gz, *o[1:4], row_ptr, col, t_row_ptr, t_perm)
+        b.conv_forward_perm(p, x, y, W, o[4], row_ptr, col, perm)
+        b.conv_backward_perm(p, x, y, W, gz, *o[5:8], row_ptr, col, t_row_ptr, t_perm, perm)
+        b.conv_double_backward(p, x, y, W, gz, La, Lb, LC, *o[8:], row_ptr, col, t_row_ptr, t_perm)
+        torch.cuda.synchronize()
+        return out
+
+    want = run(ranges, torch.float64, *ins)
+    for call in range(2):       # the second call finds the counters as the first one left them
+        got = run(plan, torch.float64 if prec == "f64" else torch.float32, *ins)
+        for what, ref in want.items():
+            assert bool(torch.isfinite(got[what]).all()), what
+            # as oracle comparisons: relative to the value or the root mean square, whichever is larger; sums of n terms in
+            # fp32 err by about 2^-24 sqrt(n) of their own size, 3e-5 for 200 000 edges, and only hub rows are so long
+            err = ((got[what].double() - ref).abs() / ref.abs().clamp(min=float(ref.square().mean().sqrt()))).max()
+            assert float(err) <= (1e-10 if prec == "f64" else 1e-4), (what, float(err))

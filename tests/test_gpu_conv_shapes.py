@@ -57,9 +57,11 @@ def test_lane_maps_above_one_wave(spec_name, prec):
     check(spec_name, "empty_ends", prec)
 
 
+@pytest.mark.parametrize("rows", ["0", "1"])      # 1: the same rows in windows of the row kernels
 @pytest.mark.parametrize("prec", ["f64", "f32"])
 @pytest.mark.parametrize("spec_name", ["odd_row", "mul1", "small"])
-def test_rows_split_over_thousands_of_ranges(spec_name, prec):
+def test_rows_split_over_thousands_of_ranges(spec_name, prec, rows, monkeypatch):
+    monkeypatch.setenv("CGTP_CONV_ROWS", rows)
     check(spec_name, "hub", prec, double=spec_name == "odd_row")
 
 
