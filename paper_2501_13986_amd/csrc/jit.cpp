@@ -8,7 +8,9 @@
 #include <sys/stat.h>
 #include <unistd.h>
 
+#include <climits>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <fstream>
 #include <sstream>
@@ -76,24 +78,86 @@ void write_file_atomic(const std::string& path, const std::vector<char>& data) {
   if (std::rename(tmp.c_str(), path.c_str()) != 0) std::remove(tmp.c_str());
 }
 
+// The run-time compiler.  A process that has loaded torch has torch's own hipRTC and code object manager in its global scope, of
+// the same names as the installed ones, and the linker would take those: the code of a plan would depend on what was imported
+// first (torch's clang 20 against the installed clang 22: uvw step of 100 000 rows 281 and 272 us, one uvw forward 732 and 600
+// bytes of private memory).  The installed compiler is therefore loaded into a namespace of its own; where that fails, the linked
+// one is used.  `id` names the compiler in the keys of the cache: both report one hipRTC version, so the code object manager, which
+// holds the compiler, is named by its file and size.
+struct Rtc {
+  decltype(&hiprtcCreateProgram) create = hiprtcCreateProgram;
+  decltype(&hiprtcCompileProgram) compile = hiprtcCompileProgram;
+  decltype(&hiprtcGetProgramLogSize) log_size = hiprtcGetProgramLogSize;
+  decltype(&hiprtcGetProgramLog) log = hiprtcGetProgramLog;
+  decltype(&hiprtcGetCodeSize) code_size = hiprtcGetCodeSize;
+  decltype(&hiprtcGetCode) code = hiprtcGetCode;
+  decltype(&hiprtcDestroyProgram) destroy = hiprtcDestroyProgram;
+  decltype(&hiprtcGetErrorString) error_string = hiprtcGetErrorString;
+  decltype(&hiprtcVersion) version = hiprtcVersion;
+  std::string id;
+
+  Rtc() {
+    void* manager = (void*)&amd_comgr_get_version;
+    if (env_int("CGTP_OWN_COMPILER", 1)) load(manager);
+    int major = 0, minor = 0;
+    (void)version(&major, &minor);
+    id = "hiprtc " + std::to_string(major) + "." + std::to_string(minor);
+    Dl_info info;
+    char path[PATH_MAX];
+    struct stat st;
+    if (dladdr(manager, &info) && info.dli_fname && realpath(info.dli_fname, path) && stat(path, &st) == 0)
+      id += std::string(" ") + (std::strrchr(path, '/') + 1) + " " + std::to_string((long long)st.st_size);
+  }
+
+ private:
+  template <class F>
+  static bool find(void* lib, const char* name, F& f) {
+    void* p = dlsym(lib, name);
+    if (p) f = (F)p;
+    return p != nullptr;
+  }
+  void load(void*& manager) {
+    const std::string dir = "/opt/rocm/lib/";
+    void* lib = dlmopen(LM_ID_NEWLM, (dir + "libhiprtc.so." + std::to_string(HIP_VERSION_MAJOR)).c_str(), RTLD_NOW | RTLD_LOCAL);
+    Lmid_t space;
+    if (!lib || dlinfo(lib, RTLD_DI_LMID, &space) != 0) return;
+    void* comgr = dlmopen(space, (dir + "libamd_comgr.so." + std::to_string(AMD_COMGR_INTERFACE_VERSION_MAJOR)).c_str(), RTLD_NOW | RTLD_LOCAL);
+    void* own = comgr ? dlsym(comgr, "amd_comgr_get_version") : nullptr;
+    Rtc r(*this);
+    if (!own || !find(lib, "hiprtcCreateProgram", r.create) || !find(lib, "hiprtcCompileProgram", r.compile) ||
+        !find(lib, "hiprtcGetProgramLogSize", r.log_size) || !find(lib, "hiprtcGetProgramLog", r.log) ||
+        !find(lib, "hiprtcGetCodeSize", r.code_size) || !find(lib, "hiprtcGetCode", r.code) ||
+        !find(lib, "hiprtcDestroyProgram", r.destroy) || !find(lib, "hiprtcGetErrorString", r.error_string) || !find(lib, "hiprtcVersion", r.version))
+      return;
+    *this = r;
+    manager = own;
+  }
+};
+
+const Rtc& rtc() {
+  static const Rtc* r = new Rtc;   // kept until the process ends, as the compiler's libraries are
+  return *r;
+}
+
 std::vector<char> compile(const Kernel& k) {
+  const Rtc& c = rtc();
   hiprtcProgram prog;
-  if (hiprtcCreateProgram(&prog, k.source.c_str(), (k.name + ".hip").c_str(), 0, nullptr, nullptr) != HIPRTC_SUCCESS)
+  if (c.create(&prog, k.source.c_str(), (k.name + ".hip").c_str(), 0, nullptr, nullptr) != HIPRTC_SUCCESS)
     throw std::runtime_error("hiprtcCreateProgram failed for " + k.name);
-  hiprtcResult r = hiprtcCompileProgram(prog, kNumOptions, const_cast<const char**>(kOptions));
+  hiprtcResult r = c.compile(prog, kNumOptions, const_cast<const char**>(kOptions));
   if (r != HIPRTC_SUCCESS) {
     size_t n = 0;
-    hiprtcGetProgramLogSize(prog, &n);
+    c.log_size(prog, &n);
     std::string log(n, '\0');
-    if (n) hiprtcGetProgramLog(prog, &log[0]);
-    hiprtcDestroyProgram(&prog);
-    throw std::runtime_error("hipRTC failed for " + k.name + ": " + hiprtcGetErrorString(r) + "\n" + log);
+    if (n) c.log(prog, &log[0]);
+    c.destroy(&prog);
+    throw std::runtime_error("hipRTC failed for " + k.name + ": " + c.error_string(r) + "\n" + log);
   }
   size_t n = 0;
-  hiprtcGetCodeSize(prog, &n);
+  c.code_size(prog, &n);
   std::vector<char> code(n);
-  hiprtcGetCode(prog, code.data());
-  hiprtcDestroyProgram(&prog);
+  c.code(prog, code.data());
+  c.destroy(&prog);
   return code;
 }
 
@@ -232,13 +296,11 @@ std::string jit_check_code_object(const std::string& path) {
 // device == -2: compile into the cache only.  device == -1: nothing.
 void jit_compile(Kernel& k, int device) {
   if (device == -1 || k.source.empty()) return;
-  // the key covers everything that decides the code: source, options, the run-time compiler's version and the
-  // version of the checks a code object has to pass before it is stored
+  // the key covers everything that decides the code: source, options, the run-time compiler and the version of the
+  // checks a code object has to pass before it is stored
   std::string opts;
   for (int i = 0; i < kNumOptions; ++i) opts += std::string(kOptions[i]) + " ";
-  int rtc_major = 0, rtc_minor = 0;
-  (void)hiprtcVersion(&rtc_major, &rtc_minor);
-  opts += "hiprtc " + std::to_string(rtc_major) + "." + std::to_string(rtc_minor) + " checks " + std::to_string(kCheckVersion) + " ";
+  opts += rtc().id + " checks " + std::to_string(kCheckVersion) + " ";
   char key[40];
   std::snprintf(key, sizeof key, "%016llx", (unsigned long long)fnv1a(k.source, fnv1a(opts)));
   std::string dir = cache_dir();
