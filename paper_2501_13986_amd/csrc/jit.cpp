@@ -292,10 +292,8 @@ std::string jit_check_code_object(const std::string& path) {
   return vector_instruction_under_empty_mask(disassemble(code));
 }
 
-// device >= 0: compile (or fetch from the cache) and load on that device.
-// device == -2: compile into the cache only.  device == -1: nothing.
-void jit_compile(Kernel& k, int device) {
-  if (device == -1 || k.source.empty()) return;
+// Compiles or fetches from the cache, and checks.
+static void compile_and_check(Kernel& k) {
   // the key covers everything that decides the code: source, options, the run-time compiler and the version of the
   // checks a code object has to pass before it is stored
   std::string opts;
@@ -347,8 +345,17 @@ void jit_compile(Kernel& k, int device) {
   if (v_ >= 0) k.scratch = (int)v_;
   v_ = metadata_int(code, ".group_segment_fixed_size");
   if (v_ >= 0) k.lds = (int)v_;
+  k.code = std::move(code);
+}
+
+// device >= 0: compile (or fetch from the cache) and load on that device.
+// device == -2: compile into the cache only.  device == -1: nothing.
+void jit_compile(Kernel& k, int device) {
+  if (device == -1 || k.source.empty()) return;
+  if (k.code.empty()) compile_and_check(k);
   if (device < 0) return;
-  hipError_t e = hipModuleLoadData(&k.module, code.data());
+  hipError_t e = hipModuleLoadData(&k.module, k.code.data());
+  k.code = std::vector<char>();
   if (e != hipSuccess) throw std::runtime_error("hipModuleLoadData failed for " + k.name + ": " + hipGetErrorString(e));
   e = hipModuleGetFunction(&k.fn, k.module, k.name.c_str());
   if (e != hipSuccess) throw std::runtime_error("hipModuleGetFunction failed for " + k.name + ": " + hipGetErrorString(e));

@@ -74,6 +74,7 @@ struct Schedule {
 struct Kernel {
   std::string source;
   std::string name;
+  std::vector<char> code;   // compiled and checked, until it is loaded
   hipModule_t module = nullptr;
   hipFunction_t fn = nullptr;
   int vgprs = 0, agprs = 0, sgprs = 0, lds = 0, scratch = 0;  // vgprs counts both register kinds
