@@ -168,7 +168,7 @@ def main() -> int:
         dbytes = bytes_model(kind, prec, n, V)
         dflops = n * (F_FWD if kind.endswith("fwd") else F_BWD)
         # the walk by rows or by edge ranges, whichever kernel the step runs
-        name = next((k for k in ("cgtp_" + kind + "_row", "cgtp_" + kind) if measured_traffic(k, prec)), "cgtp_" + kind)
+        name = plan(prec).conv_kernel({"conv_fwd": b.K_CONV_FWD, "conv_bwd": b.K_CONV_BWD}.get(kind, -1), V, n) or "cgtp_" + kind
         hbm_frac = dbytes / ms / 1e6 / HBM_PEAK_GBS
         alu_frac = dflops / ms / 1e9 / VALU_PEAK_TFLOPS[prec]
         if alu_frac > hbm_frac:

@@ -151,6 +151,12 @@ const char* cgtp_plan_source(const cgtp_plan* plan, int32_t kernel);
  * plan was compiled without a device).  Available once the kernel has been compiled (device >= 0 or -2). */
 cgtp_status cgtp_plan_kernel_info(const cgtp_plan* plan, int32_t kernel, int32_t info[6]);
 
+/* Name of the kernel that does the work of a convolution of E > 0 edges on V nodes: the walk by edge ranges
+ * (cgtp_conv_fwd, cgtp_conv_bwd, cgtp_conv_dbl_bwd) or by rows (cgtp_conv_fwd_row, ...; of the second-order pass: with
+ * the scratch it asks for).  kernel: CGTP_K_CONV_FWD, CGTP_K_CONV_BWD or CGTP_K_CONV_DBL_BWD.  NULL for other kernels
+ * and for plans without loaded convolution kernels. */
+const char* cgtp_plan_conv_kernel(const cgtp_plan* plan, int32_t kernel, int64_t V, int64_t E);
+
 /* ---- batched tensor product (paper Alg. 1-2) and its backward (Alg. 3) --------------- */
 
 /* z[b] = TP(P, x[b], y[b], W[b]) for b < B.  x [B,dim_x], y [B,dim_y], W [B,n_w] or [n_w]

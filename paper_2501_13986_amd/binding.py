@@ -22,7 +22,7 @@ STATUS = {0: "CGTP_OK", 1: "CGTP_EINVAL", 2: "CGTP_EUNSUPPORTED", 3: "CGTP_ECOMP
 
 EXPORTS = [
     "cgtp_plan_create", "cgtp_plan_create_ex", "cgtp_plan_destroy", "cgtp_plan_dim", "cgtp_plan_num_paths", "cgtp_plan_get_path",
-    "cgtp_plan_path_nonzeros", "cgtp_plan_flops", "cgtp_plan_source", "cgtp_plan_kernel_info",
+    "cgtp_plan_path_nonzeros", "cgtp_plan_flops", "cgtp_plan_source", "cgtp_plan_kernel_info", "cgtp_plan_conv_kernel",
     "tp_forward", "tp_backward", "tp_double_backward", "conv_forward", "conv_forward_static", "conv_backward", "conv_forward_perm", "conv_backward_perm", "conv_double_backward", "conv_double_backward_ws",
     "cgtp_conv_double_workspace_bytes", "conv_forward_atomic", "conv_backward_atomic",
     "cgtp_csr_from_coo", "cgtp_csr_from_coo_async", "cgtp_csr_workspace_bytes", "cgtp_last_error", "cgtp_check_code_object",
@@ -72,6 +72,8 @@ def lib() -> C.CDLL:
     L.cgtp_plan_source.argtypes = [vp, i32]
     L.cgtp_plan_source.restype = C.c_char_p
     L.cgtp_plan_kernel_info.argtypes = [vp, i32, C.POINTER(i32)]
+    L.cgtp_plan_conv_kernel.argtypes = [vp, i32, i64, i64]
+    L.cgtp_plan_conv_kernel.restype = C.c_char_p
     L.tp_forward.argtypes = [vp, vp, vp, vp, vp, i64, vp]
     L.tp_backward.argtypes = [vp] + [vp] * 7 + [i64, vp]
     L.tp_double_backward.argtypes = [vp] + [vp] * 11 + [i64, vp]
@@ -180,6 +182,11 @@ class Plan:
         a = (C.c_int32 * 6)()
         _check(lib().cgtp_plan_kernel_info(self._h, kernel, a))
         return dict(vgprs=a[0], sgprs=a[1], lds=a[2], scratch=a[3], wg=a[4], blocks_per_cu=a[5])
+
+    def conv_kernel(self, kernel: int, V: int, E: int) -> Optional[str]:
+        """Name of the kernel that a convolution of this size runs (kernel: K_CONV_FWD, K_CONV_BWD, K_CONV_DBL_BWD)."""
+        s = lib().cgtp_plan_conv_kernel(self._h, kernel, V, E)
+        return None if s is None else s.decode()
 
 
 def tp_forward(plan: Plan, x, y, W, z, B: Optional[int] = None):

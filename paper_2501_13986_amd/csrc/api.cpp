@@ -1217,6 +1217,15 @@ cgtp_status conv_double_backward(cgtp_plan* plan, const void* x_nodes, const voi
                                  Lgz_nodes, V, E, row_ptr, col, t_row_ptr, t_perm, nullptr, 0, hip_stream);
 }
 
+const char* cgtp_plan_conv_kernel(const cgtp_plan* plan, int32_t kernel, int64_t V, int64_t E) {
+  if (!plan || plan->P.mode != CGTP_UVU || V <= 0 || E <= 0) return nullptr;
+  if (kernel != CGTP_K_CONV_FWD && kernel != CGTP_K_CONV_BWD && kernel != CGTP_K_CONV_DBL_BWD) return nullptr;
+  const Plan& P = plan->P;
+  if (!P.k[kernel].fn) return nullptr;
+  const Kernel* rows = kernel == CGTP_K_CONV_DBL_BWD ? double_walk(P, V, E).rows : conv_by_rows(P, kernel == CGTP_K_CONV_BWD, V, E);
+  return rows ? rows->name.c_str() : P.k[kernel].name.c_str();
+}
+
 size_t cgtp_conv_double_workspace_bytes(const cgtp_plan* plan, int64_t V, int64_t E) {
   if (!plan || plan->P.mode != CGTP_UVU || V <= 0 || E <= 0 || !plan->P.k[CGTP_K_CONV_DBL_BWD].fn) return 0;
   const DoubleWalk d = double_walk(plan->P, V, E);

@@ -121,12 +121,12 @@ def test_counts_left_behind_are_none_of_the_next_call(spec_name, fill, monkeypat
 
 
 # degrees of the ordinary rows, then of a few long ones.  Rows above 2 048 take their receivers from memory, above 768 the
-# second-order kernel of fewer waves; 140 000 edges are more than 1 024 of the smallest windows; with 340 000 edges the weights
-# exceed the Infinity Cache (non-temporal streams) and 8 000 rows come in three rounds of workgroups or more
+# second-order kernel of fewer waves; 140 000 edges are more than 1 024 of the smallest windows; with 360 000 edges the weights
+# exceed the Infinity Cache (non-temporal streams) and 17 000 rows come in four rounds of workgroups or more
 @pytest.mark.parametrize("prec", ["f64", "f32"])
 @pytest.mark.parametrize("spec_name,V,degree,hubs", [("small", 2100, 3, (600, 1500, 257)), ("mul32", 2100, 3, (600, 1500, 257)), ("mul32", 1000, 5, (1200,)),
                                                      ("mul8", 900, 40, (70000, 30000)), ("small", 900, 40, (70000, 200000)),
-                                                     ("mul32", 8000, 40, (20000, 600)), ("mul96", 8000, 12, (20000, 600))])
+                                                     ("mul32", 17000, 20, (20000, 600)), ("mul96", 8000, 12, (20000, 600))])
 def test_long_rows_in_every_kind_of_row_kernel(spec_name, V, degree, hubs, prec, monkeypatch):
     """Against the walks by edge ranges in fp64 (which the oracle checks on smaller graphs), on graphs too large for the oracle."""
     from paper_2501_13986_amd import binding as b
@@ -166,6 +166,11 @@ def test_long_rows_in_every_kind_of_row_kernel(spec_name, V, degree, hubs, prec,
         torch.cuda.synchronize()
         return out
 
+    kernels = [(b.K_CONV_FWD, "cgtp_conv_fwd"), (b.K_CONV_BWD, "cgtp_conv_bwd")]
+    for k, name in kernels:
+        assert plan.conv_kernel(k, V, E) == name + "_row" and ranges.conv_kernel(k, V, E) == name
+    if prec == "f32":      # (fp64: not every plan has the registers)
+        assert plan.conv_kernel(b.K_CONV_DBL_BWD, V, E) == "cgtp_conv_dbl_row"
     want = run(ranges, torch.float64, *ins)
     for call in range(2):       # the second call finds the counters as the first one left them
         got = run(plan, torch.float64 if prec == "f64" else torch.float32, *ins)
