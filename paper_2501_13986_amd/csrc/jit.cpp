@@ -78,86 +78,49 @@ void write_file_atomic(const std::string& path, const std::vector<char>& data) {
   if (std::rename(tmp.c_str(), path.c_str()) != 0) std::remove(tmp.c_str());
 }
 
-// The run-time compiler.  A process that has loaded torch has torch's own hipRTC and code object manager in its global scope, of
-// the same names as the installed ones, and the linker would take those: the code of a plan would depend on what was imported
-// first (torch's clang 20 against the installed clang 22: uvw step of 100 000 rows 281 and 272 us, one uvw forward 732 and 600
-// bytes of private memory).  The installed compiler is therefore loaded into a namespace of its own; where that fails, the linked
-// one is used.  `id` names the compiler in the keys of the cache: both report one hipRTC version, so the code object manager, which
-// holds the compiler, is named by its file and size.
-struct Rtc {
-  decltype(&hiprtcCreateProgram) create = hiprtcCreateProgram;
-  decltype(&hiprtcCompileProgram) compile = hiprtcCompileProgram;
-  decltype(&hiprtcGetProgramLogSize) log_size = hiprtcGetProgramLogSize;
-  decltype(&hiprtcGetProgramLog) log = hiprtcGetProgramLog;
-  decltype(&hiprtcGetCodeSize) code_size = hiprtcGetCodeSize;
-  decltype(&hiprtcGetCode) code = hiprtcGetCode;
-  decltype(&hiprtcDestroyProgram) destroy = hiprtcDestroyProgram;
-  decltype(&hiprtcGetErrorString) error_string = hiprtcGetErrorString;
-  decltype(&hiprtcVersion) version = hiprtcVersion;
-  std::string id;
-
-  Rtc() {
-    void* manager = (void*)&amd_comgr_get_version;
-    if (env_int("CGTP_OWN_COMPILER", 1)) load(manager);
-    int major = 0, minor = 0;
-    (void)version(&major, &minor);
-    id = "hiprtc " + std::to_string(major) + "." + std::to_string(minor);
-    Dl_info info;
-    char path[PATH_MAX];
-    struct stat st;
-    if (dladdr(manager, &info) && info.dli_fname && realpath(info.dli_fname, path) && stat(path, &st) == 0)
-      id += std::string(" ") + (std::strrchr(path, '/') + 1) + " " + std::to_string((long long)st.st_size);
+// The compilers that code may be from, named by the files of hipRTC and of the code object manager, which holds the compiler (both
+// compilers here report one hipRTC version).  A process that has loaded torch compiles with torch's, whose libraries have the
+// names of the installed ones: first the compiler that this process uses, then the installed one.
+struct Compilers {
+  std::string own, installed;
+  Compilers() {
+    own = of_symbol((void*)&hiprtcCompileProgram) + of_symbol((void*)&amd_comgr_get_version);
+    const std::string dir = "/opt/rocm/lib/";
+    installed = of_file((dir + "libhiprtc.so." + std::to_string(HIP_VERSION_MAJOR)).c_str()) +
+                of_file((dir + "libamd_comgr.so." + std::to_string(AMD_COMGR_INTERFACE_VERSION_MAJOR)).c_str());
   }
 
  private:
-  template <class F>
-  static bool find(void* lib, const char* name, F& f) {
-    void* p = dlsym(lib, name);
-    if (p) f = (F)p;
-    return p != nullptr;
+  static std::string of_file(const char* file) {
+    char path[PATH_MAX];
+    struct stat st;
+    if (!realpath(file, path) || stat(path, &st) != 0) return std::string();
+    return std::string(std::strrchr(path, '/') + 1) + " " + std::to_string((long long)st.st_size) + " ";
   }
-  void load(void*& manager) {
-    const std::string dir = "/opt/rocm/lib/";
-    void* lib = dlmopen(LM_ID_NEWLM, (dir + "libhiprtc.so." + std::to_string(HIP_VERSION_MAJOR)).c_str(), RTLD_NOW | RTLD_LOCAL);
-    Lmid_t space;
-    if (!lib || dlinfo(lib, RTLD_DI_LMID, &space) != 0) return;
-    void* comgr = dlmopen(space, (dir + "libamd_comgr.so." + std::to_string(AMD_COMGR_INTERFACE_VERSION_MAJOR)).c_str(), RTLD_NOW | RTLD_LOCAL);
-    void* own = comgr ? dlsym(comgr, "amd_comgr_get_version") : nullptr;
-    Rtc r(*this);
-    if (!own || !find(lib, "hiprtcCreateProgram", r.create) || !find(lib, "hiprtcCompileProgram", r.compile) ||
-        !find(lib, "hiprtcGetProgramLogSize", r.log_size) || !find(lib, "hiprtcGetProgramLog", r.log) ||
-        !find(lib, "hiprtcGetCodeSize", r.code_size) || !find(lib, "hiprtcGetCode", r.code) ||
-        !find(lib, "hiprtcDestroyProgram", r.destroy) || !find(lib, "hiprtcGetErrorString", r.error_string) || !find(lib, "hiprtcVersion", r.version))
-      return;
-    *this = r;
-    manager = own;
+  static std::string of_symbol(void* p) {
+    Dl_info info;
+    return dladdr(p, &info) && info.dli_fname ? of_file(info.dli_fname) : std::string();
   }
 };
 
-const Rtc& rtc() {
-  static const Rtc* r = new Rtc;   // kept until the process ends, as the compiler's libraries are
-  return *r;
-}
-
 std::vector<char> compile(const Kernel& k) {
-  const Rtc& c = rtc();
   hiprtcProgram prog;
-  if (c.create(&prog, k.source.c_str(), (k.name + ".hip").c_str(), 0, nullptr, nullptr) != HIPRTC_SUCCESS)
+  if (hiprtcCreateProgram(&prog, k.source.c_str(), (k.name + ".hip").c_str(), 0, nullptr, nullptr) != HIPRTC_SUCCESS)
     throw std::runtime_error("hiprtcCreateProgram failed for " + k.name);
-  hiprtcResult r = c.compile(prog, kNumOptions, const_cast<const char**>(kOptions));
+  hiprtcResult r = hiprtcCompileProgram(prog, kNumOptions, const_cast<const char**>(kOptions));
   if (r != HIPRTC_SUCCESS) {
     size_t n = 0;
-    c.log_size(prog, &n);
+    hiprtcGetProgramLogSize(prog, &n);
     std::string log(n, '\0');
-    if (n) c.log(prog, &log[0]);
-    c.destroy(&prog);
-    throw std::runtime_error("hipRTC failed for " + k.name + ": " + c.error_string(r) + "\n" + log);
+    if (n) hiprtcGetProgramLog(prog, &log[0]);
+    hiprtcDestroyProgram(&prog);
+    throw std::runtime_error("hipRTC failed for " + k.name + ": " + hiprtcGetErrorString(r) + "\n" + log);
   }
   size_t n = 0;
-  c.code_size(prog, &n);
+  hiprtcGetCodeSize(prog, &n);
   std::vector<char> code(n);
-  c.code(prog, code.data());
-  c.destroy(&prog);
+  hiprtcGetCode(prog, code.data());
+  hiprtcDestroyProgram(&prog);
   return code;
 }
 
@@ -294,17 +257,24 @@ std::string jit_check_code_object(const std::string& path) {
 
 // Compiles or fetches from the cache, and checks.
 static void compile_and_check(Kernel& k) {
-  // the key covers everything that decides the code: source, options, the run-time compiler and the version of the
-  // checks a code object has to pass before it is stored
+  // the key covers everything that decides the code: source, options, the compiler and the version of the checks a code
+  // object has to pass before it is stored
+  static const Compilers* const compilers = new Compilers;
   std::string opts;
   for (int i = 0; i < kNumOptions; ++i) opts += std::string(kOptions[i]) + " ";
-  opts += rtc().id + " checks " + std::to_string(kCheckVersion) + " ";
-  char key[40];
-  std::snprintf(key, sizeof key, "%016llx", (unsigned long long)fnv1a(k.source, fnv1a(opts)));
-  std::string dir = cache_dir();
-  std::string path = dir.empty() ? std::string() : dir + "/" + k.name + "_" + key + ".hsaco";
+  const std::string dir = cache_dir();
+  auto file = [&](const std::string& compiler) {
+    char key[40];
+    std::snprintf(key, sizeof key, "%016llx",
+                  (unsigned long long)fnv1a(k.source, fnv1a(opts + compiler + "checks " + std::to_string(kCheckVersion) + " ")));
+    return dir + "/" + k.name + "_" + key + ".hsaco";
+  };
+  // Code of the installed compiler first, as build() leaves it, whatever this process would compile with (uvw step of 100 000 rows
+  // 272 us with the installed clang 22, 281 with torch's clang 20; the other kernels within 1 %).
+  const std::string path = dir.empty() ? std::string() : file(compilers->own);
   std::vector<char> code;
-  const bool cached = !path.empty() && read_file(path, code);
+  bool cached = !dir.empty() && !compilers->installed.empty() && compilers->installed != compilers->own && read_file(file(compilers->installed), code);
+  cached = cached || (!path.empty() && read_file(path, code));
   if (!cached) code = compile(k);
   // the check runs on cached objects as well (host only, milliseconds): a file written by another build of the
   // library, or damaged on disk, is screened like fresh code
