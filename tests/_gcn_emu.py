@@ -9,6 +9,8 @@ the compiler did, e.g. spill code placed where the execution mask is empty (the 
 register's old content, and an address built from it points anywhere).
 
 check(hsaco, lds_bytes, B, grid, row_words, elt) -> list of problems (empty: every access in bounds).
+check_groups(hsaco, args, grid, outputs): the same for workgroups whose waves exchange words through LDS and meet at barriers, and
+whose workgroups count in memory.
 exec_zero_windows(hsaco) -> vector instructions between the exit of a divergent loop (lanes leave at different
 times: exec &= ~done; branch back while exec != 0) and the next write to exec: they run with an empty mask.
 """
@@ -39,6 +41,13 @@ class OOB(Exception):
     pass
 
 
+class Lds:
+    """The words of a workgroup's LDS, and which of them nothing defined has been stored to."""
+    def __init__(self, size):
+        self.undefined = np.ones(size // 4 + 4, dtype=bool)
+        self.words = np.full(size // 4 + 4, 0xDEADBEE0, dtype=np.uint64)
+
+
 class Emu:
     def __init__(self, prog, lds_size, kernarg, buffers):
         self.prog = prog; self.idx = {a: i for i, (a, _, _) in enumerate(prog)}
@@ -50,6 +59,10 @@ class Emu:
         self.written = {}
 
     def run(self, wg_id, wave=0, max_steps=10_000_000):
+        for _ in self.to_barriers(wg_id, wave, Lds(self.lds_size), max_steps): pass
+
+    def to_barriers(self, wg_id, wave, lds, max_steps=10_000_000):
+        """Runs one wave; yields at every barrier."""
         # registers hold whatever the previous wave left: a value that makes any address built from it invalid
         P = 0xDEADBEE0
         self.s = np.full(128, P, dtype=np.uint64)     # 32-bit values, kept in 64-bit cells
@@ -62,7 +75,7 @@ class Emu:
         self.uv = np.ones((512, 64), dtype=bool); self.uv[0] = False
         self.ua = np.ones((512, 64), dtype=bool)
         self.uvcc = self.uexec = self.uscc = False
-        self.ulds = np.ones(self.lds_size // 4 + 4, dtype=bool)
+        self.ulds, self.lds = lds.undefined, lds.words
         self.uscratch = {}
         self.fexact = set()       # vector registers whose float value was computed exactly (cvt / rcp / mul chain of a division)
         self.s[0] = self.KA & M32; self.s[1] = self.KA >> 32; self.s[2] = wg_id
@@ -73,7 +86,8 @@ class Emu:
             steps += 1
             if steps > max_steps: raise RuntimeError("step limit")
             op, _, rest = ins.partition(" ")
-            if op == "s_endpgm": return steps
+            if op == "s_endpgm": return
+            if op == "s_barrier": yield
             nxt = pc + 1
             if self.track and ((op.startswith("s_cbranch_exec") and self.uexec) or (op.startswith("s_cbranch_vcc") and self.uvcc)
                                or (op.startswith("s_cbranch_scc") and self.uscc)):
@@ -200,6 +214,11 @@ class Emu:
                 return struct.unpack_from("<%dI" % ndw, t[3], a - t[0])
         return None
 
+    def keep(self, a, words):           # stores into a buffer whose contents change (a bytearray)
+        for t in self.buffers:
+            if len(t) > 3 and isinstance(t[3], bytearray) and t[0] <= a and a + 4 * len(words) <= t[0] + t[1]:
+                struct.pack_into("<%dI" % len(words), t[3], a - t[0], *words)
+
     def check_global(self, addr_txt, ins, addrs, size, m):
         for lane in np.flatnonzero(m):
             a = int(addrs[lane])
@@ -316,6 +335,11 @@ class Emu:
             elif (self.U(o[1]) & m).any():
                 self.note(f"{addr:x}: {ins}: stores a value derived from an undefined register or lane (lane {int(np.flatnonzero(self.U(o[1]) & m)[0])})")
             return
+        if op == "global_atomic_cmpswap_x2":
+            if ((self.U(o[1]) | self.U(o[2]) | (np.zeros(64, dtype=bool) if o[3] == "off" else self.U(o[3]))) & m).any():
+                self.note(f"{addr:x}: {ins}: address or value derived from an undefined register or lane")
+            self.setU(o[0], np.zeros(64, dtype=bool))
+            return
         if op.startswith(("ds_read", "ds_write")):
             rd = op.startswith("ds_read")
             at = o[1] if rd else o[0]
@@ -406,6 +430,8 @@ class Emu:
                 A, Bv = self.rd_s32(o[0]), self.rd_s32(o[1])
                 if mm.group(2) == "i32": A, Bv = (t - (1 << 32) if t >= (1 << 31) else t for t in (A, Bv))
             self.scc = int({"eq": A == Bv, "lg": A != Bv, "gt": A > Bv, "ge": A >= Bv, "lt": A < Bv, "le": A <= Bv}[mm.group(1)])
+        elif op == "s_abs_i32":
+            t = self.rd_s32(o[1]); t = (1 << 32) - t if t >= (1 << 31) else t; self.wr_s32(o[0], t); self.scc = int(t != 0)
         elif op == "s_min_u32": A, Bv = self.rd_s32(o[1]), self.rd_s32(o[2]); self.wr_s32(o[0], min(A, Bv)); self.scc = int(A < Bv)
         elif op == "s_max_u32": A, Bv = self.rd_s32(o[1]), self.rd_s32(o[2]); self.wr_s32(o[0], max(A, Bv)); self.scc = int(A > Bv)
         elif op == "s_min_i32" or op == "s_max_i32":
@@ -421,6 +447,9 @@ class Emu:
         elif op == "s_mul_hi_i32":
             sg = lambda t: t - (1 << 32) if t >= (1 << 31) else t
             self.wr_s32(o[0], ((sg(self.rd_s32(o[1])) * sg(self.rd_s32(o[2]))) >> 32) & M32)
+        elif re.fullmatch(r"s_cmpk_(eq|lg|gt|ge|lt|le)_u32", op):
+            A, k = self.rd_s32(o[0]), self.lit(o[1]) & 0xFFFF
+            self.scc = int({"eq": A == k, "lg": A != k, "gt": A > k, "ge": A >= k, "lt": A < k, "le": A <= k}[op[7:9]])
         elif op in ("s_cmpk_eq_i32", "s_cmpk_lg_i32"):
             k = self.lit(o[1]); k = (k - 0x10000 if k >= 0x8000 else k) & M32
             self.scc = int((self.rd_s32(o[0]) == k) == (op == "s_cmpk_eq_i32"))
@@ -484,6 +513,8 @@ class Emu:
         elif op in ("v_cvt_f32_u32_e32", "v_cvt_f32_i32_e32"):
             src = self.rd_v32(o[1]); src = self.s32(src) if "i32" in op else src.astype(np.int64)
             self.wr_v(o[0], src.astype(np.float32).view(np.uint32).astype(u64)); self.fexact.add(o[0])
+        elif op == "v_cvt_f32_ubyte0_e32":
+            self.wr_v(o[0], (self.rd_v32(o[1]) & u64(255)).astype(np.float32).view(np.uint32).astype(u64)); self.fexact.add(o[0])
         elif op == "v_rcp_iflag_f32_e32" and o[1] in self.fexact:
             f_ = self.rd_v32(o[1]).astype(np.uint32).view(np.float32)
             with np.errstate(all="ignore"): r_ = (np.float32(1) / f_).astype(np.float32)
@@ -492,6 +523,17 @@ class Emu:
             f1, f2 = (self.rd_v32(t).astype(np.uint32).view(np.float32) for t in o[1:])
             with np.errstate(all="ignore"): self.wr_v(o[0], (f1 * f2).astype(np.float32).view(np.uint32).astype(u64))
             self.fexact.add(o[0])
+        elif op == "v_trunc_f32_e32" and o[1] in self.fexact:
+            f_ = np.trunc(self.rd_v32(o[1]).astype(np.uint32).view(np.float32))
+            self.wr_v(o[0], f_.view(np.uint32).astype(u64)); self.fexact.add(o[0])
+        elif op == "v_fma_f32" and all(t.lstrip("-") in self.fexact for t in o[1:]):      # (the remainder of a division)
+            f1, f2, f3 = ((-1 if t[0] == "-" else 1) * self.rd_v32(t.lstrip("-")).astype(np.uint32).view(np.float32).astype(np.float64) for t in o[1:])
+            self.wr_v(o[0], (f1 * f2 + f3).astype(np.float32).view(np.uint32).astype(u64)); self.fexact.add(o[0])
+        elif re.fullmatch(r"v_cmp_(gt|lt|ge|le|eq)_f32_e64", op) and all(t.strip("|") in self.fexact for t in o[1:]):
+            A, Bv = (self.rd_v32(t.strip("|")).astype(np.uint32).view(np.float32) for t in o[1:])
+            A, Bv = (np.abs(f_) if t[0] == "|" else f_ for f_, t in ((A, o[1]), (Bv, o[2])))
+            res = {"gt": A > Bv, "lt": A < Bv, "ge": A >= Bv, "le": A <= Bv, "eq": A == Bv}[op[6:8]]
+            self.wr_s64(o[0], self.bits(res & self.mask()))
         elif op in ("v_cvt_u32_f32_e32", "v_cvt_i32_f32_e32"):
             if o[1] not in self.fexact: raise NotImplementedError("integer from a floating-point value that was not evaluated: " + ins)
             f_ = self.rd_v32(o[1]).astype(np.uint32).view(np.float32).astype(np.float64)
@@ -593,6 +635,18 @@ class Emu:
             res = {"gt": A > Bv, "lt": A < Bv, "ge": A >= Bv, "le": A <= Bv, "eq": A == Bv, "ne": A != Bv}[mm.group(1)]
             self.wr_s64(dst, self.bits(res & self.mask()))
         # ---------------- memory
+        elif op == "global_atomic_cmpswap_x2":      # returns the old value (sc0); data: new, then expected
+            assert "sc0" in rest, ins
+            addrs = self.rd_v64(o[1]) if o[3] == "off" else self.rd_v32(o[1]) + u64(self.rd_s64(o[3]))
+            addrs = (addrs.astype(np.int64) + self.lit(mods.get("offset", "0"))).astype(u64)
+            self.check_global(addr, ins, addrs, 8, self.mask())
+            d, s_ = self.rng(o[0]), self.rng(o[2])
+            for lane in np.flatnonzero(self.mask()):
+                old = self.fetch(int(addrs[lane]), 2)
+                assert old is not None, "atomic on a buffer without contents: " + ins
+                new, want = ([int(self.v[s_[1] + k][lane]) for k in pair] for pair in ((0, 1), (2, 3)))
+                if list(old) == want: self.keep(int(addrs[lane]), new)
+                self.v[d[1]][lane], self.v[d[1] + 1][lane] = old
         elif op.startswith("global_load") or op.startswith("global_store"):
             n = {"dword": 1, "dwordx2": 2, "dwordx3": 3, "dwordx4": 4}[op.split("_")[-1]]
             load_ = op.startswith("global_load")
@@ -603,7 +657,11 @@ class Emu:
             else: addrs = self.rd_v32(at) + u64(self.rd_s64(sa))
             addrs = (addrs.astype(np.int64) + off).astype(u64)
             self.check_global(addr, ins, addrs, 4 * n, self.mask())
-            if not load_: self.mark_written(addrs, 4 * n, self.mask())
+            if not load_:
+                self.mark_written(addrs, 4 * n, self.mask())
+                if any(len(t) > 3 and isinstance(t[3], bytearray) for t in self.buffers):
+                    r = self.rng(o[1]); f = self.v if r[0] == "v" else self.a
+                    for lane in np.flatnonzero(self.mask()): self.keep(int(addrs[lane]), [int(f[r[1] + k][lane]) for k in range(n)])
             if load_:
                 self.wr_zero(o[0])
                 if any(len(t) > 3 and t[3] is not None for t in self.buffers):      # integer arrays: real values
@@ -619,12 +677,20 @@ class Emu:
             if re.search(r"2(st64)?_b(32|64)$", op):
                 el = 8 if "b64" in op else 4
                 unit = el * (64 if "st64" in op else 1)
-                for key in ("offset0", "offset1"):
-                    self.check_lds(addr, ins, (base + u64(self.lit(mods.get(key, "0")) * unit)) & u64(M32), el, self.mask())
+                offs = [self.lit(mods.get(key, "0")) * unit for key in ("offset0", "offset1")]
             else:
                 el = {"b32": 4, "b64": 8, "b96": 12, "b128": 16}[op.split("_")[-1]]
-                self.check_lds(addr, ins, (base + u64(self.lit(mods.get("offset", "0")))) & u64(M32), el, self.mask())
-            if rd: self.wr_zero(o[0])
+                offs = [self.lit(mods.get("offset", "0"))]
+            m = self.mask()
+            for t, off in enumerate(offs):
+                at_ = (base + u64(off)) & u64(M32)
+                self.check_lds(addr, ins, at_, el, m)
+                r = self.rng(o[0] if rd else o[1 + t]); f = self.v if r[0] == "v" else self.a
+                w = (at_ >> u64(2)).astype(np.int64)
+                for k in range(el // 4):
+                    if rd: f[r[1] + (t * (el // 4)) + k][m] = self.lds[w[m] + k]
+                    else: self.lds[w[m] + k] = f[r[1] + k][m]
+            if rd: self.fexact.discard(o[0])
         elif op.startswith("scratch_store") or op.startswith("scratch_load"):
             # private memory, one copy per lane, addressed by immediate offset (+ scalar offset): values are kept exactly
             n = {"dword": 1, "dwordx2": 2, "dwordx3": 3, "dwordx4": 4}[op.split("_")[-1]]
@@ -691,6 +757,49 @@ def check_args(hsaco, lds_bytes, args, grid, waves=1):
             except OOB:
                 return emu.problems
     return emu.problems
+
+
+def metadata(hsaco, key):
+    """An unsigned entry of the kernel's metadata (MessagePack: a short string, then the number)."""
+    code = open(hsaco, "rb").read()
+    at = code.index(bytes([0xa0 | len(key)]) + key.encode()) + 1 + len(key)
+    width = {0xcc: 1, 0xcd: 2, 0xce: 4, 0xcf: 8}.get(code[at])
+    return code[at] if width is None else int.from_bytes(code[at + 1:at + 1 + width], "big")
+
+
+def check_groups(hsaco, args, grid, outputs=(), order=None):
+    """As check_args(), for workgroups whose waves cooperate (LDS contents and barriers are emulated; workgroups run one after the
+    other in `order`).  ("count", bytearray): a buffer of integers that the kernel changes.  `outputs`: arguments every byte of
+    which the kernel has to write."""
+    prog, waves, lds_bytes = load(hsaco), metadata(hsaco, ".max_flat_workgroup_size") // 64, metadata(hsaco, ".group_segment_fixed_size")
+    bufs, ka = [], b""
+    for i, a in enumerate(args):
+        base = 0x1000_0000_0000 + i * 0x10_0000_0000
+        if a[0] == "buf": bufs.append((base, a[1], f"arg{i}", np.ascontiguousarray(a[2]).tobytes() if len(a) > 2 else None)); ka += struct.pack("<Q", base)
+        elif a[0] == "count": bufs.append((base, len(a[1]), f"arg{i}", a[1])); ka += struct.pack("<Q", base)
+        else: ka += struct.pack({"null": "<Q", "i64": "<q", "i32": "<i"}[a[0]], a[1] if len(a) > 1 else 0)
+        if a[0] != "i32": assert len(ka) % 8 == 0
+    ka += b"\0" * (-len(ka) % 8)
+    hidden = struct.pack("<IIIHHH", grid, 1, 1, 64 * waves, 1, 1)
+    ka += hidden + b"\0" * (256 - len(hidden))
+    problems, written = [], {}
+    for wg in (range(grid) if order is None else order):
+        lds, running = Lds(lds_bytes), []
+        for wave in range(waves):
+            emu = Emu(prog, lds_bytes, ka, bufs)
+            emu.problems, emu.written = problems, written
+            running.append(emu.to_barriers(wg, wave, lds))
+        try:
+            while running:
+                ended = [next(g, "end") == "end" for g in running]
+                if any(ended) != all(ended): problems.append(f"workgroup {wg}: waves {np.flatnonzero(ended)} ended where others wait at a barrier"); return problems
+                if all(ended): break
+        except OOB:
+            return problems
+    for i in outputs:
+        w = written.get(f"arg{i}", np.zeros(args[i][1], dtype=bool))
+        if not w.all(): problems.append(f"output argument {i}: byte {int(np.flatnonzero(~w)[0])} is never written")
+    return problems
 
 
 def exec_zero_windows(hsaco):

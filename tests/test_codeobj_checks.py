@@ -188,6 +188,65 @@ def test_compiled_convolution_kernels(tmp_path, kernel, monkeypatch):
         assert problems and "outside every buffer" in problems[0], problems[:2]
 
 
+ROW_PLANS = {
+    # the benchmark's irreps; degrees of its rows: none, one worker's, over two windows
+    "mace": ("128x0e+128x1o+128x2e", "1x0e+1x1o+1x2e+1x3o", "128x0e+128x1o+128x2e+128x3o", b.CGTP_F32, [0, 3, 10]),
+    # rows that end inside a vector; exactly a window, over four and over two, which meet in a window
+    "workers_share_waves": ("5x0e+5x1o", "1x0e+1x1o", "5x0e+5x1o+5x1e", b.CGTP_F64, [0, 3, 8, 21, 13, 1, 0]),
+}
+
+
+@pytest.mark.parametrize("kernel", ["cgtp_conv_fwd_row", "cgtp_conv_bwd_row", "cgtp_conv_dbl_row", "cgtp_conv_row_sums"])
+@pytest.mark.parametrize("name", list(ROW_PLANS))
+def test_compiled_row_kernels(tmp_path, name, kernel, monkeypatch):
+    """The kernels with a workgroup per row, all compiled variants, with windows of eight edges.  Every byte of every output is
+    written, and the counters of the long rows are zero again, whichever workgroup comes last and whatever an earlier call left
+    in them.  With one node index out of range the gather must be reported."""
+    import numpy as np
+    import struct
+    from oracle import conv as oconv
+    monkeypatch.setenv("CGTP_CACHE_DIR", str(tmp_path))
+    ix, iy, iz, dt, deg = ROW_PLANS[name]
+    p = b.Plan(ix, iy, iz, dtype=dt, device=-2)
+    lg, el = 3, 8 if dt == b.CGTP_F64 else 4
+    V, E = len(deg), sum(deg)
+    rng = np.random.default_rng(5)
+    recv, send = np.repeat(np.arange(V), deg), rng.permutation(np.repeat(np.arange(V), deg))
+    row_ptr, col, perm, t_row_ptr, t_perm = oconv.csr_from_coo(recv.astype(np.int64), send.astype(np.int64), V)
+    t_recv = oconv.rows_of_edges(row_ptr)[t_perm].astype(np.int64)
+    x, y, w, z = p.dim_x, p.dim_y, p.n_w, p.dim_z
+    windows = (E - 1 >> lg) + 1
+    i64 = lambda a: ("buf", a.size * 8, a)
+    buf = lambda rows, words: ("buf", rows * words * el)
+
+    def args(counts, col_=col, perm_=t_perm, looked_up=False):
+        tail = lambda words: [("i64", V), buf(2 * windows, words), ("count", counts), ("i32", 7), ("i32", lg)]
+        if kernel == "cgtp_conv_fwd_row":
+            return [buf(V, x), buf(E, y), buf(E, w), buf(V, z), i64(row_ptr), i64(col_)] + tail(z) + [("null",)], (3,)
+        if kernel == "cgtp_conv_bwd_row":
+            return [buf(V, x), buf(E, y), buf(E, w), buf(V, z), buf(V, x), buf(E, y), buf(E, w), i64(t_row_ptr), i64(perm_), i64(row_ptr),
+                    i64(t_recv) if looked_up else ("null",)] + tail(x) + [("null",)], (4, 5, 6)
+        if kernel == "cgtp_conv_dbl_row":
+            return [buf(V, x), buf(E, y), buf(E, w), buf(V, z), buf(V, x), buf(E, y), buf(E, w), buf(E, x), buf(E, y), buf(E, w), buf(V, z),
+                    i64(row_ptr), i64(col_)] + tail(z), (7, 8, 9, 10)
+        return [buf(E, x), buf(V, x), i64(t_row_ptr), i64(perm_)] + tail(x), (1,)
+    grid = V + windows - 1
+    files = [f for f in glob.glob(os.path.join(str(tmp_path), kernel + "_*.hsaco")) if len(os.path.basename(f)) == len(kernel) + 23]
+    assert files
+    for f in files:
+        assert _gcn_emu.exec_zero_windows(f) == []
+        for fill, order, looked_up in ((0, None, False), (0x0101010101010101, range(grid - 1, -1, -1), True)):
+            counts = bytearray(struct.pack("<Q", fill) * windows)
+            a, outputs = args(counts, looked_up=looked_up)
+            assert _gcn_emu.check_groups(f, a, grid, outputs, order) == []
+            after = np.frombuffer(bytes(counts), dtype=np.uint64)
+            assert (after[after != fill] == 0).all() and (after == 0).any(), after
+        bad_col, bad_perm = col.copy(), t_perm.copy()
+        bad_col[E // 2] = V; bad_perm[E // 2] = E
+        problems = _gcn_emu.check_groups(f, args(bytearray(8 * windows), bad_col, bad_perm)[0], grid)
+        assert problems and "outside every buffer" in problems[0], problems[:2]
+
+
 HAZARD_ASM = """
 	.text
 	.globl	probe
