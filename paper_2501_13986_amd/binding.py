@@ -248,8 +248,8 @@ def conv_backward_perm(plan: Plan, x_nodes, y_edges, W_edges, gz_nodes, gx_nodes
 def conv_double_backward(plan: Plan, x_nodes, y_edges, W_edges, gz_nodes, La_nodes, Lb_edges, LC_edges, Lx_nodes, Ly_edges,
                          LW_edges, Lgz_nodes, row_ptr, col, t_row_ptr, t_perm):
     """The memory of the one walk is torch's for the time of the call: shared by all plans, given back to its allocator on the
-    current stream, part of a captured graph's pool where the call is captured.  Where torch has none left the pass goes in
-    two walks, whose sums are in another order."""
+    current stream, part of the graph's pool under torch.cuda.graph.  Where torch has none left the pass goes in two walks, whose
+    sums are in another order."""
     V, E = x_nodes.shape[0], y_edges.shape[0]
     L, scratch = lib(), None
     n = L.cgtp_conv_double_workspace_bytes(plan._h, V, E) if E >= 1024 else 0   # the rows of fewer edges fit the plan's workspace

@@ -416,7 +416,7 @@ DoubleWalk double_walk(const Plan& P, int64_t V, int64_t E) {
   d.ws = std::max((size_t)d.nf * 2 * P.dim_z() * el, d.part_b + receivers * 8);
   const LaneMap& m = P.map[CGTP_K_CONV_DBL_BWD];
   const bool few_channels = m.G * m.cpl * (int64_t)el < 128;
-  if (!few_channels && !cgtp::double_by_rows(V, E, resident_groups(P, P.k_dbl_row[1]))) return d;
+  if (!few_channels && !cgtp::double_by_rows(V, E, resident_groups(P, P.k_dbl_row[1]), m.spw)) return d;
   if (!rows_launch(P.k_dbl_row[0], V) || !rows_launch(P.k_row_sums, V) || (size_t)E > ((size_t)4 << 30) / (P.dim_x() * el)) return d;
   d.row_bytes = round_up((size_t)E * P.dim_x() * el, 256);
   d.rows = &P.k_dbl_row[V <= 768 ? 0 : 3 * E * P.n_w * (int64_t)el > (int64_t)256 << 20 ? 2 : 1];

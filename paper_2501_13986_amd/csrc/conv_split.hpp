@@ -54,11 +54,14 @@ inline int64_t most_pieces(int64_t all, int spw, std::initializer_list<int64_t> 
 // edge cost little again.)  us, ranges -> rows.  Forward, 128 channels, 20 000 nodes: degree 0.1 82 -> 54, 0.5 84 -> 98, 1
 // 96 -> 128, 2 130 -> 158, 4 210 -> 212, 7 328 -> 298; 9 000 nodes of degree 2 71 -> 69; 96 channels, 20 000 of
 // degree 4 83 -> 90; 32 channels fp64, 20 000 of degree 2 80 -> 110, 9 000 52 -> 43.
-// Second order, 128 channels (512 resident), 9 000 nodes: degree 1 162 -> 185, 4 422 -> 380; 20 000 of degree 0.1 160 -> 138, 0.25
-// 169 -> 196; 5 000 of degree 1 101 -> 103; 32 channels (1 024 resident), 20 000 nodes: degree 1 110 -> 134, 2 163 -> 190, 4 269 -> 266;
-// 9 000 of degree 1 73 -> 59.
+// Second order, 128 channels (512 resident), 9 000 nodes: degree 1 162 -> 185, 3 339 -> 311; 20 000 of degree 0.1 160 -> 138, 0.25
+// 169 -> 196, 2 560 -> 535; 5 000 of degree 1 101 -> 103, 7 000 134 -> 149; 96 channels (768) 9 000 of degree 1 76 -> 54, 20 000 125 -> 139,
+// of degree 2 189 -> 180.  Where workers share waves, 32 channels (1 024), 20 000 nodes: degree 2 163 -> 190, 3 212 -> 220, 4 269 -> 266;
+// 12 000 of degree 1 79 -> 77.
 inline bool forward_by_rows(int64_t V, int64_t E) { return V <= 10000 || E / 5 >= V || E <= V / 8; }
-inline bool double_by_rows(int64_t V, int64_t E, int64_t resident) { return V <= 10 * resident || E / 4 >= V || E <= V / 8; }
+inline bool double_by_rows(int64_t V, int64_t E, int64_t resident, int spw) {
+  return V <= 12 * resident || E / (spw > 1 ? 4 : 2) >= V || E <= V / 8;
+}
 
 // The backward, whose weights come in the order of the senders: 0 by ranges, 1 by rows, 2 by rows with non-temporal streams.
 //  - Where several workers' weights share a cache line (`few_channels`: 4 channels, 20 000 nodes of degree 32, 178 -> 97 us; degree

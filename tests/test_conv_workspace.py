@@ -65,23 +65,26 @@ int main() {
   char op[8];
   long long few, f64, cpl, spw, many, res, nt, V, E, word;
   while (std::scanf("%7s %lld %lld %lld %lld %lld %lld %lld %lld %lld %lld", op, &few, &f64, &cpl, &spw, &many, &res, &nt, &V, &E, &word) == 11)
-    std::printf("%d\n", !std::strcmp(op, "fwd") ? (int)forward_by_rows(V, E) : !std::strcmp(op, "dbl") ? (int)double_by_rows(V, E, nt)
+    std::printf("%d\n", !std::strcmp(op, "fwd") ? (int)forward_by_rows(V, E) : !std::strcmp(op, "dbl") ? (int)double_by_rows(V, E, nt, (int)spw)
                       : backward_by_rows({few != 0, f64 != 0, (int)cpl, (int)spw, many != 0, res, nt}, V, E, E * word));
 }
 '''
-# few channels, fp64, channels per lane, workers per wave, more than 128 registers, workgroups resident (plain, non-temporal), then
-# bytes of an edge's weights
+# few channels, fp64, channels per lane, workers per wave, more than 128 registers, workgroups resident (plain; non-temporal, for "dbl"
+# of the second-order kernel), then bytes of an edge's weights
 PLAN = {"mace": ((0, 0, 2, 1, 1, 256, 768), 8704), "mul96": ((0, 0, 2, 1, 0, 512, 1280), 2688), "mul32": ((0, 0, 1, 2, 0, 1024, 2048), 2176),
-        "mul32_f64": ((0, 1, 1, 2, 1, 512, 1024), 4352), "tiny": ((1, 0, 1, 16, 0, 1024, 1024), 96)}
+        "mul32_f64": ((0, 1, 1, 2, 1, 512, 1024), 4352), "tiny": ((1, 0, 1, 16, 0, 1024, 1024), 96), "mace_dbl": ((0, 0, 1, 1, 1, 512, 512), 8704),
+        "mul96_dbl": ((0, 0, 1, 1, 1, 768, 768), 2688), "mul32_dbl": ((0, 0, 1, 2, 1, 1024, 1024), 2176)}
 # measured on both sides of each line: 0 by ranges, 1 by rows, 2 by rows with non-temporal streams
 MEASURED = [("fwd", "mace", 20000, 0.1, 1), ("fwd", "mace", 20000, 1, 0), ("fwd", "mace", 20000, 7, 1), ("fwd", "mul32_f64", 20000, 2, 0),
-            ("fwd", "mul32_f64", 9000, 2, 1), ("dbl", "mace", 300, 0.5, 1), ("dbl", "mace", 20000, 1, 0), ("dbl", "mace", 20000, 0.1, 1),
-            ("dbl", "mace", 9000, 4, 1), ("dbl", "mul32", 9000, 1, 1), ("bwd", "mace", 300, 2, 1), ("bwd", "mace", 800, 2, 0),
+            ("fwd", "mul32_f64", 9000, 2, 1), ("dbl", "mace_dbl", 300, 0.5, 1), ("dbl", "mace_dbl", 20000, 1, 0), ("dbl", "mace_dbl", 20000, 0.1, 1),
+            ("dbl", "mace_dbl", 9000, 3, 1), ("dbl", "mace_dbl", 7000, 1, 0), ("dbl", "mul96_dbl", 9000, 1, 1), ("dbl", "mul96_dbl", 20000, 1, 0),
+            ("dbl", "mul96_dbl", 20000, 2, 1), ("dbl", "mul32_dbl", 12000, 1, 1), ("dbl", "mul32_dbl", 20000, 3, 0), ("dbl", "mul32_dbl", 20000, 4, 1),
+            ("bwd", "mace", 300, 2, 1), ("bwd", "mace", 800, 2, 0),
             ("bwd", "mace", 20000, 0.1, 0), ("bwd", "mace", 20000, 2, 0), ("bwd", "mace", 20000, 40, 2), ("bwd", "mace", 2000, 32, 0),
             ("bwd", "mul96", 1500, 1, 1), ("bwd", "mul96", 9000, 4, 0), ("bwd", "mul96", 3300, 6, 1), ("bwd", "mul32", 5000, 1, 1),
             ("bwd", "mul32", 20000, 2, 0), ("bwd", "mul32", 3000, 18, 1), ("bwd", "mul32_f64", 800, 1, 1), ("bwd", "mul32_f64", 5000, 3, 0),
             ("bwd", "mul32_f64", 12000, 36, 2), ("bwd", "tiny", 20000, 0.5, 1), ("fwd", "mul96", 20000, 4, 0),
-            ("dbl", "mace", 20000, 0.25, 0), ("bwd", "mul32", 9000, 7, 2)]
+            ("dbl", "mace_dbl", 20000, 0.25, 0), ("bwd", "mul32", 9000, 7, 2)]
 
 
 def test_rows_of_few_edges_go_by_ranges_where_those_are_faster(tmp_path):
